@@ -523,7 +523,8 @@ qc_status qc_grain_set_adjoint_checkpoint(qc_grain* grain, int every);
 
 /* Launch shape of the sweep kernel: energies handled by each lane (1, 2, 3,
  * 4 or 8; 0 = automatic: the fewest padded energy slots weighted by each
- * variant's measured cost).  The lanes of one trajectory segment share the
+ * variant's measured cost, and 2 instead of 4 in a launch that leaves wave
+ * slots empty).  The lanes of one trajectory segment share the
  * per-node energy sums, so fewer energies per lane means more lanes per
  * segment (a power of two up to 64; a forced value that would need more, or
  * that exceeds the number of energies of a launch, is replaced by the
@@ -536,11 +537,13 @@ qc_status qc_grain_get_lanes(const qc_grain* grain, int* energies_per_lane, int*
 
 /* Split launch shape of the SCF sweep (Matsubara poles).  Segments are
  * launched longest first.  When a launch fills the device's wave slots less
- * than twice, its longest segments set its length; with an even number of
+ * than six times, its longest segments finish last; with an even number of
  * energies per lane and twice the lanes still within 64, the segments longer
- * than frac x the longest then march with twice the lanes and half the
- * energies per lane (rounded up to whole waves).  frac in [0, 1]; 0 turns
- * the split off; the default is 0.8.  Results are identical up to the order
+ * than frac x the longest (at most a 16th of all, a 64th at two energies
+ * per lane) then march with twice the lanes and half the energies per lane
+ * (rounded up to whole waves), and all of them do in a launch that leaves
+ * wave slots empty.  frac in [0, 1]; 0 turns the split
+ * off; the default is 0.8.  Results are identical up to the order
  * of the FP64 pole sums.  Errors: QC_ERR_INVALID for frac outside [0, 1]. */
 qc_status qc_grain_set_split(qc_grain* grain, double frac);
 /* The fraction set and the number of segments the next SCF sweep launches

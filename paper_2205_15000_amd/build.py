@@ -20,6 +20,10 @@ COMMON = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # packed FP32 instructions stay off (see the design notes)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # and with them pairs of scalars gain nothing as vectors: vectorised, the
+    # same expression would be fused (rounded) differently from one energies-
+    # per-lane variant of a kernel to another
+    "-fno-slp-vectorize",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
     "-Wall", "-Wno-unused-result",
 ]

@@ -88,14 +88,17 @@ int lanes_for(int n_e, int epl) {
 }
 
 // Energies per lane: a forced value (1, 2, 3, 4, 8) if it fits 64 lanes and
-// does not exceed the energies, else the shape with the least cost G * epl * f(epl), i.e. energy slots
-// (padding included) weighted by the measured relative cost per slot of
-// each variant on gfx950 (64- and 48-pole grains).  Two per lane for 64
-// poles, three for 48, four for 256-energy blocks (both precisions).
+// does not exceed the energies, else the shape with the least cost
+// G * epl * f(epl), i.e. energy slots (padding included) weighted by the
+// relative time per slot of each variant in a launch that fills the device.
+// Measured with the Matsubara sweep of the 400 x 400 square (64 poles; three
+// per lane pads to 96 slots): mixed 1.14, 1.05, 1.39, 0.99, 1.20 ms and FP64
+// 2.32, 2.05, 2.87, 2.09, 2.30 ms for 1, 2, 3, 4, 8 per lane.  Four per lane
+// for 64 poles in mixed precision, two in FP64, three for 48 in both.
 void lane_shape(int n_e, int force, bool fp32, int& G, int& epl) {
   static const int kEpl[5] = {1, 2, 3, 4, 8};
-  static const double kCost32[5] = {1.13, 1.0, 1.28, 1.15, 1.55};
-  static const double kCost64[5] = {1.07, 1.0, 1.20, 1.12, 1.24};
+  static const double kCost32[5] = {1.08, 1.0, 0.88, 0.95, 1.14};
+  static const double kCost64[5] = {1.13, 1.0, 0.94, 1.02, 1.13};
   const double* kCost = fp32 ? kCost32 : kCost64;
   if ((force == 1 || force == 2 || force == 3 || force == 4 || force == 8) && force <= n_e &&
       lanes_for(n_e, force) <= 64) {
@@ -295,7 +298,7 @@ struct qc_grain {
   // device's wave slots per (precision, energies per lane), found on first use
   std::vector<int32_t> len_order, len_order_pair;
   double split_frac = 0.8;
-  int64_t wave_slots[9] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};
+  mutable int64_t wave_slots[9] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};
   void* gbuf = nullptr;
   double* node_out = nullptr;
   void* bc[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
@@ -570,6 +573,30 @@ void do_interp(qc_grain* g, const double* delta, const double* A, hipStream_t st
     qc::launch_interp<double>(a, cells, g->nodes, st);
 }
 
+// the device's wave slots for the Matsubara sweep kernel (resident waves),
+// found on first use
+int64_t wave_slots(const qc_grain* g, int epl) {
+  int64_t& slots = g->wave_slots[epl];
+  if (slots < 0)
+    slots = g->precision == QC_MIXED ? qc::sweep_wave_slots<float>(epl) : qc::sweep_wave_slots<double>(epl);
+  return slots;
+}
+// waves of a sweep launch: two (one per direction) for each 64/G segments
+int64_t sweep_waves(int64_t nseg, int G) { return 2 * ((nseg * G + 63) / 64); }
+
+// Lane shape of a sweep over nseg segments of a grain: lane_shape's, except
+// that a launch whose waves would leave wave slots empty at four energies per
+// lane takes two (its time is then the chain of steps of one wave, which
+// grows with the energies per lane: 32 x 32 disc, FP64, 17, 21 and 30 us for
+// 1, 2 and 4 per lane)
+void grain_shape(const qc_grain* g, int n_e, int64_t nseg, int& G, int& epl) {
+  lane_shape(n_e, g->epl_override, g->precision == QC_MIXED, G, epl);
+  if (epl == 4 && epl != g->epl_override && lanes_for(n_e, 2) <= 64 && sweep_waves(nseg, G) < wave_slots(g, epl)) {
+    epl = 2;
+    G = lanes_for(n_e, 2);
+  }
+}
+
 // arguments of a sweep over every segment, or (pair) over the segments of
 // the lower angles of the angle pairs
 qc::SweepArgs sweep_args(qc_grain* g, int n_e, int n_e_tot, int e_off, const double* eps, const double* rp,
@@ -578,8 +605,7 @@ qc::SweepArgs sweep_args(qc_grain* g, int n_e, int n_e_tot, int e_off, const dou
   pair = pair && g->pairing;
   a.nseg = pair ? g->nseg_pair : g->nseg;
   a.order = pair ? g->order_pair : g->order;
-  int epl;
-  lane_shape(n_e, g->epl_override, g->precision == QC_MIXED, a.G, epl);
+  grain_shape(g, n_e, a.nseg, a.G, a.epl);
   a.log2g = ilog2(a.G);
   a.n_e = n_e;
   a.n_e_tot = n_e_tot;
@@ -605,32 +631,37 @@ qc::SweepArgs sweep_args(qc_grain* g, int n_e, int n_e_tot, int e_off, const dou
 }
 
 // Segments of a Matsubara sweep that take the wide lane shape (2G lanes,
-// EPL/2 energies per lane; see SweepArgs::nlong): only when the launch
-// fills the device's wave slots less than twice, so that its longest
-// segments set its length, and then those longer than split_frac x the
-// longest, rounded up to whole waves
-int64_t split_count(qc_grain* g, const qc::SweepArgs& a, int epl) {
-  if (!(g->split_frac > 0.0) || epl % 2 != 0 || 2 * a.G > 64 || a.nseg == 0) return 0;
+// EPL/2 energies per lane; see SweepArgs::nlong).  A launch that leaves wave
+// slots empty takes it for all of them: its time is the chain of one wave's
+// steps, shorter with fewer energies per lane (600 x 600 disc, 16 poles,
+// FP64: 662 -> 566 us; 32 x 32 disc: 21 -> 17 us).  One that fills the slots
+// less than six times takes it for the segments longer than split_frac x the
+// longest, which otherwise finish last, rounded up to whole waves; beyond
+// that the last round weighs too little.  At most a 16th of the segments at
+// four per lane and more (400 x 400 square, mixed: 978 us without, 963 with a
+// 16th, 1018 with a sixth of them wide), a 64th at two per lane, since one
+// per lane costs more per energy (FP64: 2022 us without, 2026 with a 64th,
+// 2068 with an eighth).
+int64_t split_count(qc_grain* g, const qc::SweepArgs& a) {
+  if (!(g->split_frac > 0.0) || a.epl % 2 != 0 || 2 * a.G > 64 || a.nseg == 0) return 0;
   const std::vector<int32_t>& len = a.order == g->order_pair && g->order_pair ? g->len_order_pair : g->len_order;
   if (static_cast<int64_t>(len.size()) != a.nseg) return 0;
-  int64_t& slots = g->wave_slots[epl];
-  if (slots < 0)
-    slots = g->precision == QC_MIXED ? qc::sweep_wave_slots<float>(epl) : qc::sweep_wave_slots<double>(epl);
-  const int64_t waves = (a.nseg * a.G + 63) / 64;
-  if (slots <= 0 || waves >= 2 * slots) return 0;
+  const int64_t slots = wave_slots(g, a.epl), waves = sweep_waves(a.nseg, a.G);
+  if (slots <= 0 || waves >= 6 * slots) return 0;
+  if (waves < slots) return a.nseg;
   const double cut = g->split_frac * len[0];
   int64_t k = 0;
   while (k < a.nseg && len[k] > cut) ++k;
+  k = std::min(k, std::max<int64_t>(a.nseg / (a.epl >= 4 ? 16 : 64), 1));
   const int64_t per = 64 / (2 * a.G);
   k = (k + per - 1) / per * per;
   return std::min(k, a.nseg);
 }
 
 void launch_sweep_timed(qc_grain* g, int mode, const qc::SweepArgs& a, const qc::SweepBufs& b, hipStream_t st) {
-  int G, epl;
-  lane_shape(a.n_e, g->epl_override, g->precision == QC_MIXED, G, epl);
   // every lane marches epl existing energies (the kernel's lane layout)
-  if (epl > a.n_e || G * epl < a.n_e) throw std::logic_error("sweep lane shape does not fit the energies");
+  const int epl = a.epl;
+  if (epl > a.n_e || a.G * epl < a.n_e) throw std::logic_error("sweep lane shape does not fit the energies");
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (g->prof) {
     hcheck(hipEventCreate(&e0), "event");
@@ -689,10 +720,12 @@ void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_n
   do_interp(g, delta, A, st, true);
   qc::SweepArgs a = sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true);
   a.bc_valid = g->bc_valid;
-  {
-    int G, epl;
-    lane_shape(a.n_e, g->epl_override, g->precision == QC_MIXED, G, epl);
-    a.nlong = split_count(g, a, epl);
+  a.nlong = split_count(g, a);
+  if (a.nlong >= a.nseg && a.nseg > 0) {  // every segment: a launch of the wide shape alone
+    a.epl /= 2;
+    a.G *= 2;
+    ++a.log2g;
+    a.nlong = 0;
   }
   qc::SweepBufs b;
   b.nodes = g->nodes;
@@ -2227,6 +2260,9 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     qc::launch_back_adjoint(ba, st);
     // reverse sweep with the store the latest sweep read
     qc::AdjArgs a = sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, pair);
+    a.G = G;
+    a.log2g = ilog2(G);
+    a.epl = epl;
     a.bc_valid = g->last_bc_valid;
     qc::AdjBufs b;
     b.nodes = g->nodes;
@@ -2369,10 +2405,7 @@ qc_status qc_grain_get_split(qc_grain* g, double* frac, int64_t* n_wide) {
     if (frac) *frac = g->split_frac;
     if (n_wide) {
       hcheck(hipSetDevice(g->device), "hipSetDevice");
-      qc::SweepArgs a = sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true);
-      int G, epl;
-      lane_shape(a.n_e, g->epl_override, g->precision == QC_MIXED, G, epl);
-      *n_wide = split_count(g, a, epl);
+      *n_wide = split_count(g, sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true));
     }
     return QC_OK;
   });
@@ -2381,11 +2414,14 @@ qc_status qc_grain_get_split(qc_grain* g, double* frac, int64_t* n_wide) {
 qc_status qc_grain_get_lanes(const qc_grain* g, int* energies_per_lane, int* lanes_per_segment) {
   if (!g) return fail(QC_ERR_INVALID, "grain is NULL");
   if (!energies_per_lane || !lanes_per_segment) return fail(QC_ERR_INVALID, "output pointers are required");
-  int G = 1, epl = 1;
-  lane_shape(g->n_poles, g->epl_override, g->precision == QC_MIXED, G, epl);
-  *energies_per_lane = epl;
-  *lanes_per_segment = G;
-  return QC_OK;
+  return guarded([&]() -> qc_status {
+    hcheck(hipSetDevice(g->device), "hipSetDevice");
+    int G = 1, epl = 1;
+    grain_shape(g, g->n_poles, g->pairing ? g->nseg_pair : g->nseg, G, epl);
+    *energies_per_lane = epl;
+    *lanes_per_segment = G;
+    return QC_OK;
+  });
 }
 
 qc_status qc_profile_enable(qc_grain* g, int enable) {
@@ -2428,8 +2464,8 @@ struct qc_batch {
   int nblocks = 0;
   qc::BatchGrainDev* d_args = nullptr;  // [n] for the current launch
   int2* d_tiles = nullptr;
-  // gamma spill of the persistent sweep: wave_elems records per resident
-  // wave slot (nblocks x 4 slots), sized for the largest tile of any grain
+  // spill of the persistent sweep: wave_elems records per resident block
+  // (a wave pair), sized for the largest tile of any grain
   void* spill = nullptr;
   size_t spill_bytes = 0;
   int64_t wave_elems = 0;
@@ -2490,7 +2526,7 @@ void build_tiles(qc_batch* b) {
   if (b->d_tiles) (void)hipFree(b->d_tiles);
   b->d_tiles = static_cast<int2*>(upload(t));
   b->ntiles = static_cast<int>(t.size());
-  // per-wave spill: 64/G segments of up to maxn nodes and n_e poles each
+  // per-block spill: 64/G segments of up to maxn nodes and n_e poles each
   int64_t we = 1;
   for (qc_grain* g : b->grains) {
     int G, epl;
@@ -2498,7 +2534,7 @@ void build_tiles(qc_batch* b) {
     we = std::max(we, static_cast<int64_t>(64 / G) * g->maxn * g->n_poles);
   }
   b->wave_elems = we;
-  const size_t need = static_cast<size_t>(b->nblocks) * 4 * we * 2 * b->grains[0]->real_bytes();
+  const size_t need = static_cast<size_t>(b->nblocks) * we * 2 * b->grains[0]->real_bytes();
   if (need > b->spill_bytes) {
     drop_graph(b);  // a captured graph holds the old pointer
     if (b->spill) (void)hipFree(b->spill);
@@ -2520,6 +2556,7 @@ void upload_args(qc_batch* b, hipStream_t st) {
     qc::SweepArgs a = sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true);
     a.G = G;
     a.log2g = ilog2(G);
+    a.epl = epl;
     a.bc_valid = g->bc_valid;
     v[gi].a = a;
     v[gi].b.nodes = g->nodes;
@@ -2612,7 +2649,7 @@ qc_status qc_batch_create(qc_grain* const* grains, int n, qc_batch** out) {
     hcheck(hipSetDevice(b->device), "hipSetDevice");
     hipDeviceProp_t prop;
     hcheck(hipGetDeviceProperties(&prop, b->device), "props");
-    b->nblocks = prop.multiProcessorCount * 8;
+    b->nblocks = prop.multiProcessorCount * 16;  // blocks of one wave pair: 32 waves per CU
     for (int i = 0; i < n; ++i) {
       qc_grain* g = grains[i];
       ensure_sweep_buffers(g, false);

@@ -4,8 +4,9 @@
 //                       lattices (Sec. III.A bilinear interpolation)
 //   sweep_kernel        gamma forward / gamma~ backward along every segment
 //                       (App. C), Green's functions (Sec. II.A) and per-node
-//                       pole sums; one group of G lanes per segment, EPL
-//                       energies per lane, all angles in one launch
+//                       pole sums; one group of G lanes per segment and
+//                       direction, EPL energies per lane, all angles in one
+//                       launch
 //   rotate_back_kernel  rotated lattice -> reference cells, angle sums,
 //                       gap update (Eq. gapeq_fixpoint), current
 //                       (Eq. current_density), free-energy density
@@ -197,23 +198,50 @@ __global__ void __launch_bounds__(256) interp1_kernel(InterpArgs a, const cell4<
 // partial end steps (t = 0 and t = n) are peeled off the loops, so interior
 // steps use per-energy constants formed once for the full step h.
 //
+// Two waves share a bundle of 64/G segments, one per direction: wave 0
+// marches gamma from R_min, wave 1 gamma~ from R_max, both at once.  Each
+// leaves its values at every second node of its own first half in the spill
+// array; the waves meet at a barrier when both have reached the middle, and
+// on its second half each reads the other's values, takes one step of the
+// other march for the node between two stored ones (the same step on the
+// same inputs, so the same value), and forms the node sums there.
+//
+// What bounds it: with every node spilled by one wave that marched gamma and
+// then gamma~, the sweep of the 400 x 400 d-wave square (64 angles, 64 poles)
+// moved 5.7 GB (FP32) or 11.2 GB (FP64) at 4.1 TB/s, 85% of what a large copy
+// reaches on this card: it was bound by the spill's traffic.  Two waves halve
+// the serial chain (n + 1 steps instead of 2 n + 2); every second node halves
+// the traffic for half a march more arithmetic (26 of about 90 VALU
+// instructions per node and pole), and the sweep is bound by VALU issue.
+// Measured there: 1.41 -> 0.98 ms mixed, 2.84 -> 2.04 ms FP64; on smaller
+// grains, which the chain's latency bounds, 565 -> 330 us (200 x 200 disc, 48
+// poles, FP64) and 37 -> 17 us (32 x 32 disc).
+//
 // Per node and pole (Sec. II.A): X = gamma gamma~, g = -i pi (1-X)/(1+X),
 // f = -2 i pi gamma/(1+X), f~ = 2 i pi gamma~/(1+X); the pole sums are
 // formed from 1/(1+X) alone (identities at node_sums below).
 // --------------------------------------------------------------------------
-template <typename T, int EPL, int MODE>
-__device__ __forceinline__ void sweep_segment(const SweepArgs& a, int64_t wseg, int lane, int G, int lg,
-                                              const node4<T>* __restrict__ nodes,
-                                              const cpx<T>* __restrict__ bc_g_prev,
-                                              const cpx<T>* __restrict__ bc_gt_prev,
-                                              cpx<T>* __restrict__ bc_g_next, cpx<T>* __restrict__ bc_gt_next,
-                                              cpx<T>* __restrict__ gbase, int64_t gmul, T* __restrict__ ebuf,
-                                              double* __restrict__ lsum) {
+// Memory instructions stay on their side of this point (arithmetic may move
+// across it): the wait counts of the loops below depend on their order.
+__device__ __forceinline__ void vmem_order() { __builtin_amdgcn_sched_barrier(0x387); }
+
+// The direction of one wave: DIR = +1 marches gamma, DIR = -1 gamma~.  In
+// the order of the march the nodes are j = 0..n-1, node j at slot j or
+// n - 1 - j.  Lanes that are not live only meet the barrier.
+template <typename T, int EPL, int MODE, int DIR>
+__device__ __forceinline__ void sweep_march(const SweepArgs& a, bool live, int64_t wseg, int lane, int G, int lg,
+                                            const node4<T>* __restrict__ nodes, const cpx<T>* __restrict__ bc_prev,
+                                            cpx<T>* __restrict__ bc_next, cpx<T>* gbase, int64_t gmul,
+                                            T* __restrict__ ebuf, double* __restrict__ lsum) {
+  constexpr T sd = T(DIR);  // D -> -D* for gamma~
+  if (!live) wseg = 0;
   const int64_t seg = a.order ? static_cast<int64_t>(a.order[wseg]) : wseg;
   const int64_t slot0 = a.seg_slot0[seg];
   const int n = a.seg_n[seg];
   const int last = n > 0 ? n - 1 : 0;
-  const T hfirst = static_cast<T>(a.seg_hfirst[seg]), hlast = static_cast<T>(a.seg_hlast[seg]);
+  // nodes of the first half: gamma takes floor(n/2) of them, gamma~ the rest
+  // (a boundary-only sweep has no second half)
+  const int n1 = MODE == 2 ? n : (DIR > 0 ? n >> 1 : n - (n >> 1));
   const T hfull = static_cast<T>(a.h);
   const T q = static_cast<T>(a.q);
   const int e0 = lane * EPL;
@@ -228,153 +256,141 @@ __device__ __forceinline__ void sweep_segment(const SweepArgs& a, int64_t wseg, 
   bool own[EPL];
   for (int i = 0; i < EPL; ++i) own[i] = es + i >= e0;
 
+  // The Matsubara sweeps (modes 0 and 3) have purely imaginary energies.
+  constexpr bool kReal = MODE == 1 || MODE == 2;
   T ex[EPL], ey[EPL];
   // interior steps (length h): Kx = (-h Im z - 1)/2 and its square per energy
   T kxi[EPL], kx2i[EPL];
   for (int i = 0; i < EPL; ++i) {
     const int e = es + i;
-    ex[i] = static_cast<T>(a.eps[2 * (a.e_off + e)]);
+    ex[i] = kReal ? static_cast<T>(a.eps[2 * (a.e_off + e)]) : T(0);
     ey[i] = static_cast<T>(a.eps[2 * (a.e_off + e) + 1]);
     kxi[i] = fmaT(T(-0.5) * hfull, ey[i], T(-0.5));
     kx2i[i] = kxi[i] * kxi[i];
   }
   const T hh = T(0.5) * hfull, hq8 = T(0.125) * hfull, hqa = T(0.25) * q * hfull;
 
-  // Step with the half-step values (mean of two slots; sd = -1 applies
-  // D -> -D* for gamma~).  End steps take every constant from their length.
-  auto end_step = [&](cpx<T>* gv, const node4<T>& pv, const node4<T>& cv, T hs, T sd) {
+  // Step with the half-step values (mean of two slots).  End steps take
+  // every constant from their length.
+  auto end_step = [&](cpx<T>* gv, const node4<T>& v, T hs) {
     const T h8 = T(0.125) * hs;
     StepC<T> c;
-    c.c2x = h8 * (pv.dy + cv.dy);
-    c.c2y = h8 * (sd * (pv.dx + cv.dx));
+    c.c2x = h8 * (v.dy + v.dy);
+    c.c2y = h8 * (sd * (v.dx + v.dx));
     c.U0x = T(-4) * c.c2x;
     c.U0y = T(4) * c.c2y;
-    const T qa = T(0.5) * q * (pv.a + cv.a);
+    const T qa = T(0.5) * q * (v.a + v.a);
     for (int i = 0; i < EPL; ++i) {
       const T kx = fmaT(T(-0.5) * hs, ey[i], T(-0.5));
       gv[i] = riccati_step_c(gv[i], c, kx, kx * kx, T(0.5) * hs * (qa + ex[i]));
     }
   };
-  auto mid_step = [&](cpx<T>* gv, const node4<T>& pv, const node4<T>& cv, T sd) {
+  auto full_step = [&](cpx<T>* gv, const node4<T>& pv, const node4<T>& cv, T s) {
     StepC<T> c;
     c.c2x = hq8 * (pv.dy + cv.dy);
-    c.c2y = hq8 * (sd * (pv.dx + cv.dx));
+    c.c2y = hq8 * (s * (pv.dx + cv.dx));
     c.U0x = T(-4) * c.c2x;
     c.U0y = T(4) * c.c2y;
-    const T hq = hqa * (pv.a + cv.a);
-    for (int i = 0; i < EPL; ++i) gv[i] = riccati_step_c(gv[i], c, kxi[i], kx2i[i], fmaT(hh, ex[i], hq));
+    // (the product alone, rounded once: an fma keeps the compiler from
+    // contracting it into the sums that riccati_steps forms with it)
+    const T hq = fmaT(hqa, pv.a + cv.a, T(0));
+    T ky[EPL];
+    for (int i = 0; i < EPL; ++i) ky[i] = kReal ? fmaT(hh, ex[i], hq) : hq;
+    riccati_steps<T, EPL, !kReal>(gv, c, kxi, kx2i, ky);
   };
+  auto mid_step = [&](cpx<T>* gv, const node4<T>& pv, const node4<T>& cv) { full_step(gv, pv, cv, sd); };
+  // a step of the other direction, from node cv back to node pv
+  auto back_step = [&](cpx<T>* gv, const node4<T>& pv, const node4<T>& cv) { full_step(gv, pv, cv, -sd); };
 
-  // ---- gamma: R_min -> R_max
-  cpx<T> g[EPL];
-  // the segment's slot values; indexed with unsigned 32-bit offsets, which
-  // widen to the 64-bit address without a sign extension
+  // slot of node j of the march, clamped to the segment's slots; unsigned
+  // 32-bit offsets widen to the 64-bit address without a sign extension
+  auto slot = [&](int j) { return static_cast<uint32_t>(DIR > 0 ? min(j, last) : max(last - j, 0)); };
   const node4<T>* const nseg = nodes + slot0;
-  node4<T> prev = nseg[0];
-  {
-    const int64_t tb = seg * 4;
-    const double wsum = a.tap_start_w[tb] + a.tap_start_w[tb + 1] + a.tap_start_w[tb + 2] + a.tap_start_w[tb + 3];
-    if (a.bc_valid && wsum > 0.0) {
-      for (int i = 0; i < EPL; ++i) g[i] = mk(T(0), T(0));
-      for (int c = 0; c < 4; ++c) {
-        const T w = static_cast<T>(a.tap_start_w[tb + c]);
-        const cpx<T>* src = bc_g_prev + static_cast<int64_t>(a.tap_start_seg[tb + c]) * a.n_e_tot + a.e_off;
+  // spill of this segment, slot t at gseg[t * n_e]: the grain's array
+  // (gmul = n_e) or a wave pair's own scratch (gmul = 0); this lane's entries
+  // start at glane
+  cpx<T>* const glane = gbase + slot0 * gmul + es;
+
+  // ---- first half: start value, first partial step, nodes 0 .. n1 - 1
+  cpx<T> g[EPL];
+  node4<T> prev;
+  if (live) {
+    prev = nseg[slot(0)];
+    {
+      const int64_t tb = seg * 4;
+      const double* tw = (DIR > 0 ? a.tap_start_w : a.tap_end_w) + tb;
+      const int32_t* ts = (DIR > 0 ? a.tap_start_seg : a.tap_end_seg) + tb;
+      const double wsum = tw[0] + tw[1] + tw[2] + tw[3];
+      if (a.bc_valid && wsum > 0.0) {
+        for (int i = 0; i < EPL; ++i) g[i] = mk(T(0), T(0));
+        for (int c = 0; c < 4; ++c) {
+          const T w = static_cast<T>(tw[c]);
+          const cpx<T>* src = bc_prev + static_cast<int64_t>(ts[c]) * a.n_e_tot + a.e_off;
+          for (int i = 0; i < EPL; ++i) {
+            const cpx<T> v = src[es + i];
+            g[i] = mk(g[i].x + w * v.x, g[i].y + w * v.y);
+          }
+        }
+      } else {
+        const T qa = q * prev.a;
+        // (the real part from memory in every mode: a zero the compiler knows
+        // would be shared by the energies and change which products it fuses)
         for (int i = 0; i < EPL; ++i) {
-          const cpx<T> v = src[es + i];
-          g[i] = mk(g[i].x + w * v.x, g[i].y + w * v.y);
+          const T er = static_cast<T>(a.eps[2 * (a.e_off + es + i)]);
+          g[i] = bulk_root(qa + er, ey[i], sd * prev.dx, prev.dy);
         }
       }
-    } else {
-      const T qa = q * prev.a;
-      for (int i = 0; i < EPL; ++i) g[i] = bulk_root(qa + ex[i], ey[i], prev.dx, prev.dy);
+    }
+    // the partial step next to the start (the whole segment if n = 0)
+    end_step(g, prev, static_cast<T>(DIR > 0 || n == 0 ? a.seg_hfirst[seg] : a.seg_hlast[seg]));
+    // Slot values are loaded one step ahead, so the load overlaps a step.  A
+    // node's value is stored at the start of the next step, beside that
+    // step's load: the wait for the load then finds the store done too (a
+    // store issued at the end of a step would be waited for right away).
+    // Every lane stores all its EPL entries (a duplicate writes the value its
+    // owner writes).
+    if (n1 > 0) {
+      node4<T> nxt = nseg[slot(1)];
+      int j = 0;  // the node g stands at
+      auto store_g = [&]() {
+        cpx<T>* dst = glane + static_cast<int64_t>(slot(j)) * a.n_e;
+        if (MODE != 2)
+          for (int i = 0; i < EPL; ++i) dst[i] = g[i];
+      };
+      auto step = [&]() {
+        const node4<T> cur = nxt;
+        nxt = nseg[slot(j + 2)];
+        mid_step(g, prev, cur);
+        prev = cur;
+        ++j;
+      };
+      // stored: node 0 and every second node counted back from n1 - 2
+      store_g();
+      if (!(n1 & 1)) step();
+      while (j + 2 < n1) {
+        step();
+        store_g();
+        step();
+      }
     }
   }
-  // gamma spill of this segment, node t at gseg[t * n_e]: the grain's array
-  // (gmul = n_e) or a wave's own scratch (gmul = 0); this lane's entries
-  // start at gseg + es
-  cpx<T>* const gseg = gbase + slot0 * gmul;
-  cpx<T>* const glane = gseg + es;
-  // Every lane stores all its EPL entries (a duplicate writes the value its
-  // owner writes).  With no conditional stores the compiler knows how many
-  // stores were issued after a prefetch and waits for the prefetch alone.
-  auto store_g = [&](int t) {
-    cpx<T>* dst = glane + static_cast<int64_t>(t) * a.n_e;
-    for (int i = 0; i < EPL; ++i) dst[i] = g[i];
-  };
-  // Slot values are loaded one step ahead, so the load overlaps a step.  A
-  // wait for that load must not also wait for a gamma store issued just
-  // before it: in FP32 the stores close each step, and the loop is entered
-  // as it repeats (prefetch, then two stores), so the compiler waits for the
-  // prefetch alone; in FP64, where the compiler sinks the first prefetch
-  // below step 0's store, a node's gamma is stored in the next step, right
-  // after that step's prefetch.
-  constexpr bool late_store = sizeof(T) == 4;
-  node4<T> nxt = nseg[static_cast<uint32_t>(min(1, last))];
-  // step 0 from R_min (the boundary point takes slot 0's values); a segment
-  // with no node still owns one slot, so its store is in range
-  end_step(g, prev, prev, hfirst, T(1));
-  if (late_store && MODE != 2) store_g(0);
-  // (FP32: two steps per loop turn, so the look-ahead registers rotate by
-  // renaming instead of moves; in FP64 that would cost a wave per SIMD)
-  constexpr int kUnrollG = sizeof(T) == 4 ? 2 : 1;
-#pragma unroll kUnrollG
-  for (int t = 1; t < n; ++t) {
-    const node4<T> cur = nxt;
-    nxt = nseg[static_cast<uint32_t>(min(t + 1, last))];
-    if (!late_store && MODE != 2) store_g(t - 1);
-    mid_step(g, prev, cur, T(1));
-    prev = cur;
-    if (late_store && MODE != 2) store_g(t);
-  }
-  if (!late_store && MODE != 2 && n > 0) store_g(n - 1);
-  // step n to R_max (the boundary point takes slot n-1's values)
-  if (n > 0) end_step(g, prev, prev, hlast, T(1));
-  // end values for the next sweep (the LDOS output pass writes them only
-  // when iterating to convergence: bc_g_next given)
-  if (MODE == 0 || MODE == 2 || (MODE == 1 && bc_g_next)) {
-    cpx<T>* dst = bc_g_next + seg * a.n_e_tot + a.e_off + es;
-    for (int i = 0; i < EPL; ++i)
-      if (own[i]) dst[i] = g[i];
-  }
+  // ---- the waves of the pair meet: the other's first half is in the spill
+  if (MODE != 2) __syncthreads();
+  if (!live) return;
 
-  // ---- gamma~: R_max -> R_min with D -> -D*
-  // pole weights R_p of the lane's energies (0 for padding), kept in FP64:
+  // pole weights R_p of the lane's energies (0 for duplicates), kept in FP64:
   // the gap denominator holds them exactly, and rounding them to FP32 in
   // the node sums would bias every gap update the same way
   double rw[EPL];
   for (int i = 0; i < EPL; ++i)
     rw[i] = (MODE == 0 && own[i]) ? a.rp[a.e_off + es + i] : 0.0;
-  cpx<T> gt[EPL];
-  prev = nseg[static_cast<uint32_t>(last)];
-  {
-    const int64_t tb = seg * 4;
-    const double wsum = a.tap_end_w[tb] + a.tap_end_w[tb + 1] + a.tap_end_w[tb + 2] + a.tap_end_w[tb + 3];
-    if (a.bc_valid && wsum > 0.0) {
-      for (int i = 0; i < EPL; ++i) gt[i] = mk(T(0), T(0));
-      for (int c = 0; c < 4; ++c) {
-        const T w = static_cast<T>(a.tap_end_w[tb + c]);
-        const cpx<T>* src = bc_gt_prev + static_cast<int64_t>(a.tap_end_seg[tb + c]) * a.n_e_tot + a.e_off;
-        for (int i = 0; i < EPL; ++i) {
-          const cpx<T> v = src[es + i];
-          gt[i] = mk(gt[i].x + w * v.x, gt[i].y + w * v.y);
-        }
-      }
-    } else {
-      const T qa = q * prev.a;
-      for (int i = 0; i < EPL; ++i) gt[i] = bulk_root(qa + ex[i], ey[i], -prev.dx, prev.dy);
-    }
-  }
 
   // Per node and pole (Sec. II.A), with X = gamma gamma~ and I = 1/(1+X):
   //   f + conj f~ = -2 i pi [Re((gamma + gamma~) I) + i Im((gamma - gamma~) I)],
   //   Re g = pi Im((1-X)/(1+X)) = 2 pi Im I,
   //   (D* f + D f~) / (pi + i g) = i (D gamma~ - D* gamma)  since pi + i g = 2 pi I,
   // so the Eilenberger free-energy term needs no division.
-  // gamma of a node for this lane's energies
-  auto load_g = [&](cpx<T>* gv, int t) {
-    const cpx<T>* src = glane + static_cast<int64_t>(t) * a.n_e;
-    for (int i = 0; i < EPL; ++i) gv[i] = src[i];
-  };
+  //
   // Node sums through LDS (MODE 0, G >= 8).  The wave's buffer holds two
   // nodes x four components x 64 lanes; slot b of component c of lane l is
   // lsum[b * 256 + c * 64 + l].  Lanes of one wave see each other's LDS
@@ -399,27 +415,28 @@ __device__ __forceinline__ void sweep_segment(const SweepArgs& a, int64_t wseg, 
     if (lp >= 2) v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
     if (lp >= 3) v += dpp_f64<0x141>(v);  // row_half_mirror: lane 0 of 8 adds lane 7
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // slot b = o >> 2 holds node0 - b; component o & 3
-    if (r == 0 && (o >> 2) < cnt) a.node_out[(node0 - (o >> 2)) * 4 + (o & 3)] = a.twopi_tt * v;
+    // slot b = o >> 2 holds the b-th node of the pair; component o & 3
+    if (r == 0 && (o >> 2) < cnt) a.node_out[(node0 + DIR * (o >> 2)) * 4 + (o & 3)] = a.twopi_tt * v;
   };
-  // k counts the nodes visited before this one (the same for every group of
-  // the wave, since all groups start their march together)
-  auto node_sums = [&](int64_t node, const node4<T>& nv, const cpx<T>* gn, int k) {
+  // sums at one node from this wave's value g and the other direction's go;
+  // k counts the nodes of the second half visited before this one (the same
+  // for every group of the wave, since all groups start it together)
+  auto node_sums = [&](int64_t node, const node4<T>& nv, const cpx<T>* go, int k) {
     if (MODE == 0) {
       double sfx, sfy, sg, si;
       if constexpr (sizeof(T) == 4) {
         // mixed precision: each pole's terms are formed from the FP32
         // marches, weighted by R_p and summed over poles in FP64
         for (int i = 0; i < EPL; ++i) {
-          const cpx<T> gg = gn[i];
-          const T xx = fmaT(gg.x, gt[i].x, -(gg.y * gt[i].y));
-          const T xy = fmaT(gg.x, gt[i].y, gg.y * gt[i].x);
+          const cpx<T> gg = DIR > 0 ? g[i] : go[i], gt = DIR > 0 ? go[i] : g[i];
+          const T xx = fmaT(gg.x, gt.x, -(gg.y * gt.y));
+          const T xy = fmaT(gg.x, gt.y, gg.y * gt.x);
           const T dxr = T(1) + xx;
           // I = 1/(1+X) = (dxr - i xy) u with u = 1 / |1+X|^2
           const T u = drcp(fmaT(dxr, dxr, xy * xy));
           const T ix = dxr * u, iy = xy * u;  // I = ix - i iy
-          const T sxs = gg.x + gt[i].x, sys = gg.y + gt[i].y;
-          const T dxs = gg.x - gt[i].x, dys = gg.y - gt[i].y;
+          const T sxs = gg.x + gt.x, sys = gg.y + gt.y;
+          const T dxs = gg.x - gt.x, dys = gg.y - gt.y;
           const double tfx = static_cast<double>(fmaT(sxs, ix, sys * iy));     // Re((gamma + gamma~) I)
           const double tfy = static_cast<double>(fmaT(dys, ix, -(dxs * iy)));  // Im((gamma - gamma~) I)
           const double tg = static_cast<double>(iy);                           // -Im I
@@ -439,15 +456,15 @@ __device__ __forceinline__ void sweep_segment(const SweepArgs& a, int64_t wseg, 
       } else {
         T pfx = T(0), pfy = T(0), pg = T(0), p1 = T(0), p2 = T(0);
         for (int i = 0; i < EPL; ++i) {
-          const cpx<T> gg = gn[i];
-          const T xx = fmaT(gg.x, gt[i].x, -(gg.y * gt[i].y));
-          const T xy = fmaT(gg.x, gt[i].y, gg.y * gt[i].x);
+          const cpx<T> gg = DIR > 0 ? g[i] : go[i], gt = DIR > 0 ? go[i] : g[i];
+          const T xx = fmaT(gg.x, gt.x, -(gg.y * gt.y));
+          const T xy = fmaT(gg.x, gt.y, gg.y * gt.x);
           const T dxr = T(1) + xx;
           // I = 1/(1+X) = (dxr - i xy) u / R with u = R / |1+X|^2 (R the pole weight)
           const T r = static_cast<T>(rw[i]);
           const T u = r * drcp(fmaT(dxr, dxr, xy * xy));
-          const T sxs = gg.x + gt[i].x, sys = gg.y + gt[i].y;
-          const T dxs = gg.x - gt[i].x, dys = gg.y - gt[i].y;
+          const T sxs = gg.x + gt.x, sys = gg.y + gt.y;
+          const T dxs = gg.x - gt.x, dys = gg.y - gt.y;
           pfx = fmaT(u, fmaT(sxs, dxr, sys * xy), pfx);     // R Re((gamma + gamma~) I)
           pfy = fmaT(u, fmaT(dys, dxr, -(dxs * xy)), pfy);  // R Im((gamma - gamma~) I)
           pg = fmaT(-u, xy, pg);                            // R Im I
@@ -462,15 +479,14 @@ __device__ __forceinline__ void sweep_segment(const SweepArgs& a, int64_t wseg, 
       }
       // S_f = -2 i pi t~ (sfx + i sfy), S_g = 2 pi t~ sg, S_I = 2 pi t~ si
       if (G >= 8) {
-        // the lane's four partials go to LDS; every second node the group
-        // sums the pair (this node and the one before it, node + 1)
+        // the lane's four partials go to LDS, where the group sums them
+        // when a pair of nodes is there (see the loop below)
         const int b = k & 1;
         double* w = lsum + b * 256 + (threadIdx.x & 63);
         w[0] = sfy;
         w[64] = -sfx;
         w[128] = sg;
         w[192] = si;
-        if (b) lds_reduce(node + 1, 2);
       } else if (G >= 4) {
         // lane q of the group (q < 4) ends with component q of the node's sums
         const double v = group_sum4_scatter(sfy, -sfx, sg, si, G, lane);
@@ -487,155 +503,153 @@ __device__ __forceinline__ void sweep_segment(const SweepArgs& a, int64_t wseg, 
           reinterpret_cast<double4*>(a.node_out)[node] = o;
         }
       }
-    } else if (MODE == 1) {  // N/N_F = -Im g / pi = Re((1-X)/(1+X)) = 2 Re I - 1 per energy
-      T* dst = ebuf + node * a.n_e + es;
+    } else {
+      // MODE 1: N/N_F = -Im g / pi = Re((1-X)/(1+X)) = 2 Re I - 1 per energy;
+      // MODE 3: (1-X)/(1+X) = 2 I - 1 per energy, complex (g = -i pi times it)
+      T* dst = ebuf + (MODE == 1 ? 1 : 2) * (node * a.n_e + es);
       for (int i = 0; i < EPL; ++i) {
         if (!own[i]) continue;
-        const cpx<T> gg = gn[i];
-        const T xx = fmaT(gg.x, gt[i].x, -(gg.y * gt[i].y));
-        const T xy = fmaT(gg.x, gt[i].y, gg.y * gt[i].x);
+        const cpx<T> gg = DIR > 0 ? g[i] : go[i], gt = DIR > 0 ? go[i] : g[i];
+        const T xx = fmaT(gg.x, gt.x, -(gg.y * gt.y));
+        const T xy = fmaT(gg.x, gt.y, gg.y * gt.x);
         const T dxr = T(1) + xx;
         const T ri = drcp(fmaT(dxr, dxr, xy * xy));
-        dst[i] = fmaT(T(2) * dxr, ri, T(-1));
-      }
-    } else {  // MODE 3: (1-X)/(1+X) = 2 I - 1 per energy, complex (g = -i pi times it)
-      T* dst = ebuf + 2 * (node * a.n_e + es);
-      for (int i = 0; i < EPL; ++i) {
-        if (!own[i]) continue;
-        const cpx<T> gg = gn[i];
-        const T xx = fmaT(gg.x, gt[i].x, -(gg.y * gt[i].y));
-        const T xy = fmaT(gg.x, gt[i].y, gg.y * gt[i].x);
-        const T dxr = T(1) + xx;
-        const T ri = drcp(fmaT(dxr, dxr, xy * xy));
-        dst[2 * i] = fmaT(T(2) * dxr, ri, T(-1));
-        dst[2 * i + 1] = T(-2) * xy * ri;
+        if (MODE == 1) {
+          dst[i] = fmaT(T(2) * dxr, ri, T(-1));
+        } else {
+          dst[2 * i] = fmaT(T(2) * dxr, ri, T(-1));
+          dst[2 * i + 1] = T(-2) * xy * ri;
+        }
       }
     }
   };
-
-  // step n from R_max (boundary point = slot n-1; the whole segment if n = 0)
-  cpx<T> gn[EPL];
-  if (MODE != 2) load_g(gn, last);
-  end_step(gt, prev, prev, n > 0 ? hlast : hfirst, T(-1));
-  if (MODE != 2 && n > 0) node_sums(slot0 + n - 1, prev, gn, 0);
-  // slot values and gamma are loaded one step ahead, so the loads overlap
-  // a step (gamma comes back from HBM: it was written a whole march ago)
-  // (FP32 only: in FP64 the registers would cost a wave per SIMD)
-  constexpr bool gpre = MODE != 2 && sizeof(T) == 4;
-  // (the prefetched row, max(t - 2, 0) at step t, is walked down with a
-  // pointer rather than formed from t, which costs 64-bit multiplies)
-  nxt = nseg[static_cast<uint32_t>(max(n - 2, 0))];
-  cpx<T> gnx[EPL];
-  const cpx<T>* grow = glane + static_cast<int64_t>(max(n - 2, 0)) * a.n_e;
-  auto load_row = [&](cpx<T>* gv, const cpx<T>* row) {
-    for (int i = 0; i < EPL; ++i) gv[i] = row[i];
-  };
-  if (gpre) load_row(gnx, grow);
-  for (int t = n - 1; t >= 1; --t) {
-    const node4<T> cur = nxt;
-    nxt = nseg[static_cast<uint32_t>(max(t - 2, 0))];
-    if (gpre) {
-      for (int i = 0; i < EPL; ++i) gn[i] = gnx[i];
-      if (t >= 2) grow -= a.n_e;
-      load_row(gnx, grow);
-    } else if (MODE != 2) {
-      load_g(gn, t - 1);
+  // ---- second half: nodes n1 .. n - 1 in pairs, slot values and the other
+  // direction's values read one pair ahead (those come back from HBM)
+  if (MODE != 2) {
+    int j = n1;
+    node4<T> vA = nseg[slot(j)], vB = nseg[slot(j + 1)];
+    cpx<T> oB[EPL];
+    auto load_row = [&](cpx<T>* gv, int jj) {
+      const cpx<T>* row = glane + static_cast<int64_t>(slot(jj)) * a.n_e;
+      for (int i = 0; i < EPL; ++i) gv[i] = row[i];
+    };
+    load_row(oB, j + 1);
+    for (; j + 1 < n; j += 2) {
+      const node4<T> cA = vA, cB = vB;
+      cpx<T> gA[EPL], gB[EPL];
+      for (int i = 0; i < EPL; ++i) gA[i] = gB[i] = oB[i];
+      // The sums of the pair before this one: reduced and stored here, ahead
+      // of the loads for the next pair, so that the wait for those loads
+      // finds this store done (issued at the end of a turn, its latency
+      // would be waited for at the start of the next).
+      if (MODE == 0 && G >= 8 && j > n1) lds_reduce(slot0 + slot(j - 2), 2);
+      vA = nseg[slot(j + 2)];
+      vB = nseg[slot(j + 3)];
+      load_row(oB, j + 3);
+      vmem_order();
+      mid_step(g, prev, cA);
+      back_step(gA, cA, cB);  // node j was not stored: one step from node j + 1
+      node_sums(slot0 + slot(j), cA, gA, 0);
+      mid_step(g, cA, cB);
+      node_sums(slot0 + slot(j + 1), cB, gB, 1);
+      prev = cB;
     }
-    mid_step(gt, prev, cur, T(-1));
-    prev = cur;
-    if (MODE != 2) node_sums(slot0 + t - 1, cur, gn, n - t);
+    if (MODE == 0 && G >= 8 && j > n1) lds_reduce(slot0 + slot(j - 2), 2);
+    if (j < n) {  // an odd count leaves the last node alone (the other direction's first, always stored)
+      if (n > 1) mid_step(g, prev, vA);  // n = 1: the first partial step already reached the node
+      node_sums(slot0 + slot(j), vA, oB, 0);
+      prev = vA;
+      if (MODE == 0 && G >= 8) lds_reduce(slot0 + slot(j), 1);
+    }
   }
-  // with an odd node count, node 0 is left alone in slot 0
-  if (MODE == 0 && G >= 8 && (n & 1)) lds_reduce(slot0, 1);
-  // step 0 to R_min (boundary point = slot 0)
-  if (n > 0) end_step(gt, prev, prev, hfirst, T(-1));
-  if (MODE == 0 || MODE == 2 || (MODE == 1 && bc_gt_next)) {
-    cpx<T>* dst = bc_gt_next + seg * a.n_e_tot + a.e_off + es;
+  // the partial step to the far end
+  if (n > 0) end_step(g, prev, static_cast<T>(DIR > 0 ? a.seg_hlast[seg] : a.seg_hfirst[seg]));
+  // end values for the next sweep (the LDOS output pass writes them only
+  // when iterating to convergence: bc_next given)
+  if (MODE == 0 || MODE == 2 || (MODE == 1 && bc_next)) {
+    cpx<T>* dst = bc_next + seg * a.n_e_tot + a.e_off + es;
     for (int i = 0; i < EPL; ++i)
-      if (own[i]) dst[i] = gt[i];
+      if (own[i]) dst[i] = g[i];
   }
 }
 
-// Occupancy floors (waves per SIMD) for the FP32 variants: 7 (<= 72 VGPRs)
-// with two energies per lane (the spills, gamma look-ahead included, stay
-// outside the loops; 6 waves without spills ran slower); with four,
-// 4 (<= 128) for the pole-sum sweep, which spills in its loops at 5, and 5
-// for the other modes; the rest keep the compiler's default.
+// one bundle of 64/G segments by the two waves of a 128-thread block
 template <typename T, int EPL, int MODE>
-constexpr int sweep_min_waves() {
-  return (sizeof(T) == 4 && EPL == 4) ? (MODE == 0 ? 4 : 5) : (sizeof(T) == 4 && EPL == 2) ? 7 : 1;
+__device__ __forceinline__ void sweep_bundle(const SweepArgs& a, int64_t wseg0, int G, int lg, const SweepBufs& b,
+                                             cpx<T>* gbase, int64_t gmul, double* lsum) {
+  const int l64 = threadIdx.x & 63;
+  const int dir = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int64_t wseg = wseg0 + (l64 >> lg);
+  const bool live = wseg < a.nseg;
+  const int lane = l64 & (G - 1);
+  const node4<T>* nodes = static_cast<const node4<T>*>(b.nodes);
+  T* ebuf = static_cast<T*>(b.ebuf);
+  // (the branch is uniform over each wave, and each wave meets the one barrier once)
+  if (dir == 0)
+    sweep_march<T, EPL, MODE, 1>(a, live, wseg, lane, G, lg, nodes, static_cast<const cpx<T>*>(b.bc_g_prev),
+                                 static_cast<cpx<T>*>(b.bc_g_next), gbase, gmul, ebuf, lsum);
+  else
+    sweep_march<T, EPL, MODE, -1>(a, live, wseg, lane, G, lg, nodes, static_cast<const cpx<T>*>(b.bc_gt_prev),
+                                  static_cast<cpx<T>*>(b.bc_gt_next), gbase, gmul, ebuf, lsum);
 }
 
 template <typename T, int EPL, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<T, EPL, MODE>())))
-sweep_kernel(SweepArgs a, const node4<T>* __restrict__ nodes,
-                                                    const cpx<T>* __restrict__ bc_g_prev,
-                                                    const cpx<T>* __restrict__ bc_gt_prev,
-                                                    cpx<T>* __restrict__ bc_g_next,
-                                                    cpx<T>* __restrict__ bc_gt_next,
-                                                    cpx<T>* __restrict__ gbuf, T* __restrict__ ebuf) {
-  const int64_t gtid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(128)
+sweep_kernel(SweepArgs a, SweepBufs b) {
   double* lsum = nullptr;
   if constexpr (MODE == 0) {
-    __shared__ double red[4 * 512];  // two nodes x four sums x 64 lanes per wave
+    __shared__ double red[2 * 512];  // two nodes x four sums x 64 lanes per wave
     lsum = red + (threadIdx.x >> 6) * 512;
   }
+  cpx<T>* const gbuf = static_cast<cpx<T>*>(b.gbuf);
   // The launch order is longest first.  In a launch that fills the device's
-  // wave slots about once, the longest segments set its length; the first
+  // wave slots a few times, the longest segments finish last; the first
   // nlong of them march with twice the lanes and half the energies per lane,
   // so they finish in about half the time.  The split falls on a wave
   // boundary (nlong * 2G is a multiple of 64), so each wave takes one shape.
-  int64_t r = gtid, first = 0;
+  int64_t w = blockIdx.x, first = 0;
   if constexpr (MODE == 0 && EPL % 2 == 0) {
     first = a.nlong;
-    const int64_t nl = a.nlong << (a.log2g + 1);
-    if (r < nl) {
-      sweep_segment<T, EPL / 2, MODE>(a, r >> (a.log2g + 1), static_cast<int>(r & (2 * a.G - 1)), 2 * a.G,
-                                      a.log2g + 1, nodes, bc_g_prev, bc_gt_prev, bc_g_next, bc_gt_next, gbuf, a.n_e,
-                                      ebuf, lsum);
+    const int64_t wl = (a.nlong << (a.log2g + 1)) >> 6;
+    if (w < wl) {
+      sweep_bundle<T, EPL / 2, MODE>(a, w << (5 - a.log2g), 2 * a.G, a.log2g + 1, b, gbuf, a.n_e, lsum);
       return;
     }
-    r -= nl;
+    w -= wl;
   }
-  const int64_t wseg = first + (r >> a.log2g);
-  const int lane = static_cast<int>(r & (a.G - 1));
-  if (wseg >= a.nseg) return;  // whole lane groups leave together (G | 64)
-  sweep_segment<T, EPL, MODE>(a, wseg, lane, a.G, a.log2g, nodes, bc_g_prev, bc_gt_prev, bc_g_next, bc_gt_next,
-                              gbuf, a.n_e, ebuf, lsum);
+  sweep_bundle<T, EPL, MODE>(a, first + (w << (6 - a.log2g)), a.G, a.log2g, b, gbuf, a.n_e, lsum);
 }
 
-// Batched grains: one persistent launch.  Every wave pulls tiles (a grain
-// and a bundle of 64/G of its segments) from a queue sorted by cost until
-// the queue is empty; every wave reaches that exit.  The gamma spill of a
-// tile lives only between its two marches, so each wave keeps it in its own
-// slice of `spill` (wave_elems records; segment k of the tile at
-// k * maxn * n_e), reused tile after tile: the spill memory is set by the
-// resident waves, not by the number or size of the grains.
+// Batched grains: one persistent launch.  Every block (a wave pair) pulls
+// tiles (a grain and a bundle of 64/G of its segments) from a queue sorted by
+// cost until the queue is empty; every block reaches that exit.  The spill of
+// a tile lives only between the two halves of its marches, so each block
+// keeps it in its own slice of `spill` (wave_elems records; segment k of the
+// tile at k * maxn * n_e), reused tile after tile: the spill memory is set by
+// the resident blocks, not by the number or size of the grains.
 template <typename T, int EPL>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<T, EPL, 0>())))
+__global__ void __launch_bounds__(128)
 batch_sweep_kernel(const BatchGrainDev* __restrict__ grains,
                                                           const int2* __restrict__ tiles, int ntiles,
                                                           int* __restrict__ counter, cpx<T>* __restrict__ spill,
                                                           int64_t wave_elems) {
   const int l64 = threadIdx.x & 63;
-  cpx<T>* const wspill = spill + (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * wave_elems;
-  __shared__ double red[4 * 512];  // node-sum exchange, two nodes x four sums x 64 lanes per wave
+  cpx<T>* const wspill = spill + static_cast<int64_t>(blockIdx.x) * wave_elems;
+  __shared__ double red[2 * 512];  // node-sum exchange, two nodes x four sums x 64 lanes per wave
+  __shared__ int next;
   while (true) {
-    int t = 0;
-    if (l64 == 0) t = atomicAdd(counter, 1);
-    // all 64 lanes are active here, so the first active lane is lane 0; the
-    // tile index becomes wave-uniform and the grain's arguments scalar loads
-    t = __builtin_amdgcn_readfirstlane(t);
+    if (threadIdx.x == 0) next = atomicAdd(counter, 1);
+    __syncthreads();
+    // the tile index is uniform: the grain's arguments become scalar loads
+    const int t = __builtin_amdgcn_readfirstlane(next);
+    __syncthreads();  // (read by both waves before the next tile overwrites it)
     if (t >= ntiles) break;
     const int2 tile = tiles[t];
     const BatchGrainDev& gd = grains[tile.x];
-    const int64_t wseg = static_cast<int64_t>(tile.y) + (l64 >> gd.a.log2g);
-    if (wseg < gd.a.nseg)
-      sweep_segment<T, EPL, 0>(gd.a, wseg, l64 & (gd.a.G - 1), gd.a.G, gd.a.log2g, static_cast<const node4<T>*>(gd.b.nodes),
-                               static_cast<const cpx<T>*>(gd.b.bc_g_prev), static_cast<const cpx<T>*>(gd.b.bc_gt_prev),
-                               static_cast<cpx<T>*>(gd.b.bc_g_next), static_cast<cpx<T>*>(gd.b.bc_gt_next),
-                               wspill + static_cast<int64_t>(l64 >> gd.a.log2g) * gd.a.maxn * gd.a.n_e, 0, nullptr,
-                               red + (threadIdx.x >> 6) * 512);
+    const int lg = gd.a.log2g;
+    sweep_bundle<T, EPL, 0>(gd.a, tile.y, gd.a.G, lg, gd.b,
+                            wspill + static_cast<int64_t>(l64 >> lg) * gd.a.maxn * gd.a.n_e, 0,
+                            red + (threadIdx.x >> 6) * 512);
   }
 }
 
@@ -1319,12 +1333,10 @@ template void launch_interp<float>(const InterpArgs&, void*, void*, hipStream_t)
 template <typename T, int EPL, int MODE>
 static void launch_sweep_t(const SweepArgs& a, const SweepBufs& b, hipStream_t st) {
   const bool split = MODE == 0 && EPL % 2 == 0 && a.nlong > 0;
-  const int64_t threads = split ? a.nlong * 2 * a.G + (a.nseg - a.nlong) * a.G : a.nseg * a.G;
-  hipLaunchKernelGGL((sweep_kernel<T, EPL, MODE>), dim3(nblk(threads)), dim3(256), 0, st, a,
-                     static_cast<const node4<T>*>(b.nodes),
-                     static_cast<const cpx<T>*>(b.bc_g_prev), static_cast<const cpx<T>*>(b.bc_gt_prev),
-                     static_cast<cpx<T>*>(b.bc_g_next), static_cast<cpx<T>*>(b.bc_gt_next),
-                     static_cast<cpx<T>*>(b.gbuf), static_cast<T*>(b.ebuf));
+  const int64_t nl = split ? a.nlong : 0;
+  // one block of two waves per bundle of 64/G segments
+  const int64_t bundles = nl * 2 * a.G / 64 + ((a.nseg - nl) * a.G + 63) / 64;
+  hipLaunchKernelGGL((sweep_kernel<T, EPL, MODE>), dim3(static_cast<unsigned>(bundles)), dim3(128), 0, st, a, b);
 }
 
 template <typename T, int MODE>
@@ -1358,8 +1370,8 @@ static int64_t wave_slots_t() {
   int dev = 0, blocks = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, sweep_kernel<T, EPL, 0>, 256, 0) != hipSuccess) return 0;
-  return static_cast<int64_t>(blocks) * 4 * cus;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, sweep_kernel<T, EPL, 0>, 128, 0) != hipSuccess) return 0;
+  return static_cast<int64_t>(blocks) * 2 * cus;
 }
 
 template <typename T>
@@ -1381,7 +1393,7 @@ void launch_batch_sweep(int epl, const BatchGrainDev* grains, const int2* tiles,
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter);
   cpx<T>* sp = static_cast<cpx<T>*>(spill);
 #define QC_BATCH(E)                                                                                                  \
-  hipLaunchKernelGGL((batch_sweep_kernel<T, E>), dim3(nblocks), dim3(256), 0, st, grains, tiles, ntiles, counter, sp, \
+  hipLaunchKernelGGL((batch_sweep_kernel<T, E>), dim3(nblocks), dim3(128), 0, st, grains, tiles, ntiles, counter, sp, \
                      wave_elems)
   switch (epl) {
     case 1: QC_BATCH(1); break;

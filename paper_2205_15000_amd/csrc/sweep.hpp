@@ -46,6 +46,7 @@ struct SweepArgs {
   int64_t nseg;
   const int32_t* order;   // launch order of the segments (longest first) or nullptr
   int G, log2g;           // lanes per segment (power of two dividing 64)
+  int epl;                // energies per lane
   int n_e;                // energies in this launch (stride of gbuf / ebuf)
   int n_e_tot;            // stride of the boundary stores
   int e_off;              // first energy of this launch
@@ -75,7 +76,7 @@ struct SweepBufs {
   const void* bc_gt_prev;
   void* bc_g_next;
   void* bc_gt_next;
-  void* gbuf;             // gamma spill [nslot][n_e] (single-grain launches)
+  void* gbuf;             // spill of the marches [nslot][n_e] (single-grain launches)
   void* ebuf;
 };
 
