@@ -334,10 +334,9 @@ struct qc_grain {
   double* part_host = nullptr;
   double* bbuf = nullptr;
   // A-solve
-  int px = 0, py = 0, lpx = 0, lpy = 0;
+  qc::FftLen lx{1, 0}, ly{1, 0};
   double2* fw = nullptr;
-  double2* fw2 = nullptr;
-  double2* ghat = nullptr;
+  double* ghat = nullptr;
   double2* twx = nullptr;
   double2* twy = nullptr;
   // SCF scratch
@@ -434,7 +433,7 @@ void free_grain(qc_grain* g) {
                   g->sink, g->wk, g->seg_slot0, g->seg_n, g->seg_hfirst, g->seg_hlast, g->tap_s_seg,
                   g->tap_s_w, g->tap_e_seg, g->tap_e_w, g->grain_cells, g->rb_idx, g->rb_w, g->rb4, g->mask,
                   g->eps, g->rpd, g->den, g->logt, g->nodes, g->cells, g->order, g->gbuf, g->node_out, g->bc[0][0],
-                  g->bc[0][1], g->bc[1][0], g->bc[1][1], g->omega_cell, g->dmean, g->part, g->bbuf, g->fw, g->fw2,
+                  g->bc[0][1], g->bc[1][0], g->bc[1][1], g->omega_cell, g->dmean, g->part, g->bbuf, g->fw,
                   g->ghat, g->twx, g->twy, g->dnew, g->jcur, g->jold, g->anew, g->vel_d, g->vel_a, g->gtbuf, g->lgt, g->gS, g->gV,
                   g->bt_ptr, g->bt_c, g->bt_w, g->it_dptr, g->it_ds, g->it_dw, g->it_aptr, g->it_as, g->it_aw,
                   g->ckbase, g->ckg, g->ckgt, g->ckscr, g->lw_acc, g->lw_dl, g->lw_save, g->order_pair, g->rb4_pair,
@@ -469,25 +468,9 @@ double region_sum(const qc_grain* g, int r) {
   return s;
 }
 
-// rows along x, transpose, rows along y (result in fw2, [px][py] layout);
-// rows y >= nz_rows of fw are zero and keep a zero transform
-void fft_forward_2d(qc_grain* g, hipStream_t st, int sign, int nz_rows) {
-  qc::launch_fft_rows(g->fw, nz_rows, g->lpx, g->twx, sign, nullptr, st);
-  qc::launch_transpose(g->fw, g->fw2, g->py, g->px, st);
-  qc::launch_fft_rows(g->fw2, g->px, g->lpy, g->twy, sign, nullptr, st);
-}
-
-// inverse of fw2 times pre (elementwise, [px][py]) into fw; only rows
-// y < out_rows of fw are transformed along x
-void fft_inverse_2d(qc_grain* g, hipStream_t st, const double2* pre, int out_rows) {
-  qc::launch_fft_rows(g->fw2, g->px, g->lpy, g->twy, +1, pre, st);
-  qc::launch_transpose(g->fw2, g->fw, g->px, g->py, st);
-  qc::launch_fft_rows(g->fw, out_rows, g->lpx, g->twx, +1, nullptr, st);
-}
-
 std::vector<double2> twiddles(int n) {
-  std::vector<double2> tw(std::max(1, n / 2));
-  for (int k = 0; k < n / 2; ++k) tw[k] = make_double2(std::cos(2.0 * kPi * k / n), -std::sin(2.0 * kPi * k / n));
+  std::vector<double2> tw(n);
+  for (int k = 0; k < n; ++k) tw[k] = make_double2(std::cos(2.0 * kPi * k / n), -std::sin(2.0 * kPi * k / n));
   return tw;
 }
 
@@ -1052,26 +1035,28 @@ qc_status qc_grain_create(int device, const qc_grain_desc* desc, qc_grain** out)
     g->jold = static_cast<double*>(dalloc(sizeof(double) * 2 * g->ncell));
     g->anew = static_cast<double*>(dalloc(sizeof(double) * 2 * g->ncell));
     if (g->kappa > 0.0) {
-      g->px = 1 << ilog2(2 * p.nx);
-      g->py = 1 << ilog2(2 * p.ny);
-      g->lpx = ilog2(g->px);
-      g->lpy = ilog2(g->py);
-      if (g->lpx > 12 || g->lpy > 12) throw std::invalid_argument("grid too large for the A-solve (max 2048)");
-      const int64_t np = static_cast<int64_t>(g->px) * g->py;
-      std::vector<double2> gp(np);
-      for (int y = 0; y < g->py; ++y)
-        for (int x = 0; x < g->px; ++x) {
-          const int m = std::min(x, g->px - x), n = std::min(y, g->py - y);
-          const double v = (m <= p.nx - 1 && n <= p.ny - 1) ? green_mn(m, n, p.h) : 0.0;
-          gp[static_cast<int64_t>(y) * g->px + x] = make_double2(v, 0.0);
+      if (ilog2(2 * p.nx) > 12 || ilog2(2 * p.ny) > 12)
+        throw std::invalid_argument("grid too large for the A-solve (max 2048)");
+      g->lx = qc::fft_length(2 * p.nx);
+      g->ly = qc::fft_length(2 * p.ny);
+      const int px = g->lx.n(), py = g->ly.n();
+      const int64_t np = static_cast<int64_t>(px) * py;
+      std::vector<double> gp(np);
+      for (int y = 0; y < py; ++y)
+        for (int x = 0; x < px; ++x) {
+          const int m = std::min(x, px - x), n = std::min(y, py - y);
+          gp[static_cast<int64_t>(y) * px + x] = (m <= p.nx - 1 && n <= p.ny - 1) ? green_mn(m, n, p.h) : 0.0;
         }
-      g->twx = static_cast<double2*>(upload(twiddles(g->px)));
-      g->twy = static_cast<double2*>(upload(twiddles(g->py)));
-      g->fw = static_cast<double2*>(upload(gp));
-      g->fw2 = static_cast<double2*>(dalloc(sizeof(double2) * np));
-      g->ghat = static_cast<double2*>(dalloc(sizeof(double2) * np));
-      fft_forward_2d(g, nullptr, -1, g->py);
-      hcheck(hipMemcpy(g->ghat, g->fw2, sizeof(double2) * np, hipMemcpyDeviceToDevice), "copy");
+      g->twx = static_cast<double2*>(upload(twiddles(px)));
+      g->twy = static_cast<double2*>(upload(twiddles(py)));
+      g->fw = static_cast<double2*>(dalloc(sizeof(double2) * qc::vecpot_work_elems(g->lx, g->ly)));
+      hcheck(qc::vecpot_prepare(g->lx, g->ly), "A-solve LDS");
+      g->ghat = static_cast<double*>(dalloc(sizeof(double) * np));
+      double* gd = static_cast<double*>(upload(gp));
+      qc::launch_vecpot_table(gd, g->lx, g->ly, g->twx, g->twy, g->fw, g->ghat, nullptr);
+      const hipError_t e = hipDeviceSynchronize();
+      (void)hipFree(gd);
+      hcheck(e, "A-solve table");
     }
     hcheck(hipDeviceSynchronize(), "grain setup");
     return QC_OK;
@@ -1237,8 +1222,9 @@ void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipS
   // mean current over the grain cells, subtracted before the solve (App. D)
   qc::launch_block_sum2({j, g->grain_cells, g->ncg, 0, region(g, kRJx)},
                         {j + g->ncell, g->grain_cells, g->ncg, 0, region(g, kRJy)}, kParts, st);
-  qc::launch_means(region(g, kRJx), kParts, 1.0 / static_cast<double>(g->ncg), g->dmean, st);
+  const double inv_n = 1.0 / static_cast<double>(g->ncg);
   if (g->a_nmodes > 0) {
+    qc::launch_means(region(g, kRJx), kParts, inv_n, g->dmean, st);
     // the separable kernel kept to its largest modes: two MFMA contractions
     qc::launch_masked_current(j, g->mask, g->ncell, g->dmean, g->a_jp, st);
     qc::launch_eig_vecpot(g->nx, g->a_nmodes, g->a_jp, g->a_vk, g->a_lam, g->a_y, A_out,
@@ -1247,14 +1233,9 @@ void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipS
     hcheck(hipGetLastError(), "A-solve launch");
     return;
   }
-  qc::launch_pad_current(j, g->mask, g->nx, g->ny, g->px, g->py, g->dmean, g->fw, st);
-  // the padded current is zero beyond row ny, and only rows < ny of the
-  // correlation are kept; the product with the kernel's transform is taken
-  // as the inverse pass loads its rows
-  fft_forward_2d(g, st, -1, g->ny);
-  fft_inverse_2d(g, st, g->ghat, g->ny);
-  const double scale = -1.0 / (g->kappa * g->kappa * static_cast<double>(g->px) * g->py);
-  qc::launch_unpad_A(g->fw, g->nx, g->ny, g->px, scale, A_out, st);
+  const double scale = -1.0 / (g->kappa * g->kappa * static_cast<double>(g->lx.n()) * g->ly.n());
+  qc::launch_vecpot_fft(j, g->mask, g->nx, g->ny, g->lx, g->ly, region(g, kRJx), kParts, inv_n, g->twx, g->twy, g->fw,
+                        g->ghat, scale, A_out, st);
   if (B_out) qc::launch_curl(A_out, B_out, g->nx, g->ny, g->h, st);
   hcheck(hipGetLastError(), "A-solve launch");
 }

@@ -11,7 +11,7 @@
 //                       gap update (Eq. gapeq_fixpoint), current
 //                       (Eq. current_density), free-energy density
 //   ldos_back_kernel    rotate-back of the per-energy LDOS values
-//   fft / A-solve / curl / reductions / Picard helpers (App. D, App. E)
+//   curl / reductions / Picard helpers (App. D, App. E)
 #include "kernels.hpp"
 #include "sweep.hpp"
 
@@ -1152,10 +1152,6 @@ __global__ void __launch_bounds__(256) congacc_update_kernel(double* __restrict_
   }
 }
 
-// --------------------------------------------------------------------------
-// A-solve (App. D): zero-padded FFT correlation with the cell-averaged
-// Green's function of the 2D Laplacian
-// --------------------------------------------------------------------------
 // grain means of the two current components from block partials (fixed
 // summation order, the same as a host-side sum of the partials)
 __global__ void __launch_bounds__(256) means_kernel(const double* __restrict__ part, int nparts, double inv_n,
@@ -1179,113 +1175,6 @@ __global__ void __launch_bounds__(256) means_kernel(const double* __restrict__ p
     mean[0] = sh[0][0] * inv_n;
     mean[1] = sh[1][0] * inv_n;
   }
-}
-
-__global__ void __launch_bounds__(256) pad_current_kernel(const double* __restrict__ j, const uint8_t* __restrict__ mask,
-                                                          int nx, int ny, int px, int py,
-                                                          const double* __restrict__ mean, double2* __restrict__ w) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<int64_t>(px) * py) return;
-  const int x = static_cast<int>(t % px), y = static_cast<int>(t / px);
-  double2 v = make_double2(0.0, 0.0);
-  if (x < nx && y < ny) {
-    const int64_t c = static_cast<int64_t>(y) * nx + x;
-    if (mask[c]) v = make_double2(j[c] - mean[0], j[static_cast<int64_t>(nx) * ny + c] - mean[1]);
-  }
-  w[t] = v;
-}
-
-// In-place radix-2 FFT of every row (length n = 2^logn) of a [rows][n]
-// complex array, one workgroup per row, staged in LDS.  sign = -1 forward.
-// pre (optional, same layout): the input is multiplied by it on the way in.
-__global__ void __launch_bounds__(256) fft_rows_kernel(double2* __restrict__ w, int logn,
-                                                       const double2* __restrict__ tw, int sign,
-                                                       const double2* __restrict__ pre) {
-  extern __shared__ double2 buf[];
-  const int n = 1 << logn;
-  double2* row = w + static_cast<int64_t>(blockIdx.x) * n;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const int r = static_cast<int>(__builtin_bitreverse32(static_cast<unsigned>(i)) >> (32 - logn));
-    double2 v = row[i];
-    if (pre) {
-      const double2 b = pre[static_cast<int64_t>(blockIdx.x) * n + i];
-      v = make_double2(v.x * b.x - v.y * b.y, v.x * b.y + v.y * b.x);
-    }
-    buf[r] = v;
-  }
-  __syncthreads();
-  // twiddle exp(-+2 pi i pos / 2^s) of stage s
-  auto twiddle = [&](int pos, int s) {
-    double2 tf = tw[pos << (logn - s)];
-    if (sign > 0) tf.y = -tf.y;
-    return tf;
-  };
-  auto butterfly = [](double2& u, double2& v, double2 tf) {
-    const double2 vt = make_double2(v.x * tf.x - v.y * tf.y, v.x * tf.y + v.y * tf.x);
-    v = make_double2(u.x - vt.x, u.y - vt.y);
-    u = make_double2(u.x + vt.x, u.y + vt.y);
-  };
-  // two radix-2 stages per pass, the four elements a thread combines held in
-  // registers: stage s pairs (i, i + h) and (i + 2h, i + 3h), stage s + 1
-  // pairs (i, i + 2h) and (i + h, i + 3h), h = 2^(s-1)
-  int s = 1;
-  for (; s + 1 <= logn; s += 2) {
-    const int h = 1 << (s - 1);
-    for (int b = threadIdx.x; b < n / 4; b += blockDim.x) {
-      const int grp = b / h, pos = b - grp * h;
-      const int i0 = grp * 4 * h + pos;
-      double2 x0 = buf[i0], x1 = buf[i0 + h], x2 = buf[i0 + 2 * h], x3 = buf[i0 + 3 * h];
-      const double2 t1 = twiddle(pos, s);
-      butterfly(x0, x1, t1);
-      butterfly(x2, x3, t1);
-      butterfly(x0, x2, twiddle(pos, s + 1));
-      butterfly(x1, x3, twiddle(pos + h, s + 1));
-      buf[i0] = x0;
-      buf[i0 + h] = x1;
-      buf[i0 + 2 * h] = x2;
-      buf[i0 + 3 * h] = x3;
-    }
-    __syncthreads();
-  }
-  if (s == logn) {  // odd logn: one radix-2 stage left
-    const int h = 1 << (s - 1);
-    for (int b = threadIdx.x; b < n / 2; b += blockDim.x) {
-      const int grp = b / h, pos = b - grp * h;
-      const int i0 = grp * 2 * h + pos;
-      double2 u = buf[i0], v = buf[i0 + h];
-      butterfly(u, v, twiddle(pos, s));
-      buf[i0] = u;
-      buf[i0 + h] = v;
-    }
-    __syncthreads();
-  }
-  for (int i = threadIdx.x; i < n; i += blockDim.x) row[i] = buf[i];
-}
-
-// out[x][y] = in[y][x] for a [rows][cols] complex array, 32x32 LDS tiles
-__global__ void __launch_bounds__(256) transpose_kernel(const double2* __restrict__ in, double2* __restrict__ out,
-                                                        int rows, int cols) {
-  __shared__ double2 tile[32][33];
-  const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
-  for (int r = threadIdx.y; r < 32; r += 8) {
-    const int y = by + r, x = bx + threadIdx.x;
-    if (y < rows && x < cols) tile[r][threadIdx.x] = in[static_cast<int64_t>(y) * cols + x];
-  }
-  __syncthreads();
-  for (int r = threadIdx.y; r < 32; r += 8) {
-    const int x = bx + r, y = by + threadIdx.x;
-    if (x < cols && y < rows) out[static_cast<int64_t>(x) * rows + y] = tile[threadIdx.x][r];
-  }
-}
-
-__global__ void __launch_bounds__(256) unpad_A_kernel(const double2* __restrict__ w, int nx, int ny, int px,
-                                                      double scale, double* __restrict__ A) {
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (c >= static_cast<int64_t>(nx) * ny) return;
-  const int x = static_cast<int>(c % nx), y = static_cast<int>(c / nx);
-  const double2 v = w[static_cast<int64_t>(y) * px + x];
-  A[c] = scale * v.x;
-  A[static_cast<int64_t>(nx) * ny + c] = scale * v.y;
 }
 
 // --------------------------------------------------------------------------
@@ -1517,21 +1406,4 @@ void launch_scale(const double* x, double s, int64_t n, double* y, hipStream_t s
 void launch_means(const double* part, int nparts, double inv_n, double* mean, hipStream_t st) {
   hipLaunchKernelGGL(means_kernel, dim3(1), dim3(256), 0, st, part, nparts, inv_n, mean);
 }
-void launch_pad_current(const double* j, const uint8_t* mask, int nx, int ny, int px, int py, const double* mean,
-                        double2* w, hipStream_t st) {
-  hipLaunchKernelGGL(pad_current_kernel, dim3(nblk(static_cast<int64_t>(px) * py)), dim3(256), 0, st, j, mask, nx,
-                     ny, px, py, mean, w);
-}
-void launch_fft_rows(double2* w, int rows, int logn, const double2* tw, int sign, const double2* pre, hipStream_t st) {
-  hipLaunchKernelGGL(fft_rows_kernel, dim3(rows), dim3(256), sizeof(double2) << logn, st, w, logn, tw, sign, pre);
-}
-void launch_transpose(const double2* in, double2* out, int rows, int cols, hipStream_t st) {
-  hipLaunchKernelGGL(transpose_kernel, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(32, 8), 0, st, in, out, rows,
-                     cols);
-}
-void launch_unpad_A(const double2* w, int nx, int ny, int px, double scale, double* A, hipStream_t st) {
-  hipLaunchKernelGGL(unpad_A_kernel, dim3(nblk(static_cast<int64_t>(nx) * ny)), dim3(256), 0, st, w, nx, ny, px,
-                     scale, A);
-}
-
 }  // namespace qc

@@ -331,10 +331,26 @@ void launch_masked_current(const double* j, const uint8_t* mask, int64_t ncell, 
 // per grain cell (x - cx) j_y - (y - cy) j_x, grain-cell order
 void launch_torque(const double* j, const int32_t* grain_cells, int64_t ncg, int64_t ncell, int nx, double x0,
                    double y0, double h, double cx, double cy, double* out, hipStream_t st);
-void launch_pad_current(const double* j, const uint8_t* mask, int nx, int ny, int px, int py, const double* mean,
-                        double2* w, hipStream_t st);
-void launch_fft_rows(double2* w, int rows, int logn, const double2* tw, int sign, const double2* pre, hipStream_t st);
-void launch_transpose(const double2* in, double2* out, int rows, int cols, hipStream_t st);
-void launch_unpad_A(const double2* w, int nx, int ny, int px, double scale, double* A, hipStream_t st);
+// FFT A-solve (vecpot.hip), padded grid px x py with px, py = r 2^k
+struct FftLen {
+  int r, k;
+  __host__ __device__ int n() const { return r << k; }
+};
+// the padded length for sequences of at least m elements
+FftLen fft_length(int m);
+// once per grain before the launches below (device current)
+hipError_t vecpot_prepare(FftLen lx, FftLen ly);
+// elements of the work array w
+int64_t vecpot_work_elems(FftLen lx, FftLen ly);
+// w: work; twx / twy: exp(-2 pi i j / n) for j < n; ghat: the
+// kernel's transform [px][py], in the order the column pass uses it.
+// Table of the kernel g [py][px]:
+void launch_vecpot_table(const double* g, FftLen lx, FftLen ly, const double2* twx, const double2* twy, double2* w,
+                         double* ghat, hipStream_t st);
+// A = scale x (correlation of the masked current minus its grain mean); part:
+// nparts partials of the grain sums of j_x, then of j_y
+void launch_vecpot_fft(const double* j, const uint8_t* mask, int nx, int ny, FftLen lx, FftLen ly, const double* part,
+                       int nparts, double inv_n, const double2* twx, const double2* twy, double2* w, double* ghat,
+                       double scale, double* A, hipStream_t st);
 
 }  // namespace qc
