@@ -66,10 +66,17 @@ void* upload(const std::vector<V>& v) {
   return p;
 }
 
+bool release_idle_workspaces();
+
 void* dalloc(size_t bytes) {
   void* p = nullptr;
   if (bytes == 0) return nullptr;
-  hcheck(hipMalloc(&p, bytes), "hipMalloc");
+  hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory && release_idle_workspaces()) {
+    (void)hipGetLastError();
+    e = hipMalloc(&p, bytes);
+  }
+  hcheck(e, "hipMalloc");
   return p;
 }
 
@@ -251,6 +258,7 @@ struct qc_plan {
 
 struct qc_grain {
   int device = 0;
+  size_t device_bytes = 0;  // memory of the device
   qc_plan_info info{};
   int nx = 0, ny = 0, ncomp = 0, n_theta = 0, n_poles = 0, precision = 0;
   double h = 0, t = 0, kappa = 0, q = -1, twopi_rz = 0;
@@ -382,6 +390,11 @@ struct qc_grain {
   double* lw_acc = nullptr;
   double* lw_dl = nullptr;
   void* lw_save = nullptr;
+  // work memory of the LDOS and Green's function calls, kept from call to
+  // call (see Lease)
+  void* ws = nullptr;
+  size_t ws_bytes = 0;
+  bool ws_busy = false;
   // profiling
   bool prof = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;
@@ -428,7 +441,96 @@ enum {
 
 namespace {
 
+// Work memory of the calls that need gigabytes for their own duration (LDOS,
+// Green's function): one block, kept by the grain when the call has ended.
+// Mapping and unmapping it on each call cost more than the call's kernels
+// (96 energies on 208 x 208 cells, 128 angles: 4.2 GB, 5 ms of kernels, 55 ms
+// alone and 121 ms back to back with the allocations).  What is kept is
+// bounded: together at most a 16th of a device's memory (a block beyond that
+// is freed when its call ends), every idle block on a device is freed when an
+// allocation on it fails, and a grain's when the grain is destroyed.
+std::mutex g_ws_mu;
+std::vector<qc_grain*> g_ws_owners;  // grains that hold a block
+
+// the grain's block, under g_ws_mu
+void drop_workspace(qc_grain* g) {
+  if (g->ws) (void)hipFree(g->ws);
+  g->ws = nullptr;
+  g->ws_bytes = 0;
+  g_ws_owners.erase(std::remove(g_ws_owners.begin(), g_ws_owners.end(), g), g_ws_owners.end());
+}
+
+// frees the idle blocks of the current device; false when there are none
+bool release_idle_workspaces() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lock(g_ws_mu);
+  bool any = false;
+  for (qc_grain* g : std::vector<qc_grain*>(g_ws_owners))
+    if (g->device == dev && !g->ws_busy) {
+      drop_workspace(g);
+      any = true;
+    }
+  return any;
+}
+
+class Lease {
+ public:
+  explicit Lease(qc_grain* g) : g_(g) {
+    std::lock_guard<std::mutex> lock(g_ws_mu);
+    g_->ws_busy = true;
+  }
+  Lease(const Lease&) = delete;
+  Lease& operator=(const Lease&) = delete;
+  // bytes already held, which the caller may count as free memory
+  size_t held() const { return g_->ws_bytes; }
+  // the block, at least `bytes` long
+  char* get(size_t bytes) {
+    if (g_->ws_bytes < bytes) {
+      {
+        std::lock_guard<std::mutex> lock(g_ws_mu);
+        drop_workspace(g_);
+      }
+      void* p = dalloc(bytes);
+      std::lock_guard<std::mutex> lock(g_ws_mu);
+      g_->ws = p;
+      g_->ws_bytes = bytes;
+      g_ws_owners.push_back(g_);
+    }
+    return static_cast<char*>(g_->ws);
+  }
+  // the call's work on the block has ended (its stream was waited for)
+  void done() { done_ = true; }
+  ~Lease() {
+    std::lock_guard<std::mutex> lock(g_ws_mu);
+    g_->ws_busy = false;
+    size_t kept = 0;
+    for (const qc_grain* o : g_ws_owners)
+      if (o->device == g_->device) kept += o->ws_bytes;
+    // (a call that failed may have left work in flight: hipFree waits for it)
+    if (!done_ || kept > g_->device_bytes / 16) drop_workspace(g_);
+  }
+
+ private:
+  qc_grain* g_;
+  bool done_ = false;
+};
+
+// consecutive pieces of a block
+struct Carve {
+  size_t off = 0;
+  size_t take(size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 255) & ~size_t(255);
+    return at;
+  }
+};
+
 void free_grain(qc_grain* g) {
+  {
+    std::lock_guard<std::mutex> lock(g_ws_mu);
+    drop_workspace(g);
+  }
   void* ptrs[] = {g->slot_angle, g->slot_px, g->slot_py, g->slot_fb, g->seg_geo, g->aext, g->eta, g->cosk,
                   g->sink, g->wk, g->seg_slot0, g->seg_n, g->seg_hfirst, g->seg_hlast, g->tap_s_seg,
                   g->tap_s_w, g->tap_e_seg, g->tap_e_w, g->grain_cells, g->rb_idx, g->rb_w, g->rb4, g->mask,
@@ -518,6 +620,31 @@ qc::BackArgs back_args(qc_grain* g, const double* delta, double* dnew, double* j
   r.omega = omega;
   r.omega_cell = g->omega_cell;
   return r;
+}
+
+// rotate-back of the per-energy values of ne energies from e_off on (LDOS,
+// Green's function)
+qc::LdosBackArgs ldos_back_args(const qc_grain* g, int ne, int e_off, double* out) {
+  qc::LdosBackArgs la{};
+  la.ncg = g->ncg;
+  la.ncell = g->ncell;
+  la.n_theta = g->n_theta;
+  la.n_e = ne;
+  la.e_off = e_off;
+  la.grain_cells = g->grain_cells;
+  la.rb4 = g->rb4;
+  la.nx = g->nx;
+  la.x0 = g->x0;
+  la.y0 = g->y0;
+  la.h = g->h;
+  la.cx = g->cx;
+  la.cy = g->cy;
+  la.half = g->half;
+  la.wk = g->wk;
+  la.cosk = g->cosk;
+  la.sink = g->sink;
+  la.out = out;
+  return la;
 }
 
 // node values of every slot, or (pair) of the slots of the lower angles of
@@ -907,6 +1034,7 @@ qc_status qc_grain_create(int device, const qc_grain_desc* desc, qc_grain** out)
       throw HipError(std::string("device is ") + prop.gcnArchName + ", this library is built for gfx950");
     hcheck(hipSetDevice(device), "hipSetDevice");
     g->device = device;
+    g->device_bytes = prop.totalGlobalMem;
     qc::Plan p;
     fill_plan_inputs(desc, p);
     qc::build_plan(p);
@@ -1670,13 +1798,7 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
   if (!(broadening > 0.0) || !std::isfinite(broadening)) return fail(QC_ERR_INVALID, "broadening must be > 0");
   for (int i = 0; i < n_e; ++i)
     if (!std::isfinite(energies[i])) return fail(QC_ERR_INVALID, "energies must be finite");
-  void* bcl[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
-  double* deps = nullptr;
-  int32_t* dpart = nullptr;
-  int32_t* dmap = nullptr;
-  void* lg = nullptr;
-  void* le = nullptr;
-  qc_status rs = guarded([&]() -> qc_status {
+  return guarded([&]() -> qc_status {
     hipStream_t st = S(stream);
     hcheck(hipSetDevice(g->device), "hipSetDevice");
     const size_t rb = g->real_bytes();
@@ -1710,18 +1832,53 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
       for (int j = 0; j < n_e; ++j) inv[perm[j]] = j;
       part_run.resize(static_cast<size_t>(n_e));
       for (int j = 0; j < n_e; ++j) part_run[j] = inv[partner[perm[j]]];
-      dpart = static_cast<int32_t*>(upload(part_run));
-      dmap = static_cast<int32_t*>(upload(perm));
     }
     std::vector<double> eps(2 * n_e);
     for (int i = 0; i < n_e; ++i) {
       eps[2 * i] = energies[perm[i]];
       eps[2 * i + 1] = broadening;
     }
-    deps = static_cast<double*>(upload(eps));
+    // output pass in energy blocks of up to 64 (long contiguous rows), bounded
+    // by half of the free device memory
+    Lease lease(g);
+    const double per_e = static_cast<double>(g->nslot) * 3.0 * rb;
+    double budget = static_cast<double>(1 << 30);
+    if (64 * per_e > budget) {
+      size_t free_b = 0, total_b = 0;
+      hcheck(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
+      budget = std::max(budget, 0.5 * static_cast<double>(free_b + lease.held()));
+    }
+    int blk = 64;
+    while (blk > 1 && blk * per_e > budget) blk >>= 1;
+    blk = std::min(blk, n_e);
+    // paired output: blocks of even size hold whole pairs (self-partners,
+    // last in the run order, pair with themselves)
+    const bool out_pair = pair && g->rb_fold && (blk % 2 == 0 || blk == n_e);
+    const int64_t out_slots = out_pair ? g->nslot_pair : g->nslot;
+    Carve cv;
+    const size_t o_eps = cv.take(sizeof(double) * 2 * n_e), o_part = cv.take(sizeof(int32_t) * n_e),
+                 o_map = cv.take(sizeof(int32_t) * n_e);
+    size_t o_bc[2][2];
     for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b) bcl[a][b] = dalloc(2 * rb * g->nseg * n_e);
-    do_interp(g, delta, A_ind, st);
+      for (int b = 0; b < 2; ++b) o_bc[a][b] = cv.take(2 * rb * g->nseg * n_e);
+    const size_t o_g = cv.take(2 * rb * out_slots * blk), o_e = cv.take(rb * out_slots * blk);
+    char* const ws = lease.get(cv.off);
+    void* bcl[2][2];
+    for (int a = 0; a < 2; ++a)
+      for (int b = 0; b < 2; ++b) bcl[a][b] = ws + o_bc[a][b];
+    double* const deps = reinterpret_cast<double*>(ws + o_eps);
+    int32_t* const dpart = reinterpret_cast<int32_t*>(ws + o_part);
+    int32_t* const dmap = pair ? reinterpret_cast<int32_t*>(ws + o_map) : nullptr;
+    void* const lg = ws + o_g;
+    void* const le = ws + o_e;
+    hcheck(hipMemcpyAsync(deps, eps.data(), sizeof(double) * eps.size(), hipMemcpyHostToDevice, st), "H2D");
+    if (pair) {
+      hcheck(hipMemcpyAsync(dpart, part_run.data(), sizeof(int32_t) * n_e, hipMemcpyHostToDevice, st), "H2D");
+      hcheck(hipMemcpyAsync(dmap, perm.data(), sizeof(int32_t) * n_e, hipMemcpyHostToDevice, st), "H2D");
+    }
+    // (the boundary sweeps of a paired set and its paired output march the
+    // lower angles only; an unpaired output pass reads every angle's slots)
+    do_interp(g, delta, A_ind, st, out_pair);
     const int blk_all = 256;  // energies of one boundary-only launch (64 lanes x 4)
     int cur = 0;
     qc::SweepBufs b;
@@ -1747,21 +1904,6 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
       }
       cur = 1 - cur;
     }
-    // output pass in energy blocks of up to 64 (32 lanes of two energies per
-    // segment: long contiguous gamma and LDOS rows), bounded by half of the
-    // free device memory
-    size_t free_b = 0, total_b = 0;
-    hcheck(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
-    const double budget = std::max(static_cast<double>(1 << 30), 0.5 * static_cast<double>(free_b));
-    const double per_e = static_cast<double>(g->nslot) * 3.0 * rb;
-    int blk = 64;
-    while (blk > 1 && blk * per_e > budget) blk >>= 1;
-    blk = std::min(blk, n_e);
-    // paired output: blocks of even size hold whole pairs (self-partners,
-    // last in the run order, pair with themselves)
-    const bool out_pair = pair && g->rb_fold && (blk % 2 == 0 || blk == n_e);
-    lg = dalloc(2 * rb * g->nslot * blk);
-    le = dalloc(rb * g->nslot * blk);
     qc::launch_fill(ldos_out, static_cast<int64_t>(n_e) * g->ncell, 0.0, st);
     for (int e0 = 0; e0 < n_e; e0 += blk) {
       const int ne = std::min(blk, n_e - e0);
@@ -1774,17 +1916,7 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
       b.gbuf = lg;
       b.ebuf = le;
       launch_sweep_timed(g, 1, a, b, st);
-      qc::LdosBackArgs la{};
-      la.ncg = g->ncg;
-      la.ncell = g->ncell;
-      la.n_theta = g->n_theta;
-      la.n_e = ne;
-      la.e_off = e0;
-      la.grain_cells = g->grain_cells;
-      la.rb_idx = g->rb_idx;
-      la.rb_w = g->rb_w;
-      la.wk = g->wk;
-      la.out = ldos_out;
+      qc::LdosBackArgs la = ldos_back_args(g, ne, e0, ldos_out);
       la.e_map = dmap;
       la.e_partner = out_pair ? dpart : nullptr;
       la.fold_k0 = out_pair ? g->n_theta / 2 : 0;
@@ -1795,17 +1927,9 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
       hcheck(hipGetLastError(), "ldos launch");
     }
     hcheck(hipStreamSynchronize(st), "sync");
+    lease.done();
     return QC_OK;
   });
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      if (bcl[a][b]) (void)hipFree(bcl[a][b]);
-  if (deps) (void)hipFree(deps);
-  if (dpart) (void)hipFree(dpart);
-  if (dmap) (void)hipFree(dmap);
-  if (lg) (void)hipFree(lg);
-  if (le) (void)hipFree(le);
-  return rs;
 }
 
 qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind, const double* energies, int n_e,
@@ -1818,12 +1942,7 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
   if (!(tol >= 0.0)) return fail(QC_ERR_INVALID, "tol must be >= 0");
   for (int i = 0; i < n_e; ++i)
     if (!std::isfinite(energies[i])) return fail(QC_ERR_INVALID, "energies must be finite");
-  void* bcl[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
-  double* deps = nullptr;
-  double* prev = nullptr;
-  void* lg = nullptr;
-  void* le = nullptr;
-  qc_status rs = guarded([&]() -> qc_status {
+  return guarded([&]() -> qc_status {
     hipStream_t st = S(stream);
     hcheck(hipSetDevice(g->device), "hipSetDevice");
     const size_t rb = g->real_bytes();
@@ -1832,25 +1951,39 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
       eps[2 * i] = energies[i];
       eps[2 * i + 1] = broadening;
     }
-    deps = static_cast<double*>(upload(eps));
+    Lease lease(g);
     do_interp(g, delta, A_ind, st);
     // energy block: the caller's, or the largest power of two up to 64 whose
     // gamma rows fit in half of the free device memory
     int blk = energies_per_block;
     if (blk == 0) {
-      size_t free_b = 0, total_b = 0;
-      hcheck(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
-      const double budget = std::max(static_cast<double>(1 << 30), 0.5 * static_cast<double>(free_b));
       const double per_e = static_cast<double>(g->nslot) * 3.0 * rb + 4.0 * rb * g->nseg;
+      double budget = static_cast<double>(1 << 30);
+      if (64 * per_e > budget) {
+        size_t free_b = 0, total_b = 0;
+        hcheck(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
+        budget = std::max(budget, 0.5 * static_cast<double>(free_b + lease.held()));
+      }
       blk = 64;
       while (blk > 1 && blk * per_e > budget) blk >>= 1;
     }
     blk = std::min(blk, n_e);
+    Carve cv;
+    const size_t o_eps = cv.take(sizeof(double) * 2 * n_e);
+    size_t o_bc[2][2];
     for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b) bcl[a][b] = dalloc(2 * rb * g->nseg * blk);
-    lg = dalloc(2 * rb * g->nslot * blk);
-    le = dalloc(rb * g->nslot * blk);
-    prev = static_cast<double*>(dalloc(sizeof(double) * blk * g->ncell));
+      for (int b = 0; b < 2; ++b) o_bc[a][b] = cv.take(2 * rb * g->nseg * blk);
+    const size_t o_g = cv.take(2 * rb * g->nslot * blk), o_e = cv.take(rb * g->nslot * blk),
+                 o_prev = cv.take(sizeof(double) * blk * g->ncell);
+    char* const ws = lease.get(cv.off);
+    void* bcl[2][2];
+    for (int a = 0; a < 2; ++a)
+      for (int b = 0; b < 2; ++b) bcl[a][b] = ws + o_bc[a][b];
+    double* const deps = reinterpret_cast<double*>(ws + o_eps);
+    double* const prev = reinterpret_cast<double*>(ws + o_prev);
+    void* const lg = ws + o_g;
+    void* const le = ws + o_e;
+    hcheck(hipMemcpyAsync(deps, eps.data(), sizeof(double) * eps.size(), hipMemcpyHostToDevice, st), "H2D");
     qc::launch_fill(ldos_out, static_cast<int64_t>(n_e) * g->ncell, 0.0, st);
     int worst = 0;
     for (int e0 = 0; e0 < n_e; e0 += blk) {
@@ -1874,17 +2007,7 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
         cur = 1 - cur;
         if (it > 0)
           hcheck(hipMemcpyAsync(prev, out, sizeof(double) * ne * g->ncell, hipMemcpyDeviceToDevice, st), "copy");
-        qc::LdosBackArgs la{};
-        la.ncg = g->ncg;
-        la.ncell = g->ncell;
-        la.n_theta = g->n_theta;
-        la.n_e = ne;
-        la.e_off = 0;
-        la.grain_cells = g->grain_cells;
-        la.rb_idx = g->rb_idx;
-        la.rb_w = g->rb_w;
-        la.wk = g->wk;
-        la.out = out;
+        qc::LdosBackArgs la = ldos_back_args(g, ne, 0, out);
         if (g->precision == QC_MIXED)
           qc::launch_ldos_back<float>(la, le, st);
         else
@@ -1916,37 +2039,37 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
       worst = std::max(worst, it);
     }
     hcheck(hipStreamSynchronize(st), "sync");
+    lease.done();
     if (iters_out) *iters_out = worst;
     return QC_OK;
   });
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      if (bcl[a][b]) (void)hipFree(bcl[a][b]);
-  for (void* p : {static_cast<void*>(deps), static_cast<void*>(prev), lg, le})
-    if (p) (void)hipFree(p);
-  return rs;
 }
 
 qc_status qc_green_average(qc_grain* g, const double* delta, const double* A_ind, double* g_out, void* stream) {
   if (!g) return fail(QC_ERR_INVALID, "grain is NULL");
   if (!delta || !A_ind || !g_out) return fail(QC_ERR_INVALID, "delta, A_ind and g_out are required");
-  void* lg = nullptr;
-  void* le = nullptr;
-  qc_status rs = guarded([&]() -> qc_status {
+  return guarded([&]() -> qc_status {
     hipStream_t st = S(stream);
     hcheck(hipSetDevice(g->device), "hipSetDevice");
     const size_t rb = g->real_bytes();
     do_interp(g, delta, A_ind, st);
     // poles in blocks of up to 64, bounded by half of the free device memory
-    size_t free_b = 0, total_b = 0;
-    hcheck(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
-    const double budget = std::max(static_cast<double>(1 << 30), 0.5 * static_cast<double>(free_b));
+    Lease lease(g);
     const double per_e = static_cast<double>(g->nslot) * 4.0 * rb;
+    double budget = static_cast<double>(1 << 30);
+    if (64 * per_e > budget) {
+      size_t free_b = 0, total_b = 0;
+      hcheck(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
+      budget = std::max(budget, 0.5 * static_cast<double>(free_b + lease.held()));
+    }
     int blk = 64;
     while (blk > 1 && blk * per_e > budget) blk >>= 1;
     blk = std::min(blk, g->n_poles);
-    lg = dalloc(2 * rb * g->nslot * blk);
-    le = dalloc(2 * rb * g->nslot * blk);
+    Carve cv;
+    const size_t o_g = cv.take(2 * rb * g->nslot * blk), o_e = cv.take(2 * rb * g->nslot * blk);
+    char* const ws = lease.get(cv.off);
+    void* const lg = ws + o_g;
+    void* const le = ws + o_e;
     qc::launch_fill(g_out, 2LL * g->n_poles * g->ncell, 0.0, st);
     qc::SweepBufs b;
     b.nodes = g->nodes;
@@ -1961,17 +2084,7 @@ qc_status qc_green_average(qc_grain* g, const double* delta, const double* A_ind
       qc::SweepArgs a = sweep_args(g, ne, g->n_poles, e0, g->eps, nullptr);
       a.bc_valid = g->bc_valid;  // the start values the next sweep would use
       launch_sweep_timed(g, 3, a, b, st);
-      qc::LdosBackArgs la{};
-      la.ncg = g->ncg;
-      la.ncell = g->ncell;
-      la.n_theta = g->n_theta;
-      la.n_e = ne;
-      la.e_off = e0;
-      la.grain_cells = g->grain_cells;
-      la.rb_idx = g->rb_idx;
-      la.rb_w = g->rb_w;
-      la.wk = g->wk;
-      la.out = g_out;
+      qc::LdosBackArgs la = ldos_back_args(g, ne, e0, g_out);
       if (g->precision == QC_MIXED)
         qc::launch_green_back<float>(la, le, st);
       else
@@ -1979,11 +2092,9 @@ qc_status qc_green_average(qc_grain* g, const double* delta, const double* A_ind
       hcheck(hipGetLastError(), "green launch");
     }
     hcheck(hipStreamSynchronize(st), "sync");
+    lease.done();
     return QC_OK;
   });
-  if (lg) (void)hipFree(lg);
-  if (le) (void)hipFree(le);
-  return rs;
 }
 
 qc_status qc_get_state(const qc_grain* g, void* state, size_t* bytes, void* stream) {

@@ -12,6 +12,8 @@
 //                       (Eq. current_density), free-energy density
 //   ldos_back_kernel    rotate-back of the per-energy LDOS values
 //   curl / reductions / Picard helpers (App. D, App. E)
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "sweep.hpp"
 
@@ -667,6 +669,38 @@ __global__ void reset_counter_kernel(int* counter) {
 constexpr int kBackWaves = 4;
 constexpr int kBackFields = 12;  // 2 x (up to 4 components) + jx, jy, I, <|Delta|^2>
 
+// Bilinear weights and slots of a cell's corner record ix on one angle's
+// lattice; corners that are not nodes read slot 0 with weight 0, so the four
+// gathers issue together.  Returns the factor that renormalises the weights.
+__device__ __forceinline__ double back_weights(int4 ix, double epx, double epy, double rx, double ry, double h,
+                                               double half, double w[4], int sl[4]) {
+  // lattice coordinates (line u, node v) of the cell centre
+  const double u = rn_lattice(rx, epy, ry, -epx, h, half);
+  const double v = rn_lattice(rx, epx, ry, epy, h, half);
+  const double wu = u - __builtin_floor(u), wv = v - __builtin_floor(v);
+  w[0] = (1 - wu) * (1 - wv);
+  w[1] = wu * (1 - wv);
+  w[2] = (1 - wu) * wv;
+  w[3] = wu * wv;
+  sl[0] = ix.x;
+  sl[1] = ix.y;
+  sl[2] = ix.z;
+  sl[3] = ix.w;
+  if (ix.y == -2) {  // no lattice corner is a node: the nearest node alone
+    w[0] = 1.0;
+    w[1] = w[2] = w[3] = 0.0;
+  }
+  double tot = 0.0;
+  for (int q = 0; q < 4; ++q) {
+    if (sl[q] < 0) {
+      w[q] = 0.0;
+      sl[q] = 0;
+    }
+    tot += w[q];
+  }
+  return (ix.x | ix.y | ix.z | ix.w) < 0 ? 1.0 / tot : 1.0;
+}
+
 // NC = 1: one order-parameter component (its arrays in fixed registers);
 // NC = 4: a.ncomp <= 4 components
 template <int NC>
@@ -720,28 +754,9 @@ __global__ void __launch_bounds__(64 * kBackWaves) rotate_back_kernel(BackArgs a
   for (; k < kend; k += kBackWaves) {
     const int4 ix = ixn;
     if (k + kBackWaves < kend) ixn = a.rb4[static_cast<int64_t>(k + kBackWaves) * a.ncg + c];
-    const double epx = a.cosk[k], epy = a.sink[k];
-    // lattice coordinates (line u, node v) of the cell centre
-    const double u = rn_lattice(rx, epy, ry, -epx, a.h, a.half);
-    const double v = rn_lattice(rx, epx, ry, epy, a.h, a.half);
-    const double wu = u - __builtin_floor(u), wv = v - __builtin_floor(v);
-    double w[4] = {(1 - wu) * (1 - wv), wu * (1 - wv), (1 - wu) * wv, wu * wv};
-    int sl[4] = {ix.x, ix.y, ix.z, ix.w};
-    if (ix.y == -2) {  // no lattice corner is a node: the nearest node alone
-      w[0] = 1.0;
-      w[1] = w[2] = w[3] = 0.0;
-    }
-    // corners that are not nodes read slot 0 with weight 0, so the four
-    // gathers issue together
-    double tot = 0.0;
-    for (int qd = 0; qd < 4; ++qd) {
-      if (sl[qd] < 0) {
-        w[qd] = 0.0;
-        sl[qd] = 0;
-      }
-      tot += w[qd];
-    }
-    const double rt = (ix.x | ix.y | ix.z | ix.w) < 0 ? 1.0 / tot : 1.0;
+    double w[4];
+    int sl[4];
+    const double rt = back_weights(ix, a.cosk[k], a.sink[k], rx, ry, a.h, a.half, w, sl);
     double cfx = 0.0, cfy = 0.0, cg = 0.0, ci = 0.0;
     for (int qd = 0; qd < 4; ++qd) {
       const double4 vv = nsum[sl[qd]];
@@ -812,59 +827,83 @@ __global__ void __launch_bounds__(256) mirror_fill_kernel(const int2* __restrict
   bc_gt[dst] = mk(g.x, -g.y);
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) ldos_back_kernel(LdosBackArgs a, const T* __restrict__ ebuf) {
-  // thread per (grain cell, energy of the block), energy fastest
-  const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t c = tid / a.n_e;
-  const int e = static_cast<int>(tid - c * a.n_e);
-  if (c >= a.ncg) return;
-  // with fold_k0 each lower angle's corners serve its upper angle too, at
-  // the partner energy (N of the reversed direction at e is N at -e)
+// Rotate-back and angle sums of the per-node, per-energy values of sweep mode
+// 1 (LDOS) or 3 (CPLX: -i pi times the average of a complex value).  A row of
+// a node holds M = n_e (CPLX: 2 n_e) reals; a thread takes V consecutive ones
+// (16 B loads where the row length allows) of one cell, tpc threads a cell,
+// and forms the corner weights once for all of them, from the 16 B corner
+// records that the sweep's rotate-back reads.  The sums meet in LDS, so that
+// a lower angle's sum reaches its partner energy and the output, energy by
+// energy, is written along the cells.
+// Bound by the gathers of the rows through L2.  With one thread per (cell,
+// energy), stored indices and weights (48 B per angle and thread), and the
+// partner energy gathered as well, the kernel waited on those loads: 926 us
+// for 43264 cells x 64 angle pairs x 64 energies, 247 us now.
+template <typename T, int V>
+struct __attribute__((aligned(V * sizeof(T) < 16 ? V * sizeof(T) : 16))) vecn {
+  T v[V];
+};
+template <typename T, int V, bool CPLX>
+__global__ void __launch_bounds__(256) ldos_back_kernel(LdosBackArgs a, const T* __restrict__ ebuf, int tpc, int cpb) {
+  extern __shared__ double sums[];
+  const int M = (CPLX ? 2 : 1) * a.n_e;
+  const int lc = static_cast<int>(threadIdx.x) / tpc, te = static_cast<int>(threadIdx.x) - lc * tpc;
+  const int mbase = static_cast<int>(blockIdx.y) * tpc * V, m0 = mbase + te * V;
+  const int64_t c0 = xcd_block(blockIdx.x, gridDim.x) * cpb, c = c0 + lc;
   const bool fold = a.fold_k0 > 0;
-  const int kend = fold ? a.fold_k0 : a.n_theta;
-  const int ep = fold ? a.e_partner[a.e_off + e] - a.e_off : e;
-  double acc = 0.0;
-  for (int k = 0; k < kend; ++k) {
-    double v = 0.0, vp = 0.0;
-    for (int qd = 0; qd < 4; ++qd) {
-      const int64_t o = (static_cast<int64_t>(k) * 4 + qd) * a.ncg + c;
-      const int64_t row = static_cast<int64_t>(a.rb_idx[o]) * a.n_e;
-      const double w = a.rb_w[o];
-      v += static_cast<double>(ebuf[row + e]) * w;
-      if (fold) vp += static_cast<double>(ebuf[row + ep]) * w;
+  const int width = tpc * V, pitch = width + 1;
+  double acc[V], accp[V];
+  for (int i = 0; i < V; ++i) acc[i] = accp[i] = 0.0;
+  if (lc < cpb && c < a.ncg && m0 < M) {
+    const int cell = a.grain_cells[c];
+    const double rx = rn_cell_offset(a.x0, static_cast<double>(cell % a.nx), a.h, a.cx);
+    const double ry = rn_cell_offset(a.y0, static_cast<double>(cell / a.nx), a.h, a.cy);
+    // with fold_k0 each lower angle's corners serve its upper angle too, at
+    // the partner energy (N of the reversed direction at e is N at -e)
+    const int kend = fold ? a.fold_k0 : a.n_theta;
+    int4 ixn = a.rb4[c];
+    for (int k = 0; k < kend; ++k) {
+      const int4 ix = ixn;
+      if (k + 1 < kend) ixn = a.rb4[static_cast<int64_t>(k + 1) * a.ncg + c];
+      double w[4];
+      int sl[4];
+      const double rt = back_weights(ix, a.cosk[k], a.sink[k], rx, ry, a.h, a.half, w, sl);
+      vecn<T, V> x[4];
+      for (int q = 0; q < 4; ++q)
+        x[q] = *reinterpret_cast<const vecn<T, V>*>(ebuf + static_cast<int64_t>(sl[q]) * M + m0);
+      const double wk = a.wk[k], wp = fold ? a.wk[k + a.fold_k0] : 0.0;
+      for (int i = 0; i < V; ++i) {
+        double v = 0.0;
+        for (int q = 0; q < 4; ++q) v += static_cast<double>(x[q].v[i]) * (w[q] * rt);
+        acc[i] += wk * v;
+        if (fold) accp[i] += wp * v;
+      }
     }
-    acc += a.wk[k] * v;
-    if (fold) acc += a.wk[k + a.fold_k0] * vp;
   }
-  const int64_t eo = a.e_map ? a.e_map[a.e_off + e] : a.e_off + e;
-  a.out[eo * a.ncell + a.grain_cells[c]] = acc;
-}
-
-// Fermi-surface average of g = -i pi (1-X)/(1+X) per cell and energy of the
-// block: the rotate-back of the complex per-node values of sweep mode 3
-template <typename T>
-__global__ void __launch_bounds__(256) green_back_kernel(LdosBackArgs a, const T* __restrict__ ebuf) {
-  const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t c = tid / a.n_e;
-  const int e = static_cast<int>(tid - c * a.n_e);
-  if (c >= a.ncg) return;
-  double ax = 0.0, ay = 0.0;
-  for (int k = 0; k < a.n_theta; ++k) {
-    double vx = 0.0, vy = 0.0;
-    for (int qd = 0; qd < 4; ++qd) {
-      const int64_t o = (static_cast<int64_t>(k) * 4 + qd) * a.ncg + c;
-      const int64_t src = 2 * (static_cast<int64_t>(a.rb_idx[o]) * a.n_e + e);
-      vx += static_cast<double>(ebuf[src]) * a.rb_w[o];
-      vy += static_cast<double>(ebuf[src + 1]) * a.rb_w[o];
+  if (lc < cpb)
+    for (int i = 0; i < V; ++i) {
+      sums[lc * pitch + te * V + i] = acc[i];
+      if (fold) sums[(cpb + lc) * pitch + te * V + i] = accp[i];
     }
-    ax += a.wk[k] * vx;
-    ay += a.wk[k] * vy;
+  __syncthreads();
+  const int ne = (CPLX ? width / 2 : width);  // energies of this block
+  for (int t = threadIdx.x; t < cpb * ne; t += 256) {
+    const int le = t / cpb, l = t - le * cpb;
+    const int e = (CPLX ? mbase / 2 : mbase) + le;
+    if (c0 + l >= a.ncg || e >= a.n_e) continue;
+    const int64_t cell = a.grain_cells[c0 + l];
+    if constexpr (CPLX) {
+      const double pi = 3.14159265358979323846;
+      double* o = a.out + 2 * (static_cast<int64_t>(a.e_off + e) * a.ncell + cell);
+      o[0] = pi * sums[l * pitch + 2 * le + 1];  // -i pi (re + i im)
+      o[1] = -pi * sums[l * pitch + 2 * le];
+    } else {
+      double v = sums[l * pitch + le];
+      if (fold) v += sums[(cpb + l) * pitch + (a.e_partner[a.e_off + e] - a.e_off)];
+      const int64_t eo = a.e_map ? a.e_map[a.e_off + e] : a.e_off + e;
+      a.out[eo * a.ncell + cell] = v;
+    }
   }
-  const double pi = 3.14159265358979323846;
-  double* o = a.out + 2 * (static_cast<int64_t>(a.e_off + e) * a.ncell + a.grain_cells[c]);
-  o[0] = pi * ay;   // -i pi (ax + i ay)
-  o[1] = -pi * ax;
 }
 
 // --------------------------------------------------------------------------
@@ -1325,18 +1364,36 @@ void launch_rotate_back(const BackArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(rotate_back_kernel<4>, dim3((a.ncg + 63) / 64), dim3(64 * kBackWaves), 0, st, a);
 }
 
+template <typename T, int V, bool CPLX>
+static void launch_back_v(const LdosBackArgs& a, const void* ebuf, hipStream_t st) {
+  const int M = (CPLX ? 2 : 1) * a.n_e;
+  const int tpc = std::min(M / V, 256), cpb = 256 / tpc;
+  const dim3 grid(static_cast<unsigned>((a.ncg + cpb - 1) / cpb), static_cast<unsigned>((M / V + tpc - 1) / tpc));
+  const size_t lds = sizeof(double) * cpb * (tpc * V + 1) * (a.fold_k0 > 0 ? 2 : 1);
+  hipLaunchKernelGGL((ldos_back_kernel<T, V, CPLX>), grid, dim3(256), lds, st, a, static_cast<const T*>(ebuf), tpc, cpb);
+}
+// the widest loads (up to 16 B) that the row length allows
+template <typename T, bool CPLX>
+static void launch_back_t(const LdosBackArgs& a, const void* ebuf, hipStream_t st) {
+  if (a.ncg == 0) return;
+  const int M = (CPLX ? 2 : 1) * a.n_e;
+  if (sizeof(T) == 4 && M % 4 == 0)
+    launch_back_v<T, 4, CPLX>(a, ebuf, st);
+  else if (M % 2 == 0)
+    launch_back_v<T, 2, CPLX>(a, ebuf, st);
+  else
+    launch_back_v<T, 1, CPLX>(a, ebuf, st);
+}
 template <typename T>
 void launch_ldos_back(const LdosBackArgs& a, const void* ebuf, hipStream_t st) {
-  hipLaunchKernelGGL(ldos_back_kernel<T>, dim3(nblk(a.ncg * a.n_e)), dim3(256), 0, st, a,
-                     static_cast<const T*>(ebuf));
+  launch_back_t<T, false>(a, ebuf, st);
 }
 template void launch_ldos_back<double>(const LdosBackArgs&, const void*, hipStream_t);
 template void launch_ldos_back<float>(const LdosBackArgs&, const void*, hipStream_t);
 
 template <typename T>
 void launch_green_back(const LdosBackArgs& a, const void* ebuf, hipStream_t st) {
-  hipLaunchKernelGGL(green_back_kernel<T>, dim3(nblk(a.ncg * a.n_e)), dim3(256), 0, st, a,
-                     static_cast<const T*>(ebuf));
+  launch_back_t<T, true>(a, ebuf, st);
 }
 template void launch_green_back<double>(const LdosBackArgs&, const void*, hipStream_t);
 template void launch_green_back<float>(const LdosBackArgs&, const void*, hipStream_t);

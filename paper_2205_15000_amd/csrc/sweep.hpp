@@ -123,15 +123,18 @@ struct LdosBackArgs {
   int64_t ncg, ncell;
   int n_theta, n_e, e_off;
   const int32_t* grain_cells;
-  const int32_t* rb_idx;
-  const double* rb_w;
+  const int4* rb4;  // corner records as in BackArgs
+  int nx;
+  double x0, y0, h, cx, cy, half;
   const double* wk;
+  const double* cosk;
+  const double* sink;
   double* out;  // [n_e_total][ny][nx]
   // e_map: output energy index of each energy of the launch order (nullptr:
   // e_off + e).  fold_k0 > 0 (LDOS only): the per-node values exist for the
   // angles k < fold_k0 alone; angle k + fold_k0 has the corners of angle k
   // and takes the values of energy e_partner[e] (both indices of the launch
-  // order, partners within the block)
+  // order, partners within the block, which then has at most 256 energies)
   const int32_t* e_map;
   const int32_t* e_partner;
   int fold_k0;
