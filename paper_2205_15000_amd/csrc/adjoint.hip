@@ -27,44 +27,49 @@ __device__ __forceinline__ C cdivd(C a, C b) {
 __device__ __forceinline__ C cscale(double s, C a) { return mk(s * a.x, s * a.y); }
 
 // Sums over the segment's lane group of the three slot gradients (Re, Im of
-// G_Delta and the gradient of a), written (or added) to o[0..2] by the
-// group's first lanes.
-__device__ __forceinline__ void put_slot_grad(double* o, double rx, double ry, double ra, int G, int lane,
-                                              bool add) {
+// G_Delta and the gradient of a), written to o[0..2] by the group's first lanes.
+__device__ __forceinline__ void put_slot_grad(double* o, double rx, double ry, double ra, int G, int lane) {
   if (G >= 4) {
     const double v = group_sum4_scatter(rx, ry, ra, 0.0, G, lane);
     const int qq = scatter_index(lane);
-    if (lane < 4 && qq < 3) o[qq] = add ? o[qq] + v : v;
+    if (lane < 4 && qq < 3) o[qq] = v;
   } else {
     rx = group_sum(rx, G);
     ry = group_sum(ry, G);
     ra = group_sum(ra, G);
     if (lane == 0) {
-      o[0] = add ? o[0] + rx : rx;
-      o[1] = add ? o[1] + ry : ry;
-      o[2] = add ? o[2] + ra : ra;
+      o[0] = rx;
+      o[1] = ry;
+      o[2] = ra;
     }
   }
 }
 
-struct StepDer {
-  C dg, dd, ddc, dz;
+// One step y = F(g; D, z, h) taken backwards for one energy: the adjoint l of
+// y becomes that of g.  With M = 2m = g + y, Q as above and u = l Q / |Q|^2
+// (= conj(1/Q) l) the four derivatives share all their products:
+//   adjoint of g   conj(2/Q - 1) l                       = 2u - l,
+//   gradient of D  conj(ih/Q) l + (ih m^2/Q) conj(l)     = ih (m v - u),  v = m conj(u),
+//   gradient of z  Re(conj(l) 2ih m/Q)                   = -2h Im v,
+// so the sums over the energies are taken of u, M (M conj(u)) and
+// Im(M conj(u)) and the factors are put on once per step.  hd = (h/2) D and
+// hz = h Re z are the step's, qx = 1 + h Im z the energy's.
+struct StepSum {
+  C u = {0.0, 0.0}, mmu = {0.0, 0.0};
+  double mu = 0.0;
 };
-
-// derivatives of y = F(g; d, z, h) given both ends g and y
-__device__ __forceinline__ StepDer step_der(C g, C y, C d, C z, double h) {
-  const C m = mk(0.5 * (g.x + y.x), 0.5 * (g.y + y.y));
-  const C dm = cconj(d) * m;
-  const C fp = mk(-2.0 * (dm.y + z.y), 2.0 * (dm.x + z.x));  // i (2 D* m + 2 z)
-  const C qd = mk(1.0 - 0.5 * h * fp.x, -0.5 * h * fp.y);
-  const C inv = cdivd(mk(1.0, 0.0), qd);
-  StepDer r;
-  r.dg = mk(2.0 * inv.x - 1.0, 2.0 * inv.y);  // (2 - Q)/Q
-  const C ih = mk(0.0, h);
-  r.dd = ih * inv;
-  r.ddc = ih * (m * m) * inv;
-  r.dz = cscale(2.0, ih * m * inv);
-  return r;
+__device__ __forceinline__ C step_back(C g, C y, C l, C hd, double hz, double qx, StepSum& sum) {
+  const C M = g + y;
+  const double Qx = fmaT(hd.x, M.y, fmaT(-hd.y, M.x, qx));
+  const double Qy = -fmaT(hd.x, M.x, fmaT(hd.y, M.y, hz));
+  const double r = drcp(fmaT(Qx, Qx, Qy * Qy));
+  const C u = mk(r * fmaT(Qx, l.x, -(Qy * l.y)), r * fmaT(Qx, l.y, Qy * l.x));
+  const C mu = mk(fmaT(M.x, u.x, M.y * u.y), fmaT(M.y, u.x, -(M.x * u.y)));  // M conj(u)
+  sum.u = sum.u + u;
+  sum.mmu.x = fmaT(M.x, mu.x, fmaT(-M.y, mu.y, sum.mmu.x));
+  sum.mmu.y = fmaT(M.x, mu.y, fmaT(M.y, mu.x, sum.mmu.y));
+  sum.mu += mu.y;
+  return mk(fmaT(2.0, u.x, -l.x), fmaT(2.0, u.y, -l.y));
 }
 
 // adjoint of y = bulk root(z, d) (start value) with adjoint gy: adds to
@@ -79,591 +84,350 @@ __device__ __forceinline__ void bulk_adj(C y, C z, C d, C gy, C& gd, double& gzr
   gzr += (cconj(gy) * dz).x;
 }
 
-// Node-local gradients of the per-node sums at one pole (Sec. II.A, Sec. II)
-// for gamma = gg, gamma~ = gv, node order parameter dn, sum gradients gs and
-// pole weight r: the adjoint of gamma (added to lam), of gamma~ (returned
-// in lgt) and of D through S_I (added to acc).
-__device__ __forceinline__ void node_adj(C gg, C gv, C dn, const double4& gs, double r, double pt, C& lam, C& lgt,
-                                         C& acc) {
-  const C gsf = mk(gs.x, gs.y);
-  const C x = gg * gv;
-  const C inv = cdivd(mk(1.0, 0.0), mk(1.0 + x.x, x.y));
-  const C inv2 = inv * inv;
-  const C kf = cconj(gsf) * mk(0.0, -pt * r);        // S_f = -i 2pi t~ R (u + conj v)
-  const C kg = mk(0.0, -0.5 * pt * r * gs.z);        // S_g = pi t~ R Im((1-X)/(1+X))
-  const C ki = mk(0.0, -pt * r * gs.w);              // S_I = 2pi t~ R Im(D* g - D g~)
-  const C agam = kf * inv2 - cconj(kf) * (gv * gv) * inv2 - cscale(2.0, kg * gv * inv2) + ki * cconj(dn);
-  const C agt = cconj(kf) * inv2 - kf * (gg * gg) * inv2 - cscale(2.0, kg * gg * inv2) - ki * dn;
-  lam = lam + cconj(agam);
-  lgt = cconj(agt);
-  acc = acc + ki * gg - cconj(ki * gv);  // G_D through S_I
+// Node-local gradients of the per-node sums (Sec. II.A, Sec. II), without the
+// pole weight: with P = 1 + gamma gamma~, D the node's order parameter and
+// pt = 2 pi t~,
+//   S_f = -i pt R (u + conj v),  S_g = (pt/2) R Im((1-X)/(1+X)),  S_I = pt R Im(D* g - D g~)
+// the adjoint of gamma is conj[(F - conj(F) g~^2 - 2 kg g~)/P^2 + ki conj(D)]
+// and that of gamma~ conj[(conj(F) - F g^2 - 2 kg g)/P^2 - ki D], with
+// F = -i pt conj(G_f) and kg = i c/2, ki = i k: constants of the node.
+struct NodeConst {
+  C f, add;  // F (conj(F) for gamma~) and conj(ki conj D) (-conj(ki D))
+  double c;
+};
+template <int DIR>
+__device__ __forceinline__ NodeConst node_const(C dn, const double4& gs, double pt) {
+  const double k = -pt * gs.w;
+  NodeConst n;
+  n.f = mk(-pt * gs.y, DIR * (-pt * gs.x));
+  n.add = DIR > 0 ? mk(k * dn.y, -k * dn.x) : mk(k * dn.y, k * dn.x);
+  n.c = -pt * gs.z;
+  return n;
+}
+// l plus r times the adjoint, of the own value's function by the other's value o
+__device__ __forceinline__ C node_adj(C own, C o, const NodeConst& n, double r, C l) {
+  const double Px = fmaT(own.x, o.x, fmaT(-own.y, o.y, 1.0)), Py = fmaT(own.x, o.y, own.y * o.x);
+  const double ip = drcp(fmaT(Px, Px, Py * Py));
+  // T = f - o (conj(f) o + i c)
+  const double ax = fmaT(n.f.x, o.x, n.f.y * o.y), ay = fmaT(n.f.x, o.y, fmaT(-n.f.y, o.x, n.c));
+  const double tx = fmaT(-o.x, ax, fmaT(o.y, ay, n.f.x)), ty = fmaT(-o.x, ay, fmaT(-o.y, ax, n.f.y));
+  // conj(T) P^2 / |P|^4
+  const double qx = fmaT(Px, Px, -(Py * Py)), qy = 2.0 * (Px * Py), w = r * (ip * ip);
+  return mk(fmaT(w, fmaT(tx, qx, ty * qy), fmaT(r, n.add.x, l.x)),
+            fmaT(w, fmaT(tx, qy, -(ty * qx)), fmaT(r, n.add.y, l.y)));
 }
 
-template <int EPL>
-__global__ void __launch_bounds__(256) adjoint_kernel(AdjArgs a, const node4<double>* __restrict__ nodes,
-                                                      const C* __restrict__ bc_g_prev,
-                                                      const C* __restrict__ bc_gt_prev, C* __restrict__ gbuf,
-                                                      C* __restrict__ gtbuf, C* __restrict__ lgt,
-                                                      const double4* __restrict__ gS, double* __restrict__ gV) {
-  const int64_t gtid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t wseg = gtid >> a.log2g;
-  const int lane = static_cast<int>(gtid & (a.G - 1));
-  if (wseg >= a.nseg) return;
-  const int64_t seg = a.order ? static_cast<int64_t>(a.order[wseg]) : wseg;
+// Reverse mode of one march: DIR = +1 that of gamma, -1 that of gamma~.  In
+// the order of the march the nodes are j = 0..n-1 (node j at slot j or
+// n - 1 - j), step j joins nodes j - 1 and j, step 0 comes from the start
+// value and step n goes to the far end, which nothing reads: its adjoint is
+// zero.  The wave marches its own function once (forward sweep order), then
+// walks back: at every node the other function, marched along in the same
+// direction, gives the local gradients of the sums; the adjoint of the own
+// function takes them up and passes through the step before.
+//
+// The own values on the way back: CK > 0 keeps the value entering every block
+// of CK nodes and marches a block again into a per-thread scratch when the
+// walk reaches it; CK = 0 keeps every node's value.  Both do the same steps on
+// the same inputs.
+//
+// The two directions share no intermediate value, so each is a wave of its
+// own (they write gradients of their own, which the gather adds).  One wave
+// that marched gamma, then gamma~ with the adjoint of gamma, then the adjoint
+// of gamma~ from values marched again took three passes over the segment
+// instead of two and had 1.6 waves a SIMD at 38% of the issue rate.  Bound by
+// FP64 issue: two marches, one marched again, a step and a node taken back
+// (step_back, node_adj: some 70 operations for 130 before).  200 x 200 disc,
+// 48 poles, checkpoints: 2.42 ms before, 1.65 ms as two waves, 1.38 ms with
+// the shorter step, 1.20 ms with two waves a SIMD (adjoint_kernel); d-wave
+// 400 x 400, 64 poles: 7.9 ms.
+template <int EPL, int DIR>
+__device__ __forceinline__ void adjoint_march(const AdjArgs& a, int64_t seg, int lane, int64_t thr,
+                                              const node4<double>* __restrict__ nodes, const C* __restrict__ bc_prev_own,
+                                              const C* __restrict__ bc_prev_oth, C* keep, int CK,
+                                              const int64_t* __restrict__ ckbase, C* scr, int64_t nthr,
+                                              const double4* __restrict__ gS, double* __restrict__ gV) {
+  constexpr double sd = DIR;  // D -> -D* for gamma~
   const int64_t slot0 = a.seg_slot0[seg];
   const int n = a.seg_n[seg];
   const int last = n > 0 ? n - 1 : 0;
-  const double hfirst = a.seg_hfirst[seg], hlast = a.seg_hlast[seg], hfull = a.h;
-  const double q = a.q;
+  const double hfull = a.h, q = a.q;
   const int e0 = lane * EPL;
-  double ex[EPL], ey[EPL], rw[EPL];
-  bool ok[EPL];
+  // a lane's energies beyond the last one repeat it with no weight (their
+  // adjoint stays zero) and store nothing
+  auto energy = [&](int i) { return min(e0 + i, a.n_e - 1); };
+  auto ok = [&](int i) { return e0 + i < a.n_e; };
+  double ey[EPL], rw[EPL];
   for (int i = 0; i < EPL; ++i) {
-    ok[i] = e0 + i < a.n_e;
-    const int e = ok[i] ? e0 + i : a.n_e - 1;
-    ex[i] = a.eps[2 * e];
-    ey[i] = a.eps[2 * e + 1];
-    rw[i] = ok[i] ? a.rp[e] : 0.0;
+    ey[i] = a.eps[2 * energy(i) + 1];  // (Matsubara poles: no real part)
+    rw[i] = ok(i) ? a.rp[energy(i)] : 0.0;
   }
-  auto hstep = [&](int t) { return t == 0 ? hfirst : (t == n ? hlast : hfull); };
-  auto mid = [&](int t, C& dm, double& am) {
-    const node4<double> lo = nodes[slot0 + (t >= 1 ? t - 1 : 0)];
-    const node4<double> up = nodes[slot0 + (t < last ? t : last)];
-    dm = mk(0.5 * (lo.dx + up.dx), 0.5 * (lo.dy + up.dy));
-    am = 0.5 * (lo.a + up.a);
-  };
-
-  // ---- pass 1: gamma forward, stored at the nodes
+  double* const out = gV + (DIR > 0 ? 0 : 3);
+  auto slot = [&](int j) { return static_cast<uint32_t>(DIR > 0 ? min(max(j, 0), last) : max(min(last - j, last), 0)); };
+  const node4<double>* const nseg = nodes + slot0;
+  if (n == 0) {  // no node: nothing reads this segment's marches
+    put_slot_grad(out + slot0 * 6, 0.0, 0.0, 0.0, a.G, lane);
+    return;
+  }
+  const double h_in = DIR > 0 ? a.seg_hfirst[seg] : a.seg_hlast[seg];
+  const double h_out = DIR > 0 ? a.seg_hlast[seg] : a.seg_hfirst[seg];
   const int64_t tb = seg * 4;
-  const bool staps = a.bc_valid && a.tap_start_w[tb] + a.tap_start_w[tb + 1] + a.tap_start_w[tb + 2] +
-                                           a.tap_start_w[tb + 3] > 0.0;
-  const bool etaps = a.bc_valid && a.tap_end_w[tb] + a.tap_end_w[tb + 1] + a.tap_end_w[tb + 2] +
-                                           a.tap_end_w[tb + 3] > 0.0;
-  C g0[EPL], g[EPL];
-  {
-    const node4<double> v0 = nodes[slot0];
+  // start value of the own (OWN) or the other march, from the taps or the
+  // bulk root; returns whether it came from the taps
+  auto start = [&](C* v, bool own_march) {
+    const bool at_min = own_march == (DIR > 0);  // gamma starts at s_min
+    const double* tw = (at_min ? a.tap_start_w : a.tap_end_w) + tb;
+    const int32_t* ts = (at_min ? a.tap_start_seg : a.tap_end_seg) + tb;
+    const C* bc = own_march ? bc_prev_own : bc_prev_oth;
+    const bool taps = a.bc_valid && tw[0] + tw[1] + tw[2] + tw[3] > 0.0;
+    const node4<double> v0 = nseg[slot(own_march ? 0 : n - 1)];
     for (int i = 0; i < EPL; ++i) {
-      if (staps) {
-        C acc = mk(0.0, 0.0);
+      if (taps) {
+        v[i] = mk(0.0, 0.0);
         for (int c = 0; c < 4; ++c)
-          acc = acc + cscale(a.tap_start_w[tb + c],
-                             bc_g_prev[static_cast<int64_t>(a.tap_start_seg[tb + c]) * a.n_e_tot + (ok[i] ? e0 + i : a.n_e - 1)]);
-        g0[i] = acc;
+          v[i] = v[i] + cscale(tw[c], bc[static_cast<int64_t>(ts[c]) * a.n_e_tot + energy(i)]);
       } else {
-        g0[i] = bulk_root(q * v0.a + ex[i], ey[i], v0.dx, v0.dy);
+        v[i] = bulk_root(q * v0.a, ey[i], at_min ? v0.dx : -v0.dx, v0.dy);
       }
-      g[i] = g0[i];
     }
-  }
-  for (int t = 0; t <= n; ++t) {
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    const StepC<double> sc = step_consts(dm.x, dm.y, hs);
-    for (int i = 0; i < EPL; ++i) g[i] = riccati_step_z(g[i], sc, hs, q * am + ex[i], ey[i]);
-    if (t < n)
-      for (int i = 0; i < EPL; ++i)
-        if (ok[i]) gbuf[(slot0 + t) * a.n_e + e0 + i] = g[i];
-  }
-  // g[] now holds gamma at R_max
+    return taps;
+  };
+  // full step between neighbouring slots; s = sd the own march, -sd the other
+  auto full_step = [&](C* v, const node4<double>& p, const node4<double>& c, double s) {
+    StepC<double> k = step_consts(0.5 * (s * (p.dx + c.dx)), 0.5 * (p.dy + c.dy), hfull);
+    const double ky = 0.5 * hfull * (q * (0.5 * (p.a + c.a)));
+    double kx[EPL], kx2[EPL];  // (formed here: held, they cost occupancy)
+    for (int i = 0; i < EPL; ++i) {
+      kx[i] = fmaT(-0.5 * hfull, ey[i], -0.5);
+      kx2[i] = kx[i] * kx[i];
+    }
+    riccati_steps<double, EPL, true>(v, k, kx, kx2, &ky);
+  };
+  // partial step next to an end, with the value of the slot there
+  auto end_step = [&](C* v, const node4<double>& p, double hs, double s) {
+    const StepC<double> k = step_consts(s * p.dx, p.dy, hs);
+    for (int i = 0; i < EPL; ++i) v[i] = riccati_step_z(v[i], k, hs, q * p.a, ey[i]);
+  };
+  const int64_t cb = CK > 0 ? ckbase[seg] : 0;
+  auto scr_at = [&](int pos, int i) -> C& { return scr[(static_cast<int64_t>(pos) * EPL + i) * nthr + thr]; };
+  auto keep_at = [&](int64_t row, int i) -> C& { return keep[row * a.n_e + energy(i)]; };
 
-  // ---- pass 2: gamma~ backward; node-local gradients; adjoint of gamma
-  C gt0[EPL], gt[EPL], lam[EPL];
+  // ---- the own march: its values kept
+  C x[EPL];
+  const bool taps = start(x, true);
   {
-    const node4<double> v1 = nodes[slot0 + last];
-    for (int i = 0; i < EPL; ++i) {
-      if (etaps) {
-        C acc = mk(0.0, 0.0);
-        for (int c = 0; c < 4; ++c)
-          acc = acc + cscale(a.tap_end_w[tb + c],
-                             bc_gt_prev[static_cast<int64_t>(a.tap_end_seg[tb + c]) * a.n_e_tot + (ok[i] ? e0 + i : a.n_e - 1)]);
-        gt0[i] = acc;
-      } else {
-        gt0[i] = bulk_root(q * v1.a + ex[i], ey[i], -v1.dx, v1.dy);
+    node4<double> prev = nseg[slot(0)], nxt = nseg[slot(1)];
+    end_step(x, prev, h_in, sd);
+    for (int j = 0;; ++j) {  // x at node j
+      if (CK == 0) {
+        for (int i = 0; i < EPL; ++i)
+          if (ok(i)) keep_at(slot0 + slot(j), i) = x[i];
+      } else if ((j + 1) % CK == 0 && j + 1 < n) {
+        for (int i = 0; i < EPL; ++i)
+          if (ok(i)) keep_at(cb + (j + 1) / CK, i) = x[i];
       }
-      gt[i] = gt0[i];
-      lam[i] = mk(0.0, 0.0);
+      if (j == n - 1) break;
+      const node4<double> cur = nxt;
+      nxt = nseg[slot(j + 2)];
+      full_step(x, prev, cur, sd);
+      prev = cur;
     }
-  }
-  const double pt = a.twopi_tt;  // 2 pi t~
-  // Step t feeds half of its gradient to slot max(t-1,0) and half to slot
-  // min(t,last).  Going down, slot t is complete once the local gradient at
-  // node t and the upper half of step t are in (plus, for slot 0, the lower
-  // half of step 0 and the bulk start); `carry` holds the lower half of the
-  // step just processed.
-  C carry = mk(0.0, 0.0);
-  double carrya = 0.0;
-  C gcur[EPL];  // gamma at slot t (at R_max for t = n), loaded once per slot
-  for (int i = 0; i < EPL; ++i) gcur[i] = g[i];
-  for (int t = n; t >= 0; --t) {
-    C acc = carry;
-    double acca = carrya;
-    if (t < n) {
-      // node t: gradients of the per-node sums (Sec. II.A, Sec. II)
-      const int64_t node = slot0 + t;
-      const node4<double> v = nodes[node];
-      const C dn = mk(v.dx, v.dy);
-      const double4 gs = gS[node];
-      for (int i = 0; i < EPL; ++i) {
-        if (!ok[i]) continue;
-        C lv;
-        node_adj(gcur[i], gt[i], dn, gs, rw[i], pt, lam[i], lv, acc);
-        lgt[node * a.n_e + e0 + i] = lv;
-        gtbuf[node * a.n_e + e0 + i] = gt[i];
-      }
-    }
-    // step t: adjoint of gamma_{t-1} -> gamma_t; primal gamma~_t -> gamma~_{t-1}
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    C stepD = mk(0.0, 0.0);
-    double stepa = 0.0;
-    const StepC<double> sc = step_consts(-dm.x, dm.y, hs);
-    for (int i = 0; i < EPL; ++i) {
-      const C z = mk(q * am + ex[i], ey[i]);
-      if (ok[i]) {
-        const C gl = t >= 1 ? gbuf[(slot0 + t - 1) * a.n_e + e0 + i] : g0[i];
-        const C gu = gcur[i];
-        gcur[i] = gl;
-        const StepDer sd = step_der(gl, gu, dm, z, hs);
-        const C l = lam[i];
-        stepD = stepD + cconj(sd.dd) * l + sd.ddc * cconj(l);
-        stepa += q * (cconj(l) * sd.dz).x;
-        lam[i] = cconj(sd.dg) * l;
-      }
-      gt[i] = riccati_step_z(gt[i], sc, hs, z.x, z.y);
-    }
-    if (t == n && n >= 1) {  // both halves of the last step go to slot n-1
-      carry = stepD;
-      carrya = stepa;
-      continue;
-    }
-    acc = acc + cscale(0.5, stepD);
-    acca += 0.5 * stepa;
-    carry = cscale(0.5, stepD);
-    carrya = 0.5 * stepa;
-    if (t == 0) {
-      acc = acc + carry;  // lower half of step 0 is slot 0 too
-      acca += carrya;
-      if (!staps) {       // gamma started at the bulk root of slot 0's values
-        const node4<double> v0 = nodes[slot0];
-        for (int i = 0; i < EPL; ++i) {
-          if (!ok[i]) continue;
-          double gz = 0.0;
-          bulk_adj(g0[i], mk(q * v0.a + ex[i], ey[i]), mk(v0.dx, v0.dy), lam[i], acc, gz);
-          acca += q * gz;
-        }
-      }
-    }
-    put_slot_grad(gV + (slot0 + t) * 3, acc.x, acc.y, acca, a.G, lane, false);
-  }
-  // gt[] now holds gamma~ at R_min
-
-  // ---- pass 3: adjoint of gamma~ (forward in t).  Step t maps gamma~_t to
-  // gamma~_{t-1}; slot t-1 is complete after step t (slot n-1 also takes
-  // both halves of step n and the bulk start at R_max).
-  C mu[EPL];
-  C gprv[EPL];  // gamma~ at slot t-1 (at R_min for t = 0), loaded once per slot
-  for (int i = 0; i < EPL; ++i) {
-    mu[i] = mk(0.0, 0.0);
-    gprv[i] = gt[i];
-  }
-  carry = mk(0.0, 0.0);
-  carrya = 0.0;
-  for (int t = 0; t <= n; ++t) {
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    const C dprime = mk(-dm.x, dm.y);  // -conj(dm)
-    C stepD = mk(0.0, 0.0);
-    double stepa = 0.0;
-    for (int i = 0; i < EPL; ++i) {
-      if (!ok[i]) continue;
-      const C z = mk(q * am + ex[i], ey[i]);
-      const C gu = t < n ? gtbuf[(slot0 + t) * a.n_e + e0 + i] : gt0[i];
-      const C gl = gprv[i];
-      gprv[i] = gu;
-      const StepDer sd = step_der(gu, gl, dprime, z, hs);
-      const C l = mu[i];
-      const C gdp = cconj(sd.dd) * l + sd.ddc * cconj(l);  // gradient of D' = -conj(dm)
-      stepD = stepD - cconj(gdp);
-      stepa += q * (cconj(l) * sd.dz).x;
-      mu[i] = cconj(sd.dg) * l;
-      if (t < n) mu[i] = mu[i] + lgt[(slot0 + t) * a.n_e + e0 + i];
-    }
-    if (t == 0) {
-      carry = stepD;  // both halves of step 0 belong to slot 0
-      carrya = stepa;
-      if (n >= 1) continue;
-    }
-    C acc;
-    double acca;
-    int slot;
-    if (t == 0) {  // n == 0
-      acc = carry;
-      acca = carrya;
-      slot = 0;
-    } else if (t < n) {
-      acc = carry + cscale(0.5, stepD);
-      acca = carrya + 0.5 * stepa;
-      carry = cscale(0.5, stepD);
-      carrya = 0.5 * stepa;
-      slot = t - 1;
-    } else {
-      acc = carry + stepD;
-      acca = carrya + stepa;
-      slot = last;
-    }
-    if (t == n && !etaps) {  // gamma~ started at the bulk root of the last slot
-      const node4<double> v1 = nodes[slot0 + last];
-      for (int i = 0; i < EPL; ++i) {
-        if (!ok[i]) continue;
-        double gz = 0.0;
-        C gdp = mk(0.0, 0.0);
-        bulk_adj(gt0[i], mk(q * v1.a + ex[i], ey[i]), mk(-v1.dx, v1.dy), mu[i], gdp, gz);
-        acc = acc - cconj(gdp);
-        acca += q * gz;
-      }
-    }
-    put_slot_grad(gV + (slot0 + slot) * 3, acc.x, acc.y, acca, a.G, lane, true);
-  }
-}
-
-// The same reverse mode with checkpoints every CK slots instead of gamma,
-// gamma~ and the gamma~ adjoint terms at every node: pass 1 keeps gamma
-// entering each block; pass 2 (backward) recomputes each block's gamma
-// forward from its checkpoint into a per-thread scratch and keeps gamma~ at
-// each block's first slot; pass 3 (forward) recomputes a block's gamma
-// forward and gamma~ backward (from the next block's checkpoint) and forms
-// the node-local gamma~ adjoint terms again.  The recomputation runs the same
-// steps on the same inputs as the stored variant.
-template <int EPL>
-__global__ void __launch_bounds__(256) adjoint_ckpt_kernel(AdjArgs a, const node4<double>* __restrict__ nodes,
-                                                           const C* __restrict__ bc_g_prev,
-                                                           const C* __restrict__ bc_gt_prev,
-                                                           const double4* __restrict__ gS, double* __restrict__ gV,
-                                                           int CK, const int64_t* __restrict__ ckbase,
-                                                           C* __restrict__ ckg, C* __restrict__ ckgt,
-                                                           C* __restrict__ scr, int64_t nthr) {
-  const int64_t gtid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t wseg = gtid >> a.log2g;
-  const int lane = static_cast<int>(gtid & (a.G - 1));
-  if (wseg >= a.nseg) return;
-  const int64_t seg = a.order ? static_cast<int64_t>(a.order[wseg]) : wseg;
-  const int64_t slot0 = a.seg_slot0[seg];
-  const int n = a.seg_n[seg];
-  const int last = n > 0 ? n - 1 : 0;
-  const double hfirst = a.seg_hfirst[seg], hlast = a.seg_hlast[seg], hfull = a.h;
-  const double q = a.q;
-  const int e0 = lane * EPL;
-  const int64_t cb = ckbase[seg];
-  double ex[EPL], ey[EPL], rw[EPL];
-  bool ok[EPL];
-  for (int i = 0; i < EPL; ++i) {
-    ok[i] = e0 + i < a.n_e;
-    const int e = ok[i] ? e0 + i : a.n_e - 1;
-    ex[i] = a.eps[2 * e];
-    ey[i] = a.eps[2 * e + 1];
-    rw[i] = ok[i] ? a.rp[e] : 0.0;
-  }
-  auto hstep = [&](int t) { return t == 0 ? hfirst : (t == n ? hlast : hfull); };
-  auto mid = [&](int t, C& dm, double& am) {
-    const node4<double> lo = nodes[slot0 + (t >= 1 ? t - 1 : 0)];
-    const node4<double> up = nodes[slot0 + (t < last ? t : last)];
-    dm = mk(0.5 * (lo.dx + up.dx), 0.5 * (lo.dy + up.dy));
-    am = 0.5 * (lo.a + up.a);
-  };
-  // scratch: region 0 gamma, region 1 gamma~, lane-interleaved
-  auto sc_at = [&](int region, int pos, int i) -> C& {
-    return scr[((static_cast<int64_t>(region) * CK + pos) * EPL + i) * nthr + gtid];
-  };
-  auto ck_at = [&](C* base, int kb, int i) -> C& { return base[(cb + kb) * a.n_e + e0 + i]; };
-
-  const int64_t tb = seg * 4;
-  const bool staps = a.bc_valid && a.tap_start_w[tb] + a.tap_start_w[tb + 1] + a.tap_start_w[tb + 2] +
-                                           a.tap_start_w[tb + 3] > 0.0;
-  const bool etaps = a.bc_valid && a.tap_end_w[tb] + a.tap_end_w[tb + 1] + a.tap_end_w[tb + 2] +
-                                           a.tap_end_w[tb + 3] > 0.0;
-  C g0[EPL], g[EPL];
-  {
-    const node4<double> v0 = nodes[slot0];
-    for (int i = 0; i < EPL; ++i) {
-      if (staps) {
-        C acc = mk(0.0, 0.0);
-        for (int c = 0; c < 4; ++c)
-          acc = acc + cscale(a.tap_start_w[tb + c],
-                             bc_g_prev[static_cast<int64_t>(a.tap_start_seg[tb + c]) * a.n_e_tot + (ok[i] ? e0 + i : a.n_e - 1)]);
-        g0[i] = acc;
-      } else {
-        g0[i] = bulk_root(q * v0.a + ex[i], ey[i], v0.dx, v0.dy);
-      }
-      g[i] = g0[i];
-    }
-  }
-  auto gamma_step = [&](C* gv, int t) {
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    const StepC<double> sc = step_consts(dm.x, dm.y, hs);
-    for (int i = 0; i < EPL; ++i) gv[i] = riccati_step_z(gv[i], sc, hs, q * am + ex[i], ey[i]);
-  };
-  auto gammat_step = [&](C* gv, int t) {
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    const StepC<double> sc = step_consts(-dm.x, dm.y, hs);
-    for (int i = 0; i < EPL; ++i) gv[i] = riccati_step_z(gv[i], sc, hs, q * am + ex[i], ey[i]);
-  };
-  // gamma at the slots of block kb (slots kb*CK .. min((kb+1)*CK, n) - 1)
-  auto recompute_gamma = [&](int kb) {
-    C gr[EPL];
-    for (int i = 0; i < EPL; ++i) gr[i] = kb == 0 ? g0[i] : (ok[i] ? ck_at(ckg, kb, i) : g0[i]);
-    const int s0 = kb * CK, s1 = min(s0 + CK, n);
-    for (int s = s0; s < s1; ++s) {
-      gamma_step(gr, s);
-      for (int i = 0; i < EPL; ++i) sc_at(0, s - s0, i) = gr[i];
-    }
-  };
-
-  // ---- pass 1: gamma forward, kept entering each block
-  for (int t = 0; t <= n; ++t) {
-    gamma_step(g, t);
-    if (t + 1 < n && (t + 1) % CK == 0)
-      for (int i = 0; i < EPL; ++i)
-        if (ok[i]) ck_at(ckg, (t + 1) / CK, i) = g[i];
   }
 
-  // ---- pass 2: gamma~ backward; node-local gradients; adjoint of gamma
-  C gt0[EPL], gt[EPL], lam[EPL];
-  {
-    const node4<double> v1 = nodes[slot0 + last];
-    for (int i = 0; i < EPL; ++i) {
-      if (etaps) {
-        C acc = mk(0.0, 0.0);
-        for (int c = 0; c < 4; ++c)
-          acc = acc + cscale(a.tap_end_w[tb + c],
-                             bc_gt_prev[static_cast<int64_t>(a.tap_end_seg[tb + c]) * a.n_e_tot + (ok[i] ? e0 + i : a.n_e - 1)]);
-        gt0[i] = acc;
-      } else {
-        gt0[i] = bulk_root(q * v1.a + ex[i], ey[i], -v1.dx, v1.dy);
-      }
-      gt[i] = gt0[i];
-      lam[i] = mk(0.0, 0.0);
-    }
-  }
-  const double pt = a.twopi_tt;  // 2 pi t~
-  C carry = mk(0.0, 0.0);
-  double carrya = 0.0;
-  C gcur[EPL];  // gamma at slot t (at R_max for t = n)
-  for (int i = 0; i < EPL; ++i) gcur[i] = g[i];
+  // (a lane may read what another lane of its wave kept: the last energy)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+  // ---- back along the segment
   int loaded = -1;
-  for (int t = n; t >= 0; --t) {
+  // own value at node j < n - 1 (start value for j = -1)
+  auto recall = [&](C* v, int j) {
+    if (j < 0) {
+      start(v, true);
+      return;
+    }
+    if (CK == 0) {
+      for (int i = 0; i < EPL; ++i) v[i] = keep_at(slot0 + slot(j), i);
+      return;
+    }
+    const int kb = j / CK, s0 = kb * CK;
+    if (kb != loaded) {  // march block kb again, up to node j
+      loaded = kb;
+      C r[EPL];
+      if (kb == 0) {
+        start(r, true);
+      } else {
+        for (int i = 0; i < EPL; ++i) r[i] = keep_at(cb + kb, i);
+      }
+      node4<double> prev = nseg[slot(s0 - 1)], nxt = nseg[slot(s0)];
+      for (int s = s0; s <= j; ++s) {
+        const node4<double> cur = nxt;
+        nxt = nseg[slot(s + 1)];
+        if (s == 0)
+          end_step(r, cur, h_in, sd);
+        else
+          full_step(r, prev, cur, sd);
+        prev = cur;
+        for (int i = 0; i < EPL; ++i) scr_at(s - s0, i) = r[i];
+      }
+    }
+    for (int i = 0; i < EPL; ++i) v[i] = scr_at(j - s0, i);
+  };
+  C y[EPL], lam[EPL];
+  start(y, false);
+  for (int i = 0; i < EPL; ++i) lam[i] = mk(0.0, 0.0);
+  const double pt = a.twopi_tt;  // 2 pi t~
+  // Step j gives half of its slot gradient to slot j - 1 and half to slot j
+  // (step 0 both to slot 0); `carry` holds the half of the step just taken
+  // that belongs to the next slot.
+  C carry = mk(0.0, 0.0);
+  double carrya = 0.0;
+  node4<double> cur = nseg[slot(n - 1)], nxt = nseg[slot(n - 2)];
+  double4 gsn = gS[slot0 + slot(n - 1)];
+  end_step(y, cur, h_out, -sd);
+  for (int j = n - 1; j >= 0; --j) {  // x, y at node j; cur, nxt the slots j and j - 1
+    const double4 gs = gsn;
+    gsn = gS[slot0 + slot(j - 1)];
+    C xl[EPL];
+    recall(xl, j - 1);
+    const node4<double> lo = nxt;
+    nxt = nseg[slot(j - 2)];
+    const C dn = mk(cur.dx, cur.dy);
     C acc = carry;
     double acca = carrya;
-    if (t < n) {
-      const int64_t node = slot0 + t;
-      const node4<double> v = nodes[node];
-      const C dn = mk(v.dx, v.dy);
-      const double4 gs = gS[node];
-      for (int i = 0; i < EPL; ++i) {
-        if (!ok[i]) continue;
-        C lv;
-        node_adj(gcur[i], gt[i], dn, gs, rw[i], pt, lam[i], lv, acc);
-        if (t > 0 && t % CK == 0) ck_at(ckgt, t / CK, i) = gt[i];
-      }
-    }
-    if (t >= 1 && (t - 1) / CK != loaded) {
-      loaded = (t - 1) / CK;
-      recompute_gamma(loaded);
-    }
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    C stepD = mk(0.0, 0.0);
-    double stepa = 0.0;
-    const StepC<double> sc = step_consts(-dm.x, dm.y, hs);
+    // half-step values of step j (slot 0's alone for j = 0)
+    const node4<double>& lw = j > 0 ? lo : cur;
+    const double za = q * (0.5 * (lw.a + cur.a)), hs = j > 0 ? hfull : h_in;
+    const C hd = mk(0.25 * hs * (sd * (lw.dx + cur.dx)), 0.25 * hs * (lw.dy + cur.dy));
+    const NodeConst nc = node_const<DIR>(dn, gs, pt);
+    StepSum sum;
+    C si = mk(0.0, 0.0);
     for (int i = 0; i < EPL; ++i) {
-      const C z = mk(q * am + ex[i], ey[i]);
-      if (ok[i]) {
-        const C gl = t >= 1 ? sc_at(0, (t - 1) - loaded * CK, i) : g0[i];
-        const C gu = gcur[i];
-        gcur[i] = gl;
-        const StepDer sd = step_der(gl, gu, dm, z, hs);
-        const C l = lam[i];
-        stepD = stepD + cconj(sd.dd) * l + sd.ddc * cconj(l);
-        stepa += q * (cconj(l) * sd.dz).x;
-        lam[i] = cconj(sd.dg) * l;
+      lam[i] = node_adj(x[i], y[i], nc, rw[i], lam[i]);
+      if (DIR > 0) {
+        si.x = fmaT(rw[i], y[i].y - x[i].y, si.x);
+        si.y = fmaT(rw[i], x[i].x + y[i].x, si.y);
       }
-      gt[i] = riccati_step_z(gt[i], sc, hs, z.x, z.y);
+      lam[i] = step_back(xl[i], x[i], lam[i], hd, hs * za, fmaT(hs, ey[i], 1.0), sum);
     }
-    if (t == n && n >= 1) {
-      carry = stepD;
-      carrya = stepa;
-      continue;
-    }
+    if (DIR > 0) acc = acc + cscale(-pt * gs.w, si);  // D in S_I: ki g - conj(ki g~)
+    C stepD = mk(-hs * fmaT(0.25, sum.mmu.y, -sum.u.y), hs * fmaT(0.25, sum.mmu.x, -sum.u.x));
+    const double stepa = -hs * q * sum.mu;
+    if (DIR < 0) stepD = mk(-stepD.x, stepD.y);  // gradient of D from that of -D*
     acc = acc + cscale(0.5, stepD);
     acca += 0.5 * stepa;
     carry = cscale(0.5, stepD);
     carrya = 0.5 * stepa;
-    if (t == 0) {
+    if (j == 0) {
       acc = acc + carry;
       acca += carrya;
-      if (!staps) {
-        const node4<double> v0 = nodes[slot0];
-        for (int i = 0; i < EPL; ++i) {
-          if (!ok[i]) continue;
-          double gz = 0.0;
-          bulk_adj(g0[i], mk(q * v0.a + ex[i], ey[i]), mk(v0.dx, v0.dy), lam[i], acc, gz);
-          acca += q * gz;
-        }
-      }
-    }
-    put_slot_grad(gV + (slot0 + t) * 3, acc.x, acc.y, acca, a.G, lane, false);
-  }
-
-  // ---- pass 3: adjoint of gamma~, forward, block by block
-  C mu[EPL];
-  C gprv[EPL];
-  for (int i = 0; i < EPL; ++i) {
-    mu[i] = mk(0.0, 0.0);
-    gprv[i] = gt[i];
-  }
-  carry = mk(0.0, 0.0);
-  carrya = 0.0;
-  loaded = -1;
-  for (int t = 0; t <= n; ++t) {
-    if (t < n && t / CK != loaded) {
-      loaded = t / CK;
-      recompute_gamma(loaded);
-      // gamma~ over the block, backward from the next block's first slot
-      const int s0 = loaded * CK, s1 = min(s0 + CK, n);
-      C gv[EPL];
-      for (int i = 0; i < EPL; ++i) gv[i] = s1 == n ? gt0[i] : (ok[i] ? ck_at(ckgt, s1 / CK, i) : gt0[i]);
-      for (int s = s1; s > s0; --s) {
-        gammat_step(gv, s);
-        for (int i = 0; i < EPL; ++i) sc_at(1, s - 1 - s0, i) = gv[i];
-      }
-    }
-    C dm;
-    double am;
-    mid(t, dm, am);
-    const double hs = hstep(t);
-    const C dprime = mk(-dm.x, dm.y);
-    C stepD = mk(0.0, 0.0);
-    double stepa = 0.0;
-    node4<double> v;
-    double4 gs;
-    if (t < n) {
-      v = nodes[slot0 + t];
-      gs = gS[slot0 + t];
-    }
-    for (int i = 0; i < EPL; ++i) {
-      if (!ok[i]) continue;
-      const C z = mk(q * am + ex[i], ey[i]);
-      const C gu = t < n ? sc_at(1, t - loaded * CK, i) : gt0[i];
-      const C gl = gprv[i];
-      gprv[i] = gu;
-      const StepDer sd = step_der(gu, gl, dprime, z, hs);
-      const C l = mu[i];
-      const C gdp = cconj(sd.dd) * l + sd.ddc * cconj(l);
-      stepD = stepD - cconj(gdp);
-      stepa += q * (cconj(l) * sd.dz).x;
-      mu[i] = cconj(sd.dg) * l;
-      if (t < n) {
-        C lamd = mk(0.0, 0.0), accd = mk(0.0, 0.0), lv;
-        node_adj(sc_at(0, t - loaded * CK, i), gu, mk(v.dx, v.dy), gs, rw[i], pt, lamd, lv, accd);
-        mu[i] = mu[i] + lv;
-      }
-    }
-    if (t == 0) {
-      carry = stepD;
-      carrya = stepa;
-      if (n >= 1) continue;
-    }
-    C acc;
-    double acca;
-    int slot;
-    if (t == 0) {
-      acc = carry;
-      acca = carrya;
-      slot = 0;
-    } else if (t < n) {
-      acc = carry + cscale(0.5, stepD);
-      acca = carrya + 0.5 * stepa;
-      carry = cscale(0.5, stepD);
-      carrya = 0.5 * stepa;
-      slot = t - 1;
-    } else {
-      acc = carry + stepD;
-      acca = carrya + stepa;
-      slot = last;
-    }
-    if (t == n && !etaps) {
-      const node4<double> v1 = nodes[slot0 + last];
-      for (int i = 0; i < EPL; ++i) {
-        if (!ok[i]) continue;
+      if (!taps) {  // the march started at the bulk root of this slot's values
+        C gd = mk(0.0, 0.0);
         double gz = 0.0;
-        C gdp = mk(0.0, 0.0);
-        bulk_adj(gt0[i], mk(q * v1.a + ex[i], ey[i]), mk(-v1.dx, v1.dy), mu[i], gdp, gz);
-        acc = acc - cconj(gdp);
+        for (int i = 0; i < EPL; ++i)
+          if (ok(i)) bulk_adj(xl[i], mk(q * cur.a, ey[i]), mk(sd * cur.dx, cur.dy), lam[i], gd, gz);
+        acc = acc + (DIR > 0 ? gd : mk(-gd.x, gd.y));
         acca += q * gz;
       }
     }
-    put_slot_grad(gV + (slot0 + slot) * 3, acc.x, acc.y, acca, a.G, lane, true);
+    put_slot_grad(out + (slot0 + slot(j)) * 6, acc.x, acc.y, acca, a.G, lane);
+    if (j > 0) full_step(y, lo, cur, -sd);
+    for (int i = 0; i < EPL; ++i) x[i] = xl[i];
+    cur = lo;
   }
+}
+
+// blocks of two waves: the two directions of one bundle of 64/G segments.
+// Three energies a lane need 261 registers and are held to the 256 that leave
+// room for a second wave on the SIMD (nothing is spilled: 1.38 -> 1.20 ms);
+// four and eight need more than can be taken away.
+template <int EPL>
+__global__ void __launch_bounds__(128, EPL == 3 ? 2 : 1) adjoint_kernel(AdjArgs a, AdjBufs b) {
+  const int l64 = threadIdx.x & 63;
+  const int dir = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int64_t wseg = (static_cast<int64_t>(blockIdx.x) << (6 - a.log2g)) + (l64 >> a.log2g);
+  if (wseg >= a.nseg) return;  // whole lane groups leave together (G | 64)
+  const int lane = l64 & (a.G - 1);
+  const int64_t seg = a.order ? static_cast<int64_t>(a.order[wseg]) : wseg;
+  const int64_t thr = static_cast<int64_t>(blockIdx.x) * 128 + threadIdx.x;
+  const node4<double>* nodes = static_cast<const node4<double>*>(b.nodes);
+  const C* bg = static_cast<const C*>(b.bc_g_prev);
+  const C* bgt = static_cast<const C*>(b.bc_gt_prev);
+  const double4* gS = static_cast<const double4*>(b.gS);
+  if (dir == 0)
+    adjoint_march<EPL, 1>(a, seg, lane, thr, nodes, bg, bgt, static_cast<C*>(b.keep_g), b.ck, b.ckbase,
+                          static_cast<C*>(b.scr), b.nthr, gS, b.gV);
+  else
+    adjoint_march<EPL, -1>(a, seg, lane, thr, nodes, bgt, bg, static_cast<C*>(b.keep_gt), b.ck, b.ckbase,
+                           static_cast<C*>(b.scr), b.nthr, gS, b.gV);
+}
+
+// The cell gradients a rotated lattice gathers, one record per grain cell:
+// (G_{Delta_new,G} / den_G for every component, G_jx, G_jy).
+__global__ void __launch_bounds__(256) cell_grad_kernel(BackAdjArgs a) {
+  const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (c >= a.ncg) return;
+  const int64_t cell = a.grain_cells[c];
+  double* const o = a.gC + c * (2 * a.ncomp + 2);
+  for (int g = 0; g < a.ncomp; ++g) {
+    o[2 * g] = a.gdn ? a.gdn[2 * (g * a.ncell + cell)] / a.den[g] : 0.0;
+    o[2 * g + 1] = a.gdn ? a.gdn[2 * (g * a.ncell + cell) + 1] / a.den[g] : 0.0;
+  }
+  o[2 * a.ncomp] = a.gj ? a.gj[cell] : 0.0;
+  o[2 * a.ncomp + 1] = a.gj ? a.gj[a.ncell + cell] : 0.0;
 }
 
 // Gradients of the per-node sums from the cell gradients: the transpose of
 // the rotate-back gather, formed as a gather per slot over the cells whose
 // rotate-back stencil uses it (no atomics; each slot written once).
+// Bound by its table (12 B an entry, about eight entries a slot with paired
+// angles).  Four lanes share a slot: the lanes of a wave then read the table
+// in order, where a lane per slot walked its own row, 64 rows at once in the
+// cache, and waited for each entry's cell, gradient and two divisions in turn
+// (135 us, 60 us now with the records, on the 200 x 200 disc;
+// 1347 and 310 us on d-wave 400 x 400).
+constexpr int kBtLanes = 4;
 __global__ void __launch_bounds__(256) back_adjoint_kernel(BackAdjArgs a) {
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (s >= a.nslot) return;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t s = t / kBtLanes;
+  const int lane = static_cast<int>(t & (kBtLanes - 1));
+  if (s >= a.nslot) return;  // whole groups of four leave together
   const int k = a.slot_angle[s];
-  const double wk = a.wk[k], ck = a.cosk[k], sk = a.sink[k];
+  const double ck = a.cosk[k], sk = a.sink[k];
   double ex[4], ey[4];
   for (int g = 0; g < a.ncomp; ++g) {
     ex[g] = a.eta[2 * (g * a.n_theta + k)];
     ey[g] = a.eta[2 * (g * a.n_theta + k) + 1];
   }
   double sx = 0.0, sy = 0.0, sj = 0.0, sw = 0.0;
-  for (int64_t e = a.bt_ptr[s]; e < a.bt_ptr[s + 1]; ++e) {
+  const int64_t end = a.bt_ptr[s + 1];
+  for (int64_t e = a.bt_ptr[s] + lane; e < end; e += kBtLanes) {
     const double w = a.bt_w[e];
-    const int64_t cell = a.grain_cells[a.bt_c[e]];
+    const double* const r = a.gC + static_cast<int64_t>(a.bt_c[e]) * (2 * a.ncomp + 2);
     // G_{S_f} = wk sum_G eta_G G_{Num_G}, G_{Num_G} = G_{Delta_new,G} / den_G
-    if (a.gdn) {
-      double fx = 0.0, fy = 0.0;
-      for (int g = 0; g < a.ncomp; ++g) {
-        const double nx = a.gdn[2 * (g * a.ncell + cell)] / a.den[g];
-        const double ny = a.gdn[2 * (g * a.ncell + cell) + 1] / a.den[g];
-        fx += ex[g] * nx - ey[g] * ny;
-        fy += ex[g] * ny + ey[g] * nx;
-      }
-      sx += w * fx;
-      sy += w * fy;
+    double fx = 0.0, fy = 0.0;
+    for (int g = 0; g < a.ncomp; ++g) {
+      fx += ex[g] * r[2 * g] - ey[g] * r[2 * g + 1];
+      fy += ex[g] * r[2 * g + 1] + ey[g] * r[2 * g];
     }
-    if (a.gj) sj += w * (ck * a.gj[cell] + sk * a.gj[a.ncell + cell]);
+    sx += w * fx;
+    sy += w * fy;
+    sj += w * (ck * r[2 * a.ncomp] + sk * r[2 * a.ncomp + 1]);
     sw += w;
   }
-  double4 o;
-  o.x = wk * sx;
-  o.y = wk * sy;
-  o.z = a.four_q * wk * sj;
-  o.w = wk * (-a.h2 * a.gomega) * sw;  // omega = ... - I
-  reinterpret_cast<double4*>(a.gS)[s] = o;
+  const double v = group_sum4_scatter(sx, sy, sj, sw, kBtLanes, lane);
+  const int qq = scatter_index(lane);
+  const double f = qq < 2 ? 1.0 : qq == 2 ? a.four_q : -a.h2 * a.gomega;  // omega = ... - I
+  a.gS[4 * s + qq] = a.wk[k] * f * v;
 }
 
 // Gradients on the reference grid from the slot gradients: the transpose of
 // the interpolation pre-pass, as a gather per cell over the slots whose
 // stencils use it (each cell written once, zero where none does).  Sixteen
 // lanes share a cell, lane q taking every 16th entry of its lists; their
-// partial sums are combined with DPP moves.
+// partial sums are combined with DPP moves.  Bound by the lists (12 B an
+// entry, four Delta and four A entries a slot) and the gathers of gV: with
+// paired angles it stops at the lower angles' entries instead of reading the
+// upper ones' zeros (208 -> 113 us on the 200 x 200 disc).
 constexpr int kItLanes = 16;
 __global__ void __launch_bounds__(256) interp_adjoint_kernel(InterpAdjArgs a) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -671,11 +435,12 @@ __global__ void __launch_bounds__(256) interp_adjoint_kernel(InterpAdjArgs a) {
   const int q = static_cast<int>(t & (kItLanes - 1));
   if (cell >= a.ncell) return;  // whole groups of sixteen leave together
   double dx[4] = {0.0, 0.0, 0.0, 0.0}, dy[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t e = a.it_dptr[cell] + q; e < a.it_dptr[cell + 1]; e += kItLanes) {
+  for (int64_t e = a.it_dptr[cell] + q; e < a.it_dend[cell]; e += kItLanes) {
     const int64_t s = a.it_ds[e];
     const double w = a.it_dw[e];
     const int k = a.slot_angle[s];
-    const double gx = a.gV[s * 3], gy = a.gV[s * 3 + 1];
+    const double* r = a.gV + s * 6;  // the parts of the two marches
+    const double gx = r[0] + r[3], gy = r[1] + r[4];
     for (int g = 0; g < a.ncomp; ++g) {
       // y = eta w x  ->  G_x += conj(eta) w G_y
       const double ex = a.eta[2 * (g * a.n_theta + k)], ey = a.eta[2 * (g * a.n_theta + k) + 1];
@@ -684,9 +449,9 @@ __global__ void __launch_bounds__(256) interp_adjoint_kernel(InterpAdjArgs a) {
     }
   }
   double ax = 0.0, ay = 0.0;
-  for (int64_t e = a.it_aptr[cell] + q; e < a.it_aptr[cell + 1]; e += kItLanes) {
+  for (int64_t e = a.it_aptr[cell] + q; e < a.it_aend[cell]; e += kItLanes) {
     const int64_t s = a.it_as[e];
-    const double wg = a.it_aw[e] * a.gV[s * 3 + 2];
+    const double wg = a.it_aw[e] * (a.gV[s * 6 + 2] + a.gV[s * 6 + 5]);
     const int k = a.slot_angle[s];
     ax += wg * a.cosk[k];
     ay += wg * a.sink[k];
@@ -782,45 +547,20 @@ __global__ void __launch_bounds__(256) curl_adjoint_kernel(const double* __restr
 static inline unsigned nb(int64_t n) { return static_cast<unsigned>((n + 255) / 256); }
 
 void launch_adjoint(int epl, const AdjArgs& a, const AdjBufs& b, hipStream_t st) {
-  const int64_t threads = a.nseg * a.G;
-  if (b.ck > 0) {
-#define QC_ADJC(E)                                                                                        \
-  hipLaunchKernelGGL(adjoint_ckpt_kernel<E>, dim3(nb(threads)), dim3(256), 0, st, a,                      \
-                     static_cast<const node4<double>*>(b.nodes), static_cast<const C*>(b.bc_g_prev),      \
-                     static_cast<const C*>(b.bc_gt_prev), static_cast<const double4*>(b.gS), b.gV, b.ck,   \
-                     b.ckbase, static_cast<C*>(b.ckg), static_cast<C*>(b.ckgt), static_cast<C*>(b.scr), b.nthr)
-    if (epl == 1)
-      QC_ADJC(1);
-    else if (epl == 2)
-      QC_ADJC(2);
-    else if (epl == 3)
-      QC_ADJC(3);
-    else if (epl == 4)
-      QC_ADJC(4);
-    else
-      QC_ADJC(8);
-#undef QC_ADJC
-    return;
+  if (a.nseg == 0) return;
+  const dim3 grid(static_cast<unsigned>((a.nseg * a.G + 63) / 64));
+  switch (epl) {
+    case 1: hipLaunchKernelGGL(adjoint_kernel<1>, grid, dim3(128), 0, st, a, b); break;
+    case 2: hipLaunchKernelGGL(adjoint_kernel<2>, grid, dim3(128), 0, st, a, b); break;
+    case 3: hipLaunchKernelGGL(adjoint_kernel<3>, grid, dim3(128), 0, st, a, b); break;
+    case 4: hipLaunchKernelGGL(adjoint_kernel<4>, grid, dim3(128), 0, st, a, b); break;
+    default: hipLaunchKernelGGL(adjoint_kernel<8>, grid, dim3(128), 0, st, a, b); break;
   }
-#define QC_ADJ(E)                                                                                        \
-  hipLaunchKernelGGL(adjoint_kernel<E>, dim3(nb(threads)), dim3(256), 0, st, a,                          \
-                     static_cast<const node4<double>*>(b.nodes), static_cast<const C*>(b.bc_g_prev),      \
-                     static_cast<const C*>(b.bc_gt_prev), static_cast<C*>(b.gbuf), static_cast<C*>(b.gtbuf), \
-                     static_cast<C*>(b.lgt), static_cast<const double4*>(b.gS), b.gV)
-  if (epl == 1)
-    QC_ADJ(1);
-  else if (epl == 2)
-    QC_ADJ(2);
-  else if (epl == 3)
-    QC_ADJ(3);
-  else if (epl == 4)
-    QC_ADJ(4);
-  else
-    QC_ADJ(8);
-#undef QC_ADJ
 }
 void launch_back_adjoint(const BackAdjArgs& a, hipStream_t st) {
-  if (a.nslot > 0) hipLaunchKernelGGL(back_adjoint_kernel, dim3(nb(a.nslot)), dim3(256), 0, st, a);
+  if (a.nslot == 0) return;
+  if (a.ncg > 0) hipLaunchKernelGGL(cell_grad_kernel, dim3(nb(a.ncg)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(back_adjoint_kernel, dim3(nb(a.nslot * kBtLanes)), dim3(256), 0, st, a);
 }
 void launch_interp_adjoint(const InterpAdjArgs& a, hipStream_t st) {
   if (a.ncell > 0) hipLaunchKernelGGL(interp_adjoint_kernel, dim3(nb(a.ncell * kItLanes)), dim3(256), 0, st, a);

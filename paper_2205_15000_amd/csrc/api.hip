@@ -315,8 +315,8 @@ struct qc_grain {
   int last_bc_valid = -1;  // store validity seen by the latest sweep (-1: no sweep yet)
   // reverse-mode buffers (allocated on first use)
   void* gtbuf = nullptr;
-  void* lgt = nullptr;
   double* gS = nullptr;
+  double* gC = nullptr;
   double* gV = nullptr;
   // checkpointed reverse mode (adj_ck > 0): offsets and buffers for that ck
   int adj_ck = 32;
@@ -375,6 +375,8 @@ struct qc_grain {
   // transposed rotate-back of the paired reverse mode: the entries of the
   // upper angles moved onto their mirror slots
   int64_t* btp_ptr = nullptr;
+  int64_t* itp_dend = nullptr;  // ends of the lower angles' entries of a cell
+  int64_t* itp_aend = nullptr;
   int32_t* btp_c = nullptr;
   double* btp_w = nullptr;
   // eigen-truncated A-solve (App. D): tolerance, kept modes, eigenvalues and
@@ -536,7 +538,7 @@ void free_grain(qc_grain* g) {
                   g->tap_s_w, g->tap_e_seg, g->tap_e_w, g->grain_cells, g->rb_idx, g->rb_w, g->rb4, g->mask,
                   g->eps, g->rpd, g->den, g->logt, g->nodes, g->cells, g->order, g->gbuf, g->node_out, g->bc[0][0],
                   g->bc[0][1], g->bc[1][0], g->bc[1][1], g->omega_cell, g->dmean, g->part, g->bbuf, g->fw,
-                  g->ghat, g->twx, g->twy, g->dnew, g->jcur, g->jold, g->anew, g->vel_d, g->vel_a, g->gtbuf, g->lgt, g->gS, g->gV,
+                  g->ghat, g->twx, g->twy, g->dnew, g->jcur, g->jold, g->anew, g->vel_d, g->vel_a, g->gtbuf, g->gS, g->gC, g->gV, g->itp_dend, g->itp_aend,
                   g->bt_ptr, g->bt_c, g->bt_w, g->it_dptr, g->it_ds, g->it_dw, g->it_aptr, g->it_as, g->it_aw,
                   g->ckbase, g->ckg, g->ckgt, g->ckscr, g->lw_acc, g->lw_dl, g->lw_save, g->order_pair, g->rb4_pair,
                   g->mirror_pairs, g->a_lam, g->a_vk, g->a_jp, g->a_y, g->btp_ptr, g->btp_c, g->btp_w};
@@ -2267,6 +2269,17 @@ void ensure_adjoint_pair_tables(qc_grain* g) {
     ww.push_back(w[o]);
   }
   const Csr c = to_csr(g->nslot, row, col, ww);
+  // first entry of a cell that belongs to an upper angle's slot
+  auto lower_ends = [&](const int64_t* dptr, const int32_t* dcol) {
+    const std::vector<int64_t> ptr = download(dptr, g->ncell + 1);
+    const std::vector<int32_t> col = download(dcol, static_cast<size_t>(ptr[g->ncell]));
+    std::vector<int64_t> end(static_cast<size_t>(g->ncell));
+    for (int64_t i = 0; i < g->ncell; ++i)
+      end[i] = std::lower_bound(col.begin() + ptr[i], col.begin() + ptr[i + 1], g->nslot_pair) - col.begin();
+    return static_cast<int64_t*>(upload(end));
+  };
+  if (!g->itp_dend) g->itp_dend = lower_ends(g->it_dptr, g->it_ds);
+  if (!g->itp_aend) g->itp_aend = lower_ends(g->it_aptr, g->it_as);
   g->btp_ptr = static_cast<int64_t*>(upload(c.ptr));
   g->btp_c = static_cast<int32_t*>(upload(c.col));
   g->btp_w = static_cast<double*>(upload(c.w));
@@ -2289,9 +2302,11 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     const size_t nb = sizeof(double) * 2 * g->nslot * g->n_poles;
     int G, epl;
     lane_shape(g->n_poles, g->epl_override, g->precision == QC_MIXED, G, epl);
+    const bool pair = g->pairing;
+    // threads of the reverse kernel: two waves per 64/G segments
+    const int64_t nthr = 2 * (((pair ? g->nseg_pair : g->nseg) * G + 63) / 64 * 64);
     if (g->adj_ck == 0) {
       if (!g->gtbuf) g->gtbuf = dalloc(nb);
-      if (!g->lgt) g->lgt = dalloc(nb);
     } else {
       const int ck = g->adj_ck;
       if (g->ck_built != ck) {
@@ -2307,7 +2322,7 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
         g->ckgt = dalloc(cbytes);
         g->ck_built = ck;
       }
-      const size_t sbytes = sizeof(double) * 2 * 2 * static_cast<size_t>(ck) * epl * g->nseg * G;
+      const size_t sbytes = sizeof(double) * 2 * static_cast<size_t>(ck) * epl * nthr;
       if (sbytes > g->ckscr_bytes) {
         if (g->ckscr) (void)hipFree(g->ckscr);
         g->ckscr = nullptr;
@@ -2316,12 +2331,12 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
         g->ckscr_bytes = sbytes;
       }
     }
+    if (!g->gC) g->gC = static_cast<double*>(dalloc(sizeof(double) * (2 * g->ncomp + 2) * std::max<int64_t>(g->ncg, 1)));
     if (!g->gS) g->gS = static_cast<double*>(dalloc(sizeof(double) * 4 * g->nslot));
-    if (!g->gV) g->gV = static_cast<double*>(dalloc(sizeof(double) * 3 * g->nslot));
+    if (!g->gV) g->gV = static_cast<double*>(dalloc(sizeof(double) * 6 * g->nslot));
     ensure_adjoint_tables(g);
     // with angle pairs the reverse mode marches the lower angles only, as
     // the forward sweep does
-    const bool pair = g->pairing;
     if (pair) ensure_adjoint_pair_tables(g);
     do_interp(g, delta, A_ind, st, pair);
     // gradients of the per-node sums
@@ -2343,6 +2358,7 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     ba.gomega = g_omega;
     ba.gdn = g_delta_new;
     ba.gj = g_j;
+    ba.gC = g->gC;
     ba.gS = g->gS;
     ba.nslot = pair ? g->nslot_pair : g->nslot;
     ba.slot_angle = g->slot_angle;
@@ -2360,23 +2376,20 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     b.nodes = g->nodes;
     b.bc_g_prev = g->bc[1 - g->bc_cur][0];
     b.bc_gt_prev = g->bc[1 - g->bc_cur][1];
-    b.gbuf = g->gbuf;
-    b.gtbuf = g->gtbuf;
-    b.lgt = g->lgt;
     b.gS = g->gS;
     b.gV = g->gV;
+    b.keep_g = g->gbuf;
+    b.keep_gt = g->gtbuf;
     if (g->adj_ck > 0) {
       b.ck = g->adj_ck;
       b.ckbase = g->ckbase;
-      b.ckg = g->ckg;
-      b.ckgt = g->ckgt;
+      b.keep_g = g->ckg;
+      b.keep_gt = g->ckgt;
       b.scr = g->ckscr;
-      b.nthr = a.nseg * G;
+      b.nthr = nthr;
     }
     qc::launch_adjoint(epl, a, b, st);
     hcheck(hipGetLastError(), "adjoint launch");
-    // the upper angles' slots take no part in the paired map
-    if (pair) qc::launch_fill(g->gV + 3 * g->nslot_pair, 3 * (g->nslot - g->nslot_pair), 0.0, st);
     // back to the reference grid (the gather writes every cell)
     qc::InterpAdjArgs ia;
     ia.nslot = g->nslot;
@@ -2394,10 +2407,14 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     ia.gV = g->gV;
     ia.gdelta = grad_delta;
     ia.gA = grad_A;
+    // (the upper angles' slots take no part in the paired map: a cell's
+    // entries are in slot order and end before them)
     ia.it_dptr = g->it_dptr;
+    ia.it_dend = pair ? g->itp_dend : g->it_dptr + 1;
     ia.it_ds = g->it_ds;
     ia.it_dw = g->it_dw;
     ia.it_aptr = g->it_aptr;
+    ia.it_aend = pair ? g->itp_aend : g->it_aptr + 1;
     ia.it_as = g->it_as;
     ia.it_aw = g->it_aw;
     qc::launch_interp_adjoint(ia, st);

@@ -165,19 +165,18 @@ struct AdjBufs {
   const void* nodes;       // node4<double>
   const void* bc_g_prev;   // boundary store read by the differentiated sweep
   const void* bc_gt_prev;
-  void* gbuf;              // gamma at nodes  [nslot][n_e]
-  void* gtbuf;             // gamma~ at nodes [nslot][n_e]
-  void* lgt;               // node-local adjoint of gamma~ [nslot][n_e]
   const void* gS;          // gradients of the per-node sums [nslot][4]
-  double* gV;              // out: gradients of the slot values [nslot][3] (Re D, Im D, a)
-  // checkpointed variant (ck > 0): gamma and gamma~ kept every ck slots, each
-  // block of ck slots recomputed into a per-thread scratch
+  double* gV;              // out: gradients of the slot values [nslot][6]: (Re D, Im D, a) through gamma, through gamma~
+  // values of the marches kept for the walk back: ck = 0 gamma / gamma~ at
+  // every node [nslot][n_e]; ck > 0 the value entering every block of ck
+  // nodes of a march [block][n_e], ckbase the first block of each segment,
+  // and a scratch [ck][EPL][nthr] into which a block is marched again
+  void* keep_g;
+  void* keep_gt;
   int ck = 0;
-  const int64_t* ckbase = nullptr;  // first checkpoint block of each segment
-  void* ckg = nullptr;              // gamma entering block k: [block][n_e]
-  void* ckgt = nullptr;             // gamma~ at the first slot of block k: [block][n_e]
-  void* scr = nullptr;              // [2][ck][EPL][nthreads] complex
-  int64_t nthr = 0;                 // nseg * G
+  const int64_t* ckbase = nullptr;
+  void* scr = nullptr;
+  int64_t nthr = 0;        // threads of the launch
 };
 
 struct BackAdjArgs {
@@ -194,6 +193,7 @@ struct BackAdjArgs {
   double four_q, h2, gomega;
   const double* gdn;  // complex gradient of Delta_new or nullptr
   const double* gj;   // gradient of j or nullptr
+  double* gC;         // work: [ncg][2 ncomp + 2]
   double* gS;         // out: [nslot][4]
   // transpose of the rotate-back table by slot: entries [bt_ptr[s], bt_ptr[s+1])
   // hold (grain-cell position, weight)
@@ -215,15 +215,17 @@ struct InterpAdjArgs {
   const double* eta;
   const double* cosk;
   const double* sink;
-  const double* gV;
+  const double* gV;  // [nslot][6]
   double* gdelta;  // out: complex [ncomp][ny][nx]
   double* gA;      // out: [2][ny][nx]
   // transposes of the slot stencils by cell: Delta entries [it_dptr[c],
-  // it_dptr[c+1]) and A_ind entries [it_aptr[c], it_aptr[c+1]) hold (slot, weight)
+  // it_dend[c]) and A_ind entries [it_aptr[c], it_aend[c]) hold (slot, weight)
   const int64_t* it_dptr;
+  const int64_t* it_dend;
   const int32_t* it_ds;
   const double* it_dw;
   const int64_t* it_aptr;
+  const int64_t* it_aend;
   const int32_t* it_as;
   const double* it_aw;
 };
