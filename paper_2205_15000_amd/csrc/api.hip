@@ -337,7 +337,6 @@ struct qc_grain {
   int32_t* it_as = nullptr;
   double* it_aw = nullptr;
   double* omega_cell = nullptr;
-  double* dmean = nullptr;
   double* part = nullptr;
   double* part_host = nullptr;
   double* bbuf = nullptr;
@@ -537,7 +536,7 @@ void free_grain(qc_grain* g) {
                   g->sink, g->wk, g->seg_slot0, g->seg_n, g->seg_hfirst, g->seg_hlast, g->tap_s_seg,
                   g->tap_s_w, g->tap_e_seg, g->tap_e_w, g->grain_cells, g->rb_idx, g->rb_w, g->rb4, g->mask,
                   g->eps, g->rpd, g->den, g->logt, g->nodes, g->cells, g->order, g->gbuf, g->node_out, g->bc[0][0],
-                  g->bc[0][1], g->bc[1][0], g->bc[1][1], g->omega_cell, g->dmean, g->part, g->bbuf, g->fw,
+                  g->bc[0][1], g->bc[1][0], g->bc[1][1], g->omega_cell, g->part, g->bbuf, g->fw,
                   g->ghat, g->twx, g->twy, g->dnew, g->jcur, g->jold, g->anew, g->vel_d, g->vel_a, g->gtbuf, g->gS, g->gC, g->gV, g->itp_dend, g->itp_aend,
                   g->bt_ptr, g->bt_c, g->bt_w, g->it_dptr, g->it_ds, g->it_dw, g->it_aptr, g->it_as, g->it_aw,
                   g->ckbase, g->ckg, g->ckgt, g->ckscr, g->lw_acc, g->lw_dl, g->lw_save, g->order_pair, g->rb4_pair,
@@ -1156,7 +1155,6 @@ qc_status qc_grain_create(int device, const qc_grain_desc* desc, qc_grain** out)
     // gbuf, node_out and the boundary store are allocated by the first sweep
     g->omega_cell = static_cast<double*>(dalloc(sizeof(double) * g->ncg));
     g->part = static_cast<double*>(dalloc(sizeof(double) * kRegions * kParts));
-    g->dmean = static_cast<double*>(dalloc(sizeof(double) * 2));
     hcheck(hipHostMalloc(reinterpret_cast<void**>(&g->part_host), sizeof(double) * kRegions * kParts),
            "hipHostMalloc");
     g->bbuf = static_cast<double*>(dalloc(sizeof(double) * g->ncell));
@@ -1354,9 +1352,8 @@ void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipS
                         {j + g->ncell, g->grain_cells, g->ncg, 0, region(g, kRJy)}, kParts, st);
   const double inv_n = 1.0 / static_cast<double>(g->ncg);
   if (g->a_nmodes > 0) {
-    qc::launch_means(region(g, kRJx), kParts, inv_n, g->dmean, st);
     // the separable kernel kept to its largest modes: two MFMA contractions
-    qc::launch_masked_current(j, g->mask, g->ncell, g->dmean, g->a_jp, st);
+    qc::launch_masked_current(j, g->mask, g->ncell, region(g, kRJx), kParts, inv_n, g->a_jp, st);
     qc::launch_eig_vecpot(g->nx, g->a_nmodes, g->a_jp, g->a_vk, g->a_lam, g->a_y, A_out,
                           -1.0 / (g->kappa * g->kappa), st);
     if (B_out) qc::launch_curl(A_out, B_out, g->nx, g->ny, g->h, st);

@@ -1191,31 +1191,6 @@ __global__ void __launch_bounds__(256) congacc_update_kernel(double* __restrict_
   }
 }
 
-// grain means of the two current components from block partials (fixed
-// summation order, the same as a host-side sum of the partials)
-__global__ void __launch_bounds__(256) means_kernel(const double* __restrict__ part, int nparts, double inv_n,
-                                                    double* __restrict__ mean) {
-  // one block; fixed-order tree over the partials: deterministic
-  __shared__ double sh[2][256];
-  for (int c = 0; c < 2; ++c) {
-    double v = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x) v += part[c * nparts + i];
-    sh[c][threadIdx.x] = v;
-  }
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) {
-      sh[0][threadIdx.x] += sh[0][threadIdx.x + st];
-      sh[1][threadIdx.x] += sh[1][threadIdx.x + st];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    mean[0] = sh[0][0] * inv_n;
-    mean[1] = sh[1][0] * inv_n;
-  }
-}
-
 // --------------------------------------------------------------------------
 // issue-rate probe: eight independent chains of one FP32 operation per lane
 // (op 0 fma, 1 rsq, 2 sqrt, 3 rcp), for the roofline of the sweep kernels
@@ -1459,8 +1434,5 @@ void launch_lw_finish(const double* delta, const int32_t* grain_cells, int64_t n
 }
 void launch_scale(const double* x, double s, int64_t n, double* y, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(scale_kernel, dim3(nblk(n)), dim3(256), 0, st, x, s, n, y);
-}
-void launch_means(const double* part, int nparts, double inv_n, double* mean, hipStream_t st) {
-  hipLaunchKernelGGL(means_kernel, dim3(1), dim3(256), 0, st, part, nparts, inv_n, mean);
 }
 }  // namespace qc

@@ -314,7 +314,6 @@ void launch_bb_dots(const double* xnew, const double* xold, const int32_t* idx, 
                     hipStream_t st);
 void launch_picard(double* x, const double* gx, const int32_t* idx, int64_t n, int nrep, int64_t field_stride,
                    int stride, double alpha, hipStream_t st);
-void launch_means(const double* part, int nparts, double inv_n, double* mean, hipStream_t st);
 // Luttinger-Ward free energy: per grain cell c, acc[c] (+)= w * 2 sum_G
 // den_G Re(conj(delta_G) delta_new_G) (first: = instead of +=)
 void launch_lw_accumulate(const double* delta, const double* delta_new, const int32_t* grain_cells, int64_t ncg,
@@ -331,8 +330,8 @@ void launch_scale(const double* x, double s, int64_t n, double* y, hipStream_t s
 // aout [2][n][n] = alpha sum_k lam_k T_k jp T_k
 void launch_eig_vecpot(int n, int nmodes, const double* jp, const double* vk, const double* lam, double* y,
                        double* aout, double alpha, hipStream_t st);
-void launch_masked_current(const double* j, const uint8_t* mask, int64_t ncell, const double* mean, double* jp,
-                           hipStream_t st);
+void launch_masked_current(const double* j, const uint8_t* mask, int64_t ncell, const double* part, int nparts,
+                           double inv_n, double* jp, hipStream_t st);
 // per grain cell (x - cx) j_y - (y - cy) j_x, grain-cell order
 void launch_torque(const double* j, const int32_t* grain_cells, int64_t ncg, int64_t ncell, int nx, double x0,
                    double y0, double h, double cx, double cy, double* out, hipStream_t st);

@@ -9,7 +9,7 @@
 //   A   = s sum_k lambda_k T_k Y_k   (one N x (N* N) x N product; lambda_k T_k
 //                        generated from V_k, Y stacked mode by mode).
 // The Toeplitz operands are formed from the N-vector of each mode as they
-// are staged into LDS, so no N x N x N* table is stored.
+// are loaded, so no N x N x N* table is stored.
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -19,100 +19,143 @@ namespace qc {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// One wave per 32 x 32 output tile (2 x 2 MFMA 16x16x4 tiles), K staged
-// through LDS in chunks of 16.  MFMA f64 16x16x4 operands: lane l holds
-// A[l % 16][l / 16] and B[l / 16][l % 16]; the result D[l / 16 + 4 v][l % 16]
-// in element v of its four accumulators (checked on the device).
+// MFMA f64 16x16x4 operands: lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16]; the result D[l / 16 + 4 v][l % 16] in element v of its
+// four accumulators (checked on the device).  The contraction index runs in
+// chunks of 16: step s of a chunk takes its indices 4 (l / 16) + s.
 //   MODE 1: C = Y[c][k] (N x N), A = J'[c] (row-major), B[a][b] = V[k][|a - b|];
-//           blockIdx.z = c * nmodes + k.
+//           a wave per 16 x 32 tile, blockIdx.z = c * nmodes + k.
 //   MODE 2: C = A_out[c], A[r][(k, a)] = lambda_k V[k][|r - a|],
-//           B = Y[c] as an (N* N) x N row-major matrix; blockIdx.z = c.
+//           B = Y[c] as an (N* N) x N row-major matrix; a block per 32 x 16
+//           tile, its waves share the contraction, blockIdx.z = c.
+// The Toeplitz operand of the tile's second half is that of its first half one
+// chunk before, so a chunk costs four loads of it and four of the dense
+// operand for eight MFMAs (512 cycles): both go to registers, one chunk
+// ahead, with no LDS and no barrier.  Bound by the matrix cores' FP64 rate and
+// the shortage of tiles.  A wave per 32 x 32 tile with the whole contraction
+// and staging through LDS took 49 + 242 us on 200 x 200 with 5 modes (98 waves
+// on 1024 SIMDs in the second product); 15 + 11 us now (5 us at the rate a
+// large FP64 product reaches).
+constexpr int kEigWaves1 = 4, kEigWaves2 = 8;
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 template <int MODE>
-__global__ void __launch_bounds__(64) eig_gemm_kernel(int n, int nmodes, const double* __restrict__ jp,
-                                                      const double* __restrict__ vk,
-                                                      const double* __restrict__ lam, double* __restrict__ y,
-                                                      double* __restrict__ aout, double alpha) {
-  __shared__ double As[16][33];  // [k][row]
-  __shared__ double Bs[16][33];  // [k][col]
-  const int l = threadIdx.x;
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+__global__ void __launch_bounds__(64 * (MODE == 1 ? kEigWaves1 : kEigWaves2))
+    eig_gemm_kernel(int n, int nmodes, const double* __restrict__ jp, const double* __restrict__ vk,
+                    const double* __restrict__ lam, double* __restrict__ y, double* __restrict__ aout, double alpha) {
+  const int l = threadIdx.x & 63, m = l & 15, g = l >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int z = blockIdx.z;
   const int64_t nn = static_cast<int64_t>(n) * n;
-  const int K = MODE == 1 ? n : nmodes * n;
-  const double* aptr = nullptr;
-  const double* bptr = nullptr;
-  const double* vrow = nullptr;
-  double* cptr = nullptr;
+  const int r0 = MODE == 1 ? (static_cast<int>(blockIdx.y) * kEigWaves1 + wv) * 16 : static_cast<int>(blockIdx.y) * 32;
+  const int c0 = static_cast<int>(blockIdx.x) * (MODE == 1 ? 32 : 16);
+  if (MODE == 1 && r0 >= n) return;  // (no barrier in this product)
+  // Toeplitz tile origin and the dense operand's fixed index (clamped: what
+  // lies outside is not stored)
+  const int t0 = (MODE == 1 ? c0 : r0) + m;
+  const int fixed = min(MODE == 1 ? r0 + m : c0 + m, n - 1);
+  // the wave's chunks [q0, q1) of the contraction
+  const int per = (n + 15) / 16;
+  const int64_t total = MODE == 1 ? per : static_cast<int64_t>(per) * nmodes;
+  const int64_t q0 = MODE == 1 ? 0 : total * wv / kEigWaves2, q1 = MODE == 1 ? total : total * (wv + 1) / kEigWaves2;
+  v4d acc[2] = {v4d{0.0, 0.0, 0.0, 0.0}, v4d{0.0, 0.0, 0.0, 0.0}};
+  for (int64_t q = q0; q < q1;) {
+    const int k = MODE == 1 ? z % nmodes : static_cast<int>(q / per);
+    const int b0 = MODE == 1 ? 0 : static_cast<int>(q - static_cast<int64_t>(k) * per);
+    const int b1 = static_cast<int>(min(static_cast<int64_t>(per), b0 + (q1 - q)));
+    q += b1 - b0;
+    const double* const v = vk + static_cast<int64_t>(k) * n;
+    const double scale = MODE == 1 ? 1.0 : lam[k];
+    const double* const dense = MODE == 1 ? jp + (z / nmodes) * nn + static_cast<int64_t>(fixed) * n
+                                          : y + (static_cast<int64_t>(z) * nmodes + k) * nn + fixed;
+    auto toeplitz = [&](int b, double* t) {
+      for (int s = 0; s < 4; ++s) t[s] = scale * v[min(abs(16 * b + 4 * g + s - t0), n - 1)];
+    };
+    auto load = [&](int b, double* d) {
+      const int a = 16 * b + 4 * g;
+      if (16 * b + 16 <= n) {
+        if (MODE == 1) {
+          const d2u lo = *reinterpret_cast<const d2u*>(dense + a), hi = *reinterpret_cast<const d2u*>(dense + a + 2);
+          d[0] = lo.x;
+          d[1] = lo.y;
+          d[2] = hi.x;
+          d[3] = hi.y;
+        } else {
+          for (int s = 0; s < 4; ++s) d[s] = dense[static_cast<int64_t>(a + s) * n];
+        }
+      } else {  // the last chunk: zero beyond n
+        for (int s = 0; s < 4; ++s) {
+          const int e = min(a + s, n - 1);
+          const double x = dense[MODE == 1 ? e : static_cast<int64_t>(e) * n];
+          d[s] = a + s < n ? x : 0.0;
+        }
+      }
+    };
+    double tp[4], tc[4], d[4];
+    toeplitz(b0 - 1, tp);
+    toeplitz(b0, tc);
+    load(b0, d);
+    for (int b = b0; b < b1; ++b) {
+      double tn[4], dn[4];
+      const int nb = min(b + 1, b1 - 1);
+      toeplitz(nb, tn);
+      load(nb, dn);
+      for (int s = 0; s < 4; ++s) {
+        if (MODE == 1) {
+          acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[s], tc[s], acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[s], tp[s], acc[1], 0, 0, 0);
+        } else {
+          acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(tc[s], d[s], acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[s], d[s], acc[1], 0, 0, 0);
+        }
+      }
+      for (int s = 0; s < 4; ++s) {
+        tp[s] = tc[s];
+        tc[s] = tn[s];
+        d[s] = dn[s];
+      }
+    }
+  }
   if (MODE == 1) {
-    const int c = z / nmodes, k = z - (z / nmodes) * nmodes;
-    aptr = jp + c * nn;
-    vrow = vk + static_cast<int64_t>(k) * n;
-    cptr = y + static_cast<int64_t>(z) * nn;
-  } else {
-    bptr = y + static_cast<int64_t>(z) * nmodes * nn;
-    cptr = aout + static_cast<int64_t>(z) * nn;
-  }
-  v4d acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-  for (int kb = 0; kb < K; kb += 16) {
-    // stage A (32 rows x 16 k) and B (16 k x 32 cols): 8 elements per lane each
-    for (int e = 0; e < 8; ++e) {
-      const int idx = e * 64 + l;
-      {  // A: row ar, k ak (k fastest across lanes)
-        const int ar = idx >> 4, ak = idx & 15;
-        const int r = r0 + ar, q = kb + ak;
-        double v = 0.0;
-        if (r < n && q < K) {
-          if (MODE == 1) {
-            v = aptr[static_cast<int64_t>(r) * n + q];
-          } else {
-            const int k = q / n, a = q - k * n;
-            const int d = r > a ? r - a : a - r;
-            v = lam[k] * vk[static_cast<int64_t>(k) * n + d];
-          }
-        }
-        As[ak][ar] = v;
-      }
-      {  // B: k bk, column bc (columns fastest across lanes)
-        const int bk = idx >> 5, bc = idx & 31;
-        const int q = kb + bk, cc = c0 + bc;
-        double v = 0.0;
-        if (q < K && cc < n) {
-          if (MODE == 1) {
-            const int d = q > cc ? q - cc : cc - q;
-            v = vrow[d];
-          } else {
-            v = bptr[static_cast<int64_t>(q) * n + cc];
-          }
-        }
-        Bs[bk][bc] = v;
-      }
-    }
-    __syncthreads();
-    for (int s = 0; s < 4; ++s) {
-      const int kk = s * 4 + (l >> 4);
-      double av[2], bv[2];
-      for (int i = 0; i < 2; ++i) av[i] = As[kk][i * 16 + (l & 15)];
-      for (int j = 0; j < 2; ++j) bv[j] = Bs[kk][j * 16 + (l & 15)];
-      for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 2; ++i)
+    double* const out = y + static_cast<int64_t>(z) * nn;
     for (int j = 0; j < 2; ++j)
-      for (int v = 0; v < 4; ++v) {
-        const int r = r0 + i * 16 + (l >> 4) + 4 * v, cc = c0 + j * 16 + (l & 15);
-        if (r < n && cc < n) cptr[static_cast<int64_t>(r) * n + cc] = alpha * acc[i][j][v];
+      for (int e = 0; e < 4; ++e) {
+        const int r = r0 + g + 4 * e, c = c0 + 16 * j + m;
+        if (r < n && c < n) out[static_cast<int64_t>(r) * n + c] = acc[j][e];
       }
+  } else {
+    __shared__ double part[kEigWaves2][8][64];
+    for (int e = 0; e < 8; ++e) part[wv][e][l] = acc[e >> 2][e & 3];
+    __syncthreads();
+    // thread (wv, l) sums element wv of lane l over the waves
+    double sum = 0.0;
+    for (int w = 0; w < kEigWaves2; ++w) sum += part[w][wv][l];
+    const int r = r0 + 16 * (wv >> 2) + g + 4 * (wv & 3), c = c0 + m;
+    if (r < n && c < n) aout[z * nn + static_cast<int64_t>(r) * n + c] = alpha * sum;
+  }
+}
+static_assert(kEigWaves2 == 8, "a thread of the second product sums one of a lane's eight elements");
+
+// sum of component c's partials over a wave, in an order of its own
+__device__ __forceinline__ double sum_parts(const double* part, int nparts, int c, int l) {
+  double v = 0.0;
+  for (int i = l; i < nparts; i += 64) v += part[c * nparts + i];
+  return group_sum(v, 64);
 }
 
-// j' = (j - grain mean) on grain cells, zero elsewhere, both components
+// j' = (j - grain mean) on grain cells, zero elsewhere, both components; the
+// means from the block partials of the two sums (each block forms them: a
+// launch less)
 __global__ void __launch_bounds__(256) masked_current_kernel(const double* __restrict__ j,
                                                              const uint8_t* __restrict__ mask, int64_t ncell,
-                                                             const double* __restrict__ mean,
-                                                             double* __restrict__ jp) {
+                                                             const double* __restrict__ part, int nparts,
+                                                             double inv_n, double* __restrict__ jp) {
+  __shared__ double mean[2];
+  if (threadIdx.x < 128) {
+    const int c = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const double v = sum_parts(part, nparts, c, l);
+    if (l == 0) mean[c] = v * inv_n;
+  }
+  __syncthreads();
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= ncell) return;
   const bool in = mask[i] != 0;
@@ -136,14 +179,17 @@ static inline unsigned nb256(int64_t n) { return static_cast<unsigned>((n + 255)
 
 void launch_eig_vecpot(int n, int nmodes, const double* jp, const double* vk, const double* lam, double* y,
                        double* aout, double alpha, hipStream_t st) {
-  const unsigned t = static_cast<unsigned>((n + 31) / 32);
-  hipLaunchKernelGGL(eig_gemm_kernel<1>, dim3(t, t, 2 * nmodes), dim3(64), 0, st, n, nmodes, jp, vk, lam, y, aout,
-                     1.0);
-  hipLaunchKernelGGL(eig_gemm_kernel<2>, dim3(t, t, 2), dim3(64), 0, st, n, nmodes, jp, vk, lam, y, aout, alpha);
+  const unsigned t16 = static_cast<unsigned>((n + 15) / 16), t32 = static_cast<unsigned>((n + 31) / 32);
+  hipLaunchKernelGGL(eig_gemm_kernel<1>, dim3(t32, (t16 + kEigWaves1 - 1) / kEigWaves1, 2 * nmodes),
+                     dim3(64 * kEigWaves1), 0, st, n, nmodes, jp, vk, lam, y, aout, 1.0);
+  hipLaunchKernelGGL(eig_gemm_kernel<2>, dim3(t16, t32, 2), dim3(64 * kEigWaves2), 0, st, n, nmodes, jp, vk, lam, y,
+                     aout, alpha);
 }
-void launch_masked_current(const double* j, const uint8_t* mask, int64_t ncell, const double* mean, double* jp,
-                           hipStream_t st) {
-  if (ncell > 0) hipLaunchKernelGGL(masked_current_kernel, dim3(nb256(ncell)), dim3(256), 0, st, j, mask, ncell, mean, jp);
+void launch_masked_current(const double* j, const uint8_t* mask, int64_t ncell, const double* part, int nparts,
+                           double inv_n, double* jp, hipStream_t st) {
+  if (ncell > 0)
+    hipLaunchKernelGGL(masked_current_kernel, dim3(nb256(ncell)), dim3(256), 0, st, j, mask, ncell, part, nparts, inv_n,
+                       jp);
 }
 void launch_torque(const double* j, const int32_t* grain_cells, int64_t ncg, int64_t ncell, int nx, double x0,
                    double y0, double h, double cx, double cy, double* out, hipStream_t st) {
@@ -371,11 +417,9 @@ __global__ void __launch_bounds__(256) vecpot_rows_kernel(const double* __restri
   // the masked current first, its mean off it afterwards: the loads of both
   // overlap
   for (int t = threadIdx.x; t < rpb * px; t += blockDim.x) buf[t] = make_double2(0.0, 0.0);
-  if (threadIdx.x < 128) {  // wave c sums the partials of component c, in an order of its own
+  if (threadIdx.x < 128) {
     const int c = threadIdx.x >> 6, l = threadIdx.x & 63;
-    double v = 0.0;
-    for (int i = l; i < nparts; i += 64) v += part[c * nparts + i];
-    v = group_sum(v, 64);
+    const double v = sum_parts(part, nparts, c, l);
     if (l == 0) mean[c] = v * inv_n;
   }
   // (up to kHold elements per thread held over the barrier; the rest after it)
