@@ -371,6 +371,7 @@ struct qc_grain {
   int32_t* order_pair = nullptr;
   int4* rb4_pair = nullptr;
   int2* mirror_pairs = nullptr;
+  int32_t* seg_upper = nullptr;  // upper segment of each lower one
   // transposed rotate-back of the paired reverse mode: the entries of the
   // upper angles moved onto their mirror slots
   int64_t* btp_ptr = nullptr;
@@ -540,7 +541,7 @@ void free_grain(qc_grain* g) {
                   g->ghat, g->twx, g->twy, g->dnew, g->jcur, g->jold, g->anew, g->vel_d, g->vel_a, g->gtbuf, g->gS, g->gC, g->gV, g->itp_dend, g->itp_aend,
                   g->bt_ptr, g->bt_c, g->bt_w, g->it_dptr, g->it_ds, g->it_dw, g->it_aptr, g->it_as, g->it_aw,
                   g->ckbase, g->ckg, g->ckgt, g->ckscr, g->lw_acc, g->lw_dl, g->lw_save, g->order_pair, g->rb4_pair,
-                  g->mirror_pairs, g->a_lam, g->a_vk, g->a_jp, g->a_y, g->btp_ptr, g->btp_c, g->btp_w};
+                  g->mirror_pairs, g->seg_upper, g->a_lam, g->a_vk, g->a_jp, g->a_y, g->btp_ptr, g->btp_c, g->btp_w};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (g->part_host) (void)hipHostFree(g->part_host);
@@ -620,6 +621,7 @@ qc::BackArgs back_args(qc_grain* g, const double* delta, double* dnew, double* j
   r.j = j;
   r.omega = omega;
   r.omega_cell = g->omega_cell;
+  r.zero_mask = nullptr;
   return r;
 }
 
@@ -738,6 +740,7 @@ qc::SweepArgs sweep_args(qc_grain* g, int n_e, int n_e_tot, int e_off, const dou
   a.node_out = g->node_out;
   a.maxn = g->maxn;
   a.nlong = 0;
+  a.mirror = pair ? g->seg_upper : nullptr;
   return a;
 }
 
@@ -790,16 +793,6 @@ void launch_sweep_timed(qc_grain* g, int mode, const qc::SweepArgs& a, const qc:
   }
 }
 
-// the end values of the upper angles of the pairs, from their mirrors, so
-// that the boundary store is complete for every reader
-void mirror_fill(qc_grain* g, void* bc_g, void* bc_gt, hipStream_t st) {
-  if (!g->pairing) return;
-  if (g->precision == QC_MIXED)
-    qc::launch_mirror_fill<float>(g->mirror_pairs, g->npairs, g->n_poles, nullptr, bc_g, bc_gt, st);
-  else
-    qc::launch_mirror_fill<double>(g->mirror_pairs, g->npairs, g->n_poles, nullptr, bc_g, bc_gt, st);
-}
-
 double omega_from_parts(const qc_grain* g) {
   double tot = g->h * g->h * region_sum(g, kROmega);
   if (g->kappa > 0.0) tot += g->h * g->h * 0.5 * g->kappa * g->kappa * region_sum(g, kRB2);
@@ -822,9 +815,8 @@ void ensure_sweep_buffers(qc_grain* g, bool spill = true) {
 }
 
 // steps 3-8 of one iteration; omega_total (host) optional (synchronises)
-// zero_out: clear delta_new, j (and omega) first; the rotate-back writes
-// grain cells only, so a caller that keeps the off-grain cells at zero itself
-// may skip it
+// zero_out: also write zeros to delta_new, j (and omega) off the grain; a
+// caller that keeps those cells at zero itself may skip it
 void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_new, double* j, double* omega,
               double* omega_total, hipStream_t st, bool zero_out = true) {
   ensure_sweep_buffers(g);
@@ -847,17 +839,13 @@ void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_n
   b.gbuf = g->gbuf;
   b.ebuf = nullptr;
   launch_sweep_timed(g, 0, a, b, st);
-  mirror_fill(g, b.bc_g_next, b.bc_gt_next, st);
   g->last_bc_valid = g->bc_valid;
   g->bc_cur = 1 - g->bc_cur;
   g->bc_valid = 1;
 
-  if (zero_out) {
-    qc::launch_fill(delta_new, 2 * g->ncomp * g->ncell, 0.0, st);
-    qc::launch_fill(j, 2 * g->ncell, 0.0, st);
-    if (omega) qc::launch_fill(omega, g->ncell, 0.0, st);
-  }
-  qc::launch_rotate_back(back_args(g, delta, delta_new, j, omega), st);
+  qc::BackArgs r = back_args(g, delta, delta_new, j, omega);
+  r.zero_mask = zero_out ? g->mask : nullptr;
+  qc::launch_rotate_back(r, st);
   hcheck(hipGetLastError(), "rotate-back launch");
   // block partials of the free energy (condensation and magnetic parts)
   if (g->kappa > 0.0) {
@@ -1145,6 +1133,11 @@ qc_status qc_grain_create(int device, const qc_grain_desc* desc, qc_grain** out)
       std::vector<int2> mp;
       for (int64_t sg = p.nseg_pair; sg < p.nseg; ++sg) mp.push_back(make_int2(static_cast<int>(sg), p.seg_mirror[sg]));
       g->mirror_pairs = static_cast<int2*>(upload(mp));
+      std::vector<int32_t> upper(static_cast<size_t>(p.nseg_pair), -1);
+      for (const int2& m : mp) upper[m.y] = m.x;
+      for (int32_t u : upper)
+        if (u < 0) throw std::logic_error("angle pairs: a lower segment without its upper one");
+      g->seg_upper = static_cast<int32_t*>(upload(upper));
       g->npairs = static_cast<int64_t>(mp.size());
       g->nseg_pair = p.nseg_pair;
       g->nslot_pair = p.nslot_pair;
@@ -2698,7 +2691,6 @@ void batch_iteration(qc_batch* b, hipStream_t st, bool upload) {
   }
   for (size_t gi = 0; gi < b->grains.size(); ++gi) {
     qc_grain* g = b->grains[gi];
-    mirror_fill(g, g->bc[1 - g->bc_cur][0], g->bc[1 - g->bc_cur][1], st);
     rotate_back_grain(g, b->delta[gi], g->dnew, g->jcur, st);
     // A from the current (zero for an infinite penetration depth), as in the
     // single-grain Picard loop

@@ -233,7 +233,7 @@ __device__ __forceinline__ void vmem_order() { __builtin_amdgcn_sched_barrier(0x
 template <typename T, int EPL, int MODE, int DIR>
 __device__ __forceinline__ void sweep_march(const SweepArgs& a, bool live, int64_t wseg, int lane, int G, int lg,
                                             const node4<T>* __restrict__ nodes, const cpx<T>* __restrict__ bc_prev,
-                                            cpx<T>* __restrict__ bc_next, cpx<T>* gbase, int64_t gmul,
+                                            cpx<T>* __restrict__ bc_next, cpx<T>* __restrict__ bc_mirror, cpx<T>* gbase, int64_t gmul,
                                             T* __restrict__ ebuf, double* __restrict__ lsum) {
   constexpr T sd = T(DIR);  // D -> -D* for gamma~
   if (!live) wseg = 0;
@@ -572,6 +572,13 @@ __device__ __forceinline__ void sweep_march(const SweepArgs& a, bool live, int64
     cpx<T>* dst = bc_next + seg * a.n_e_tot + a.e_off + es;
     for (int i = 0; i < EPL; ++i)
       if (own[i]) dst[i] = g[i];
+    // gamma~ along a line is the conjugate of gamma along the reversed line
+    // (even order parameter): the end values of the upper angle of a pair
+    if (MODE == 0 && a.mirror) {
+      cpx<T>* mdst = bc_mirror + static_cast<int64_t>(a.mirror[seg]) * a.n_e_tot + a.e_off + es;
+      for (int i = 0; i < EPL; ++i)
+        if (own[i]) mdst[i] = mk(g[i].x, -g[i].y);
+    }
   }
 }
 
@@ -589,10 +596,12 @@ __device__ __forceinline__ void sweep_bundle(const SweepArgs& a, int64_t wseg0, 
   // (the branch is uniform over each wave, and each wave meets the one barrier once)
   if (dir == 0)
     sweep_march<T, EPL, MODE, 1>(a, live, wseg, lane, G, lg, nodes, static_cast<const cpx<T>*>(b.bc_g_prev),
-                                 static_cast<cpx<T>*>(b.bc_g_next), gbase, gmul, ebuf, lsum);
+                                 static_cast<cpx<T>*>(b.bc_g_next), static_cast<cpx<T>*>(b.bc_gt_next), gbase, gmul,
+                                 ebuf, lsum);
   else
     sweep_march<T, EPL, MODE, -1>(a, live, wseg, lane, G, lg, nodes, static_cast<const cpx<T>*>(b.bc_gt_prev),
-                                  static_cast<cpx<T>*>(b.bc_gt_next), gbase, gmul, ebuf, lsum);
+                                  static_cast<cpx<T>*>(b.bc_gt_next), static_cast<cpx<T>*>(b.bc_g_next), gbase, gmul,
+                                  ebuf, lsum);
 }
 
 template <typename T, int EPL, int MODE>
@@ -662,11 +671,10 @@ __global__ void reset_counter_kernel(int* counter) {
 // --------------------------------------------------------------------------
 // rotate back + angle sums + gap / current / free energy
 // --------------------------------------------------------------------------
-// A block of kBackWaves waves shares 64 grain cells: wave w takes the angles
-// k = w, w + kBackWaves, ... for all of them, so each load of a wave gathers
+// A block of W waves shares 64 grain cells: wave w takes the angles
+// k = w, w + W, ... for all of them, so each load of a wave gathers
 // the lattice corners of 64 neighbouring cells at one angle; the waves'
 // partial angle sums meet in LDS.
-constexpr int kBackWaves = 4;
 constexpr int kBackFields = 12;  // 2 x (up to 4 components) + jx, jy, I, <|Delta|^2>
 
 // Bilinear weights and slots of a cell's corner record ix on one angle's
@@ -703,13 +711,24 @@ __device__ __forceinline__ double back_weights(int4 ix, double epx, double epy, 
 
 // NC = 1: one order-parameter component (its arrays in fixed registers);
 // NC = 4: a.ncomp <= 4 components
-template <int NC>
-__global__ void __launch_bounds__(64 * kBackWaves) rotate_back_kernel(BackArgs a) {
-  __shared__ double part[kBackWaves - 1][kBackFields][64];
+template <int NC, int W>
+__global__ void __launch_bounds__(64 * W) rotate_back_kernel(BackArgs a) {
+  __shared__ double part[W - 1][kBackFields][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int nblk = static_cast<int>((a.ncg + 63) / 64);
+  if (static_cast<int>(blockIdx.x) >= nblk) {  // zeros off the grain
+    const int64_t cell = static_cast<int64_t>(blockIdx.x - nblk) * (64 * W) + threadIdx.x;
+    if (cell >= a.ncell || a.zero_mask[cell]) return;
+    for (int g = 0; g < a.ncomp; ++g)
+      reinterpret_cast<double2*>(a.delta_new)[g * a.ncell + cell] = make_double2(0.0, 0.0);
+    a.j[cell] = 0.0;
+    a.j[a.ncell + cell] = 0.0;
+    if (a.omega) a.omega[cell] = 0.0;
+    return;
+  }
   // each XCD takes a contiguous band of grain cells: neighbouring cells share
   // lattice corners, which then meet in the same L2
-  const int64_t c = xcd_block(blockIdx.x, gridDim.x) * 64 + lane;
+  const int64_t c = xcd_block(blockIdx.x, nblk) * 64 + lane;
   const bool live = c < a.ncg;
   const int cell = live ? a.grain_cells[c] : 0;
   constexpr int MAXC = NC;
@@ -751,9 +770,9 @@ __global__ void __launch_bounds__(64 * kBackWaves) rotate_back_kernel(BackArgs a
   int k = live ? wv : kend;
   int4 ixn = make_int4(0, 0, 0, 0);
   if (k < kend) ixn = a.rb4[static_cast<int64_t>(k) * a.ncg + c];
-  for (; k < kend; k += kBackWaves) {
+  for (; k < kend; k += W) {
     const int4 ix = ixn;
-    if (k + kBackWaves < kend) ixn = a.rb4[static_cast<int64_t>(k + kBackWaves) * a.ncg + c];
+    if (k + W < kend) ixn = a.rb4[static_cast<int64_t>(k + W) * a.ncg + c];
     double w[4];
     int sl[4];
     const double rt = back_weights(ix, a.cosk[k], a.sink[k], rx, ry, a.h, a.half, w, sl);
@@ -783,7 +802,7 @@ __global__ void __launch_bounds__(64 * kBackWaves) rotate_back_kernel(BackArgs a
   }
   __syncthreads();
   if (wv > 0 || !live) return;
-  for (int w = 0; w < kBackWaves - 1; ++w) {
+  for (int w = 0; w < W - 1; ++w) {
     const double* p = &part[w][0][lane];
     for (int g = 0; g < ncomp; ++g) {
       nx_[g] += p[64 * (2 * g)];
@@ -807,9 +826,9 @@ __global__ void __launch_bounds__(64 * kBackWaves) rotate_back_kernel(BackArgs a
   a.omega_cell[c] = om;
 }
 
-// gamma~ along a line is the conjugate of gamma along the reversed line
-// (even order parameter): the end values of the upper angle of a pair follow
-// from its mirror segment's
+// End values of the upper angles of pairs at real energies, from their mirror
+// segments' values at the partner energies (see sweep_march for the relation;
+// a Matsubara sweep writes them itself)
 template <typename T>
 __global__ void __launch_bounds__(256) mirror_fill_kernel(const int2* __restrict__ pairs, int64_t npairs, int n_e,
                                                           const int32_t* __restrict__ partner,
@@ -819,8 +838,8 @@ __global__ void __launch_bounds__(256) mirror_fill_kernel(const int2* __restrict
   const int64_t q = t / n_e;
   const int e = static_cast<int>(t - q * n_e);
   const int2 pr = pairs[q];
-  // real energies: the reversed direction at e mirrors energy -e (partner)
-  const int es = partner ? partner[e] : e;
+  // the reversed direction at e mirrors energy -e (partner)
+  const int es = partner[e];
   const int64_t dst = static_cast<int64_t>(pr.x) * n_e + e, src = static_cast<int64_t>(pr.y) * n_e + es;
   const cpx<T> g = bc_g[src], gt = bc_gt[src];
   bc_g[dst] = mk(gt.x, -gt.y);
@@ -1331,12 +1350,34 @@ void launch_mirror_fill(const int2* pairs, int64_t npairs, int n_e, const int32_
 template void launch_mirror_fill<float>(const int2*, int64_t, int, const int32_t*, void*, void*, hipStream_t);
 template void launch_mirror_fill<double>(const int2*, int64_t, int, const int32_t*, void*, void*, hipStream_t);
 
-void launch_rotate_back(const BackArgs& a, hipStream_t st) {
-  if (a.ncg == 0) return;
+template <int W>
+static void launch_back_w(const BackArgs& a, hipStream_t st) {
+  int64_t nb = (a.ncg + 63) / 64;
+  if (a.zero_mask) nb += (a.ncell + 64 * W - 1) / (64 * W);
+  const dim3 grid(static_cast<unsigned>(nb));
   if (a.ncomp == 1)
-    hipLaunchKernelGGL(rotate_back_kernel<1>, dim3((a.ncg + 63) / 64), dim3(64 * kBackWaves), 0, st, a);
+    hipLaunchKernelGGL((rotate_back_kernel<1, W>), grid, dim3(64 * W), 0, st, a);
+  else if constexpr (W <= 8)
+    hipLaunchKernelGGL((rotate_back_kernel<4, W>), grid, dim3(64 * W), 0, st, a);
+}
+// Waves a block by the number of blocks of 64 cells.  A launch is bound by the
+// gathers while its blocks fill the wave slots (1024 blocks of four waves, at
+// four waves a SIMD): more waves a block then only add partial sums (400 x 400:
+// 84, 90 and 105 us with 4, 8 and 16).  With fewer blocks it is the chain of a
+// wave's angles, which more waves shorten: 24 and 22 us with 4 and 8 on the
+// 200 x 200 disc (491 blocks), 16 and 13 us at 249 blocks, and down to a block
+// a compute unit 16 waves beat 8 or equal them (12.2 -> 10.3 us at 89 blocks, 6.3 -> 5.6 us
+// at 13).  Several components leave no registers for 16 (24 and 18 us with 4
+// and 8 at 100 blocks).
+void launch_rotate_back(const BackArgs& a, hipStream_t st) {
+  if (a.ncg == 0 && !a.zero_mask) return;
+  const int64_t blocks = (a.ncg + 63) / 64;
+  if (blocks >= 1024)
+    launch_back_w<4>(a, st);
+  else if (blocks > 256 || a.ncomp > 1)
+    launch_back_w<8>(a, st);
   else
-    hipLaunchKernelGGL(rotate_back_kernel<4>, dim3((a.ncg + 63) / 64), dim3(64 * kBackWaves), 0, st, a);
+    launch_back_w<16>(a, st);
 }
 
 template <typename T, int V, bool CPLX>

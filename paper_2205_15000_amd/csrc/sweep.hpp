@@ -68,6 +68,9 @@ struct SweepArgs {
   // segments of the launch order take 2G lanes and EPL/2 energies per lane,
   // the rest G lanes and EPL; nlong * 2G is a multiple of 64 (0: one shape)
   int64_t nlong;
+  // Matsubara sweeps over the lower angles of pairs: the upper angle's segment
+  // on the same line, by segment (nullptr: no pairs)
+  const int32_t* mirror;
 };
 
 struct SweepBufs {
@@ -117,6 +120,7 @@ struct BackArgs {
   // pair_fold: angle k + pair_k0 has the corners of angle k (the same
   // lattice points), so each gather of a lower angle serves both
   int pair_fold;
+  const uint8_t* zero_mask;  // grain mask when the off-grain cells are to be zeroed, or nullptr
 };
 
 struct LdosBackArgs {
