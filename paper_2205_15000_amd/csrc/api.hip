@@ -650,9 +650,9 @@ qc::LdosBackArgs ldos_back_args(const qc_grain* g, int ne, int e_off, double* ou
   return la;
 }
 
-// node values of every slot, or (pair) of the slots of the lower angles of
-// the angle pairs only
-void do_interp(qc_grain* g, const double* delta, const double* A, hipStream_t st, bool pair = false) {
+// arguments of the node values of every slot, or (pair) of the slots of the
+// lower angles of the angle pairs only
+qc::InterpArgs interp_args(const qc_grain* g, const double* delta, const double* A, bool pair) {
   qc::InterpArgs a;
   pair = pair && g->pairing;
   a.nslot = pair ? g->nslot_pair : g->nslot;
@@ -678,6 +678,11 @@ void do_interp(qc_grain* g, const double* delta, const double* A, hipStream_t st
   a.gauge = g->gauge;
   a.flux = g->flux;
   a.bfield = g->bfield;
+  return a;
+}
+
+void do_interp(qc_grain* g, const double* delta, const double* A, hipStream_t st, bool pair = false) {
+  const qc::InterpArgs a = interp_args(g, delta, A, pair);
   if (g->ncomp == 1 && !g->cells) g->cells = dalloc(4 * g->real_bytes() * g->ncell);
   void* cells = g->ncomp == 1 ? g->cells : nullptr;
   if (g->precision == QC_MIXED)
@@ -2571,6 +2576,10 @@ struct qc_batch {
   int ntiles = 0;
   // tiles grouped by the grains' lane shapes: one persistent launch per group
   std::vector<int> grp_epl, grp_off, grp_n;
+  // blocks of the passes around the sweep (in d_tiles, after the sweep's):
+  // packing, interpolation, rotate-back of one and of several components
+  int pass_off[4] = {0, 0, 0, 0}, pass_n[4] = {0, 0, 0, 0};
+  std::vector<char> paired;  // the grains' pairing that the tiles were built for
   int* d_counter = nullptr;  // one tile counter per group
   hipStream_t own = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -2622,9 +2631,26 @@ void build_tiles(qc_batch* b) {
     b->grp_n.push_back(static_cast<int>(all.size()));
     for (const T3& x : all) t.push_back(make_int2(x.g, x.w0));
   }
-  if (b->d_tiles) (void)hipFree(b->d_tiles);
-  b->d_tiles = static_cast<int2*>(upload(t));
   b->ntiles = static_cast<int>(t.size());
+  b->paired.clear();
+  for (qc_grain* g : b->grains) b->paired.push_back(g->pairing);
+  for (int pass = 0; pass < 4; ++pass) {
+    b->pass_off[pass] = static_cast<int>(t.size());
+    for (size_t gi = 0; gi < b->grains.size(); ++gi) {
+      const qc_grain* g = b->grains[gi];
+      const int64_t nseg = g->pairing ? g->nseg_pair : g->nseg, nslot = g->pairing ? g->nslot_pair : g->nslot;
+      const bool one = g->ncomp == 1;
+      const int64_t blocks = pass == 0   ? (one ? (g->ncell + 255) / 256 : 0)
+                             : pass == 1 ? (one ? (nseg + 3) / 4 : (nslot + 255) / 256)
+                             : one == (pass == 2) ? (g->ncg + 63) / 64
+                                                  : 0;
+      for (int64_t k = 0; k < blocks; ++k) t.push_back(make_int2(static_cast<int>(gi), static_cast<int>(k)));
+    }
+    b->pass_n[pass] = static_cast<int>(t.size()) - b->pass_off[pass];
+  }
+  if (b->d_tiles) (void)hipFree(b->d_tiles);
+  b->d_tiles = nullptr;
+  b->d_tiles = static_cast<int2*>(upload(t));
   // per-block spill: 64/G segments of up to maxn nodes and n_e poles each
   int64_t we = 1;
   for (qc_grain* g : b->grains) {
@@ -2665,38 +2691,41 @@ void upload_args(qc_batch* b, hipStream_t st) {
     v[gi].b.bc_gt_next = g->bc[1 - g->bc_cur][1];
     v[gi].b.gbuf = g->gbuf;
     v[gi].b.ebuf = nullptr;
+    v[gi].ia = interp_args(g, b->delta[gi], b->A[gi], true);
+    v[gi].cells = g->ncomp == 1 ? g->cells : nullptr;
+    v[gi].ra = back_args(g, b->delta[gi], b->delta[gi], g->jcur, nullptr);
   }
   hcheck(hipMemcpyAsync(b->d_args, v.data(), sizeof(qc::BatchGrainDev) * v.size(), hipMemcpyHostToDevice, st),
          "H2D");
   hcheck(hipStreamSynchronize(st), "sync");  // the host block is reused by the next upload
 }
 
-void rotate_back_grain(qc_grain* g, const double* delta, double* dnew, double* j, hipStream_t st) {
-  qc::launch_rotate_back(back_args(g, delta, dnew, j, nullptr), st);
-}
-
-// one Picard iteration (alpha = 1) of every grain: per-grain interpolation,
-// one persistent sweep over all grains, per-grain rotate-back, A-solve and
-// update.  Only kernel launches: it can be captured into a graph.
+// one Picard iteration (alpha = 1) of every grain: interpolation, one
+// persistent sweep over all grains, rotate-back with the step of Delta, and
+// per grain with screening the A-solve and the step of A (without, A is zero
+// and stays zero).  Only kernel launches: it can be captured into a graph.
 void batch_iteration(qc_batch* b, hipStream_t st, bool upload) {
-  for (size_t gi = 0; gi < b->grains.size(); ++gi) do_interp(b->grains[gi], b->delta[gi], b->A[gi], st, true);
   if (upload) upload_args(b, st);
+  const bool mixed = b->precision == QC_MIXED;
+  const auto pass = [&](int k) { return b->d_tiles + b->pass_off[k]; };
+  (mixed ? qc::launch_batch_interp<float> : qc::launch_batch_interp<double>)(b->d_args, pass(0), b->pass_n[0], pass(1),
+                                                                             b->pass_n[1], st);
   for (size_t k = 0; k < b->grp_epl.size(); ++k) {
-    if (b->precision == QC_MIXED)
+    if (mixed)
       qc::launch_batch_sweep<float>(b->grp_epl[k], b->d_args, b->d_tiles + b->grp_off[k], b->grp_n[k],
                                     b->d_counter + k, b->nblocks, b->spill, b->wave_elems, st);
     else
       qc::launch_batch_sweep<double>(b->grp_epl[k], b->d_args, b->d_tiles + b->grp_off[k], b->grp_n[k],
                                      b->d_counter + k, b->nblocks, b->spill, b->wave_elems, st);
   }
+  qc::launch_batch_back(false, b->d_args, pass(2), b->pass_n[2], st);
+  qc::launch_batch_back(true, b->d_args, pass(3), b->pass_n[3], st);
   for (size_t gi = 0; gi < b->grains.size(); ++gi) {
     qc_grain* g = b->grains[gi];
-    rotate_back_grain(g, b->delta[gi], g->dnew, g->jcur, st);
-    // A from the current (zero for an infinite penetration depth), as in the
-    // single-grain Picard loop
-    do_solve_A(g, g->jcur, g->anew, nullptr, st);
-    qc::launch_picard(b->A[gi], g->anew, nullptr, 2 * g->ncell, 1, 0, 1, 1.0, st);
-    qc::launch_picard(b->delta[gi], g->dnew, g->grain_cells, g->ncg, g->ncomp, g->ncell, 2, 1.0, st);
+    if (g->kappa > 0.0) {
+      do_solve_A(g, g->jcur, g->anew, nullptr, st);
+      qc::launch_picard(b->A[gi], g->anew, nullptr, 2 * g->ncell, 1, 0, 1, 1.0, st);
+    }
     g->bc_cur = 1 - g->bc_cur;
     g->bc_valid = 1;
     g->last_bc_valid = -1;  // batched sweeps are not differentiated
@@ -2759,8 +2788,6 @@ qc_status qc_batch_create(qc_grain* const* grains, int n, qc_batch** out) {
       b->A.push_back(a);
       qc::launch_fill(d, 2 * g->ncomp * g->ncell, 0.0, nullptr);
       qc::launch_fill(a, 2 * g->ncell, 0.0, nullptr);
-      // off-grain cells of delta_new stay zero: rotate-back writes grain cells only
-      qc::launch_fill(g->dnew, 2 * g->ncomp * g->ncell, 0.0, nullptr);
     }
     b->d_args = static_cast<qc::BatchGrainDev*>(dalloc(sizeof(qc::BatchGrainDev) * n));
     b->d_counter = static_cast<int*>(dalloc(8 * sizeof(int)));
@@ -2798,17 +2825,10 @@ qc_status qc_batch_set_fields(qc_batch* b, int i, const double* delta, const dou
   return guarded([&]() -> qc_status {
     qc_grain* g = b->grains[i];
     hcheck(hipSetDevice(b->device), "hipSetDevice");
-    hcheck(hipMemcpyAsync(g->dnew, delta, sizeof(double) * 2 * g->ncomp * g->ncell, hipMemcpyDeviceToDevice, S(stream)),
-           "copy");
-    qc::launch_fill(b->delta[i], 2 * g->ncomp * g->ncell, 0.0, S(stream));
-    qc::launch_picard(b->delta[i], g->dnew, g->grain_cells, g->ncg, g->ncomp, g->ncell, 2, 1.0, S(stream));
-    qc::launch_fill(g->dnew, 2 * g->ncomp * g->ncell, 0.0, S(stream));
     // no screening (kappa <= 0): no induced vector potential, A stays zero
-    if (g->kappa <= 0.0)
-      qc::launch_fill(b->A[i], 2 * g->ncell, 0.0, S(stream));
-    else
-      hcheck(hipMemcpyAsync(b->A[i], A_ind, sizeof(double) * 2 * g->ncell, hipMemcpyDeviceToDevice, S(stream)),
-             "copy");
+    qc::launch_batch_set(delta, g->kappa > 0.0 ? A_ind : nullptr, g->mask, g->ncell, g->ncomp, b->delta[i], b->A[i],
+                         S(stream));
+    hcheck(hipGetLastError(), "set fields launch");
     return QC_OK;
   });
 }
@@ -2838,6 +2858,13 @@ qc_status qc_batch_iterate(qc_batch* b, int n_iter, int use_graph, void* stream)
     hcheck(hipEventCreate(&e1), "event");
     hcheck(hipEventRecord(e0, st), "event");
     int left = n_iter;
+    // (a grain's pairing may have been switched since the tiles were built)
+    for (size_t gi = 0; gi < b->grains.size(); ++gi)
+      if (b->grains[gi]->pairing != static_cast<bool>(b->paired[gi])) {
+        drop_graph(b);
+        build_tiles(b);
+        break;
+      }
     // the first sweep of a fresh grain starts from bulk roots: run it eagerly
     bool fresh = false;
     for (qc_grain* g : b->grains) fresh = fresh || !g->bc_valid;

@@ -23,8 +23,7 @@ namespace qc {
 // interpolation pre-pass
 // --------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(256) interp_kernel(InterpArgs a, node4<T>* __restrict__ nodes) {
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void interp_slot(const InterpArgs& a, int64_t s, node4<T>* __restrict__ nodes) {
   if (s >= a.nslot) return;
   const int k = a.slot_angle[s];
   const double px = a.px[s], py = a.py[s];
@@ -60,24 +59,29 @@ __global__ void __launch_bounds__(256) interp_kernel(InterpArgs a, node4<T>* __r
   nodes[s] = v;
 }
 
+template <typename T>
+__global__ void __launch_bounds__(256) interp_kernel(InterpArgs a, node4<T>* __restrict__ nodes) {
+  interp_slot<T>(a, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, nodes);
+}
+
 // Single order-parameter component: Delta and A_ind packed per cell in the
 // sweep precision, so the gathers of a slot touch one 16 B (FP32) or 32 B
 // (FP64) record per corner and the FP32 grid stays resident in L2.  Cells
 // outside the grain carry a NaN in Re Delta: the masked interpolation reads
 // the mask from the same record instead of a separate dependent load.
 template <typename T>
-__global__ void __launch_bounds__(256) pack_cells_kernel(const double* __restrict__ delta,
-                                                         const double* __restrict__ A,
-                                                         const uint8_t* __restrict__ mask, int64_t ncell,
-                                                         cell4<T>* __restrict__ cells) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= ncell) return;
+__device__ __forceinline__ void pack_cell(const InterpArgs& a, int64_t i, cell4<T>* __restrict__ cells) {
+  if (i >= a.ncell) return;
   cell4<T> c;
-  c.dx = mask[i] ? static_cast<T>(delta[2 * i]) : __builtin_nan("");
-  c.dy = static_cast<T>(delta[2 * i + 1]);
-  c.ax = static_cast<T>(A[i]);
-  c.ay = static_cast<T>(A[ncell + i]);
+  c.dx = a.geom.mask[i] ? static_cast<T>(a.delta[2 * i]) : __builtin_nan("");
+  c.dy = static_cast<T>(a.delta[2 * i + 1]);
+  c.ax = static_cast<T>(a.A[i]);
+  c.ay = static_cast<T>(a.A[a.ncell + i]);
   cells[i] = c;
+}
+template <typename T>
+__global__ void __launch_bounds__(256) pack_cells_kernel(InterpArgs a, cell4<T>* __restrict__ cells) {
+  pack_cell<T>(a, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, cells);
 }
 
 // Same stencils as interp_kernel (identical floating-point operations for the
@@ -85,11 +89,11 @@ __global__ void __launch_bounds__(256) pack_cells_kernel(const double* __restric
 // clamped bilinear for A_ind.  Away from the array edge the two stencils
 // share their corners, and the four records serve both.
 template <typename T>
-__global__ void __launch_bounds__(256) interp1_kernel(InterpArgs a, const cell4<T>* __restrict__ cells,
-                                                      node4<T>* __restrict__ nodes) {
+__device__ __forceinline__ void interp1_block(const InterpArgs& a, int block, const cell4<T>* __restrict__ cells,
+                                              node4<T>* __restrict__ nodes) {
   // one wave per segment: its record is read once (scalar loads), and each
   // lane takes every 64th slot of the segment
-  const int64_t seg = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x >> 6));
+  const int64_t seg = __builtin_amdgcn_readfirstlane(block * 4 + static_cast<int>(threadIdx.x >> 6));
   if (seg >= a.nseg) return;
   const SegGeo sgeo = a.seg_geo[seg];
   const int nsl = sgeo.n > 0 ? sgeo.n : 1;
@@ -187,6 +191,11 @@ __global__ void __launch_bounds__(256) interp1_kernel(InterpArgs a, const cell4<
     o.pad = T(0);
     nodes[s] = o;
   }
+}
+template <typename T>
+__global__ void __launch_bounds__(256) interp1_kernel(InterpArgs a, const cell4<T>* __restrict__ cells,
+                                                      node4<T>* __restrict__ nodes) {
+  interp1_block<T>(a, static_cast<int>(blockIdx.x), cells, nodes);
 }
 
 // --------------------------------------------------------------------------
@@ -711,24 +720,13 @@ __device__ __forceinline__ double back_weights(int4 ix, double epx, double epy, 
 
 // NC = 1: one order-parameter component (its arrays in fixed registers);
 // NC = 4: a.ncomp <= 4 components
-template <int NC, int W>
-__global__ void __launch_bounds__(64 * W) rotate_back_kernel(BackArgs a) {
-  __shared__ double part[W - 1][kBackFields][64];
+// UPDATE: the Picard step of size one in place (Delta += Delta_new - Delta)
+// instead of Delta_new: a cell's Delta is read by the cell's own thread only
+template <int NC, int W, bool UPDATE>
+__device__ __forceinline__ void rotate_back_block(const BackArgs& a, int64_t block,
+                                                  double (*__restrict__ part)[kBackFields][64]) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int nblk = static_cast<int>((a.ncg + 63) / 64);
-  if (static_cast<int>(blockIdx.x) >= nblk) {  // zeros off the grain
-    const int64_t cell = static_cast<int64_t>(blockIdx.x - nblk) * (64 * W) + threadIdx.x;
-    if (cell >= a.ncell || a.zero_mask[cell]) return;
-    for (int g = 0; g < a.ncomp; ++g)
-      reinterpret_cast<double2*>(a.delta_new)[g * a.ncell + cell] = make_double2(0.0, 0.0);
-    a.j[cell] = 0.0;
-    a.j[a.ncell + cell] = 0.0;
-    if (a.omega) a.omega[cell] = 0.0;
-    return;
-  }
-  // each XCD takes a contiguous band of grain cells: neighbouring cells share
-  // lattice corners, which then meet in the same L2
-  const int64_t c = xcd_block(blockIdx.x, nblk) * 64 + lane;
+  const int64_t c = block * 64 + lane;
   const bool live = c < a.ncg;
   const int cell = live ? a.grain_cells[c] : 0;
   constexpr int MAXC = NC;
@@ -815,8 +813,10 @@ __global__ void __launch_bounds__(64 * W) rotate_back_kernel(BackArgs a) {
   }
   double om = 0.0;
   for (int g = 0; g < ncomp; ++g) {
-    a.delta_new[2 * (static_cast<int64_t>(g) * a.ncell + cell)] = nx_[g] / a.den[g];
-    a.delta_new[2 * (static_cast<int64_t>(g) * a.ncell + cell) + 1] = ny_[g] / a.den[g];
+    const double vx = nx_[g] / a.den[g], vy = ny_[g] / a.den[g];
+    double* const o = a.delta_new + 2 * (static_cast<int64_t>(g) * a.ncell + cell);
+    o[0] = UPDATE ? dx_[g] + (vx - dx_[g]) : vx;
+    o[1] = UPDATE ? dy_[g] + (vy - dy_[g]) : vy;
     om += (dx_[g] * dx_[g] + dy_[g] * dy_[g]) * a.logt[g];
   }
   om += a.twopi_rz * d2avg - icell;
@@ -824,6 +824,72 @@ __global__ void __launch_bounds__(64 * W) rotate_back_kernel(BackArgs a) {
   a.j[a.ncell + cell] = jy;
   if (a.omega) a.omega[cell] = om;
   a.omega_cell[c] = om;
+}
+
+template <int NC, int W>
+__global__ void __launch_bounds__(64 * W) rotate_back_kernel(BackArgs a) {
+  __shared__ double part[W - 1][kBackFields][64];
+  const int nblk = static_cast<int>((a.ncg + 63) / 64);
+  if (static_cast<int>(blockIdx.x) >= nblk) {  // zeros off the grain
+    const int64_t cell = static_cast<int64_t>(blockIdx.x - nblk) * (64 * W) + threadIdx.x;
+    if (cell >= a.ncell || a.zero_mask[cell]) return;
+    for (int g = 0; g < a.ncomp; ++g)
+      reinterpret_cast<double2*>(a.delta_new)[g * a.ncell + cell] = make_double2(0.0, 0.0);
+    a.j[cell] = 0.0;
+    a.j[a.ncell + cell] = 0.0;
+    if (a.omega) a.omega[cell] = 0.0;
+    return;
+  }
+  // each XCD takes a contiguous band of grain cells: neighbouring cells share
+  // lattice corners, which then meet in the same L2
+  rotate_back_block<NC, W, false>(a, xcd_block(blockIdx.x, nblk), part);
+}
+
+// Batched grains: the passes around the sweep, every grain's blocks in one
+// launch (tiles: the grain and the block of the grain).  A launch per grain
+// left most of the device idle and cost its latency each time: eight grains
+// of 64 x 64 to 176 x 176 took 45 launches and 290 us an iteration beside
+// the sweeps, 66 us now.
+template <typename T>
+__global__ void __launch_bounds__(256) batch_pack_kernel(const BatchGrainDev* __restrict__ grains,
+                                                         const int2* __restrict__ tiles) {
+  const int2 t = tiles[blockIdx.x];
+  const BatchGrainDev& gd = grains[__builtin_amdgcn_readfirstlane(t.x)];
+  pack_cell<T>(gd.ia, static_cast<int64_t>(t.y) * 256 + threadIdx.x, static_cast<cell4<T>*>(gd.cells));
+}
+// (one or several components: without or with the packed cells)
+template <typename T>
+__global__ void __launch_bounds__(256) batch_interp_kernel(const BatchGrainDev* __restrict__ grains,
+                                                           const int2* __restrict__ tiles) {
+  const int2 t = tiles[blockIdx.x];
+  const BatchGrainDev& gd = grains[__builtin_amdgcn_readfirstlane(t.x)];
+  node4<T>* nodes = static_cast<node4<T>*>(const_cast<void*>(gd.b.nodes));
+  if (gd.cells)
+    interp1_block<T>(gd.ia, __builtin_amdgcn_readfirstlane(t.y), static_cast<const cell4<T>*>(gd.cells), nodes);
+  else
+    interp_slot<T>(gd.ia, static_cast<int64_t>(t.y) * 256 + threadIdx.x, nodes);
+}
+template <int NC, int W>
+__global__ void __launch_bounds__(64 * W) batch_back_kernel(const BatchGrainDev* __restrict__ grains,
+                                                            const int2* __restrict__ tiles) {
+  __shared__ double part[W - 1][kBackFields][64];
+  const int2 t = tiles[xcd_block(blockIdx.x, gridDim.x)];
+  const BatchGrainDev& gd = grains[__builtin_amdgcn_readfirstlane(t.x)];
+  rotate_back_block<NC, W, true>(gd.ra, __builtin_amdgcn_readfirstlane(t.y), part);
+}
+
+// Fields of a batched grain: Delta on the grain and zero off it, A as given
+// or (no screening) zero
+__global__ void __launch_bounds__(256) batch_set_kernel(const double2* __restrict__ delta,
+                                                        const double* __restrict__ A,
+                                                        const uint8_t* __restrict__ mask, int64_t ncell, int ncomp,
+                                                        double2* __restrict__ delta_out, double* __restrict__ A_out) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= ncell) return;
+  for (int g = 0; g < ncomp; ++g)
+    delta_out[g * ncell + i] = mask[i] ? delta[g * ncell + i] : make_double2(0.0, 0.0);
+  A_out[i] = A ? A[i] : 0.0;
+  A_out[ncell + i] = A ? A[ncell + i] : 0.0;
 }
 
 // End values of the upper angles of pairs at real energies, from their mirror
@@ -1241,8 +1307,8 @@ template <typename T>
 void launch_interp(const InterpArgs& a, void* cells, void* nodes, hipStream_t st) {
   if (a.nslot == 0) return;
   if (cells && a.ncomp == 1) {
-    hipLaunchKernelGGL(pack_cells_kernel<T>, dim3(nblk(a.ncell)), dim3(256), 0, st, a.delta, a.A, a.geom.mask,
-                       a.ncell, static_cast<cell4<T>*>(cells));
+    hipLaunchKernelGGL(pack_cells_kernel<T>, dim3(nblk(a.ncell)), dim3(256), 0, st, a,
+                       static_cast<cell4<T>*>(cells));
     hipLaunchKernelGGL(interp1_kernel<T>, dim3(static_cast<unsigned>((a.nseg + 3) / 4)), dim3(256), 0, st, a,
                        static_cast<const cell4<T>*>(cells), static_cast<node4<T>*>(nodes));
   } else {
@@ -1369,15 +1435,45 @@ static void launch_back_w(const BackArgs& a, hipStream_t st) {
 // a compute unit 16 waves beat 8 or equal them (12.2 -> 10.3 us at 89 blocks, 6.3 -> 5.6 us
 // at 13).  Several components leave no registers for 16 (24 and 18 us with 4
 // and 8 at 100 blocks).
+static int back_waves(int64_t blocks, int ncomp) { return blocks >= 1024 ? 4 : blocks > 256 || ncomp > 1 ? 8 : 16; }
 void launch_rotate_back(const BackArgs& a, hipStream_t st) {
   if (a.ncg == 0 && !a.zero_mask) return;
-  const int64_t blocks = (a.ncg + 63) / 64;
-  if (blocks >= 1024)
-    launch_back_w<4>(a, st);
-  else if (blocks > 256 || a.ncomp > 1)
-    launch_back_w<8>(a, st);
-  else
-    launch_back_w<16>(a, st);
+  switch (back_waves((a.ncg + 63) / 64, a.ncomp)) {
+    case 4: launch_back_w<4>(a, st); break;
+    case 8: launch_back_w<8>(a, st); break;
+    default: launch_back_w<16>(a, st); break;
+  }
+}
+template <typename T>
+void launch_batch_interp(const BatchGrainDev* grains, const int2* pack, int npack, const int2* interp, int ninterp,
+                         hipStream_t st) {
+  if (npack > 0) hipLaunchKernelGGL(batch_pack_kernel<T>, dim3(npack), dim3(256), 0, st, grains, pack);
+  if (ninterp > 0) hipLaunchKernelGGL(batch_interp_kernel<T>, dim3(ninterp), dim3(256), 0, st, grains, interp);
+}
+template void launch_batch_interp<float>(const BatchGrainDev*, const int2*, int, const int2*, int, hipStream_t);
+template void launch_batch_interp<double>(const BatchGrainDev*, const int2*, int, const int2*, int, hipStream_t);
+void launch_batch_back(bool several, const BatchGrainDev* grains, const int2* tiles, int n, hipStream_t st) {
+  if (n == 0) return;
+  const int w = back_waves(n, several ? 2 : 1);
+  const dim3 grid(n), block(64 * w);
+  if (several) {
+    if (w == 4)
+      hipLaunchKernelGGL((batch_back_kernel<4, 4>), grid, block, 0, st, grains, tiles);
+    else
+      hipLaunchKernelGGL((batch_back_kernel<4, 8>), grid, block, 0, st, grains, tiles);
+  } else if (w == 4) {
+    hipLaunchKernelGGL((batch_back_kernel<1, 4>), grid, block, 0, st, grains, tiles);
+  } else if (w == 8) {
+    hipLaunchKernelGGL((batch_back_kernel<1, 8>), grid, block, 0, st, grains, tiles);
+  } else {
+    hipLaunchKernelGGL((batch_back_kernel<1, 16>), grid, block, 0, st, grains, tiles);
+  }
+}
+void launch_batch_set(const double* delta, const double* A, const uint8_t* mask, int64_t ncell, int ncomp,
+                      double* delta_out, double* A_out, hipStream_t st) {
+  if (ncell > 0)
+    hipLaunchKernelGGL(batch_set_kernel, dim3(nblk(ncell)), dim3(256), 0, st, reinterpret_cast<const double2*>(delta),
+                       A, mask, ncell, ncomp, reinterpret_cast<double2*>(delta_out), A_out);
 }
 
 template <typename T, int V, bool CPLX>

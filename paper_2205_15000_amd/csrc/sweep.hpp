@@ -83,12 +83,6 @@ struct SweepBufs {
   void* ebuf;
 };
 
-// one grain of a batched sweep: its arguments and buffers
-struct BatchGrainDev {
-  SweepArgs a;
-  SweepBufs b;
-};
-
 struct BackArgs {
   int64_t ncg;     // grain cells
   int64_t ncell;   // nx * ny
@@ -121,6 +115,15 @@ struct BackArgs {
   // lattice points), so each gather of a lower angle serves both
   int pair_fold;
   const uint8_t* zero_mask;  // grain mask when the off-grain cells are to be zeroed, or nullptr
+};
+
+// one grain of a batch: the arguments and buffers of its passes
+struct BatchGrainDev {
+  SweepArgs a;
+  SweepBufs b;
+  InterpArgs ia;
+  void* cells;  // packed cells (one component) or nullptr
+  BackArgs ra;  // delta_new: the field itself, updated in place
 };
 
 struct LdosBackArgs {
@@ -262,6 +265,13 @@ void launch_sweep(int mode, int epl, const SweepArgs& a, const SweepBufs& b, hip
 template <typename T>
 int64_t sweep_wave_slots(int epl);
 void launch_rotate_back(const BackArgs& a, hipStream_t st);
+// batched grains; the tiles are (grain, block of the grain)
+template <typename T>
+void launch_batch_interp(const BatchGrainDev* grains, const int2* pack, int npack, const int2* interp, int ninterp,
+                         hipStream_t st);
+void launch_batch_back(bool several, const BatchGrainDev* grains, const int2* tiles, int n, hipStream_t st);
+void launch_batch_set(const double* delta, const double* A, const uint8_t* mask, int64_t ncell, int ncomp,
+                      double* delta_out, double* A_out, hipStream_t st);
 // End values of the upper angle of each pair from its mirror segment:
 // gamma_end(s') = conj(gamma~_end(s)), gamma~_end(s') = conj(gamma_end(s))
 // for each (s', s) in pairs, n_e energies per segment (T = float or double)
