@@ -703,15 +703,23 @@ int64_t wave_slots(const qc_grain* g, int epl) {
 int64_t sweep_waves(int64_t nseg, int G) { return 2 * ((nseg * G + 63) / 64); }
 
 // Lane shape of a sweep over nseg segments of a grain: lane_shape's, except
-// that a launch whose waves would leave wave slots empty at four energies per
-// lane takes two (its time is then the chain of steps of one wave, which
-// grows with the energies per lane: 32 x 32 disc, FP64, 17, 21 and 30 us for
-// 1, 2 and 4 per lane)
+// that a launch whose waves would leave wave slots empty at three or four
+// energies per lane takes two: its time is then the chain of steps of one
+// wave, which grows with the energies per lane (32 x 32 disc, FP64: 17, 21 and
+// 30 us for 1, 2 and 4 per lane; 101 x 97 with a hole, 12 poles, FP64: 65 and
+// 48 us for 3 and 2 or 1).  From three, which often wastes no lanes where two
+// do, only while those fill one round (FP64) or a third more (mixed): a whole
+// sweep of a square took, for 3 and 2 per lane,
+//   FP64: 186 and 169 us (0.74 rounds at 2), 246 and 259 (1.04), 378 and 421 (1.5),
+//   mixed: 135 and 120 us (0.56), 302 and 281 (1.1), 407 and 388 (1.3), 414 and 407 (1.5).
 void grain_shape(const qc_grain* g, int n_e, int64_t nseg, int& G, int& epl) {
-  lane_shape(n_e, g->epl_override, g->precision == QC_MIXED, G, epl);
-  if (epl == 4 && epl != g->epl_override && lanes_for(n_e, 2) <= 64 && sweep_waves(nseg, G) < wave_slots(g, epl)) {
+  const bool mixed = g->precision == QC_MIXED;
+  lane_shape(n_e, g->epl_override, mixed, G, epl);
+  const int G2 = lanes_for(n_e, 2);
+  if ((epl == 4 || epl == 3) && epl != g->epl_override && G2 <= 64 && sweep_waves(nseg, G) < wave_slots(g, epl) &&
+      (epl == 4 || 3 * sweep_waves(nseg, G2) <= (mixed ? 4 : 3) * wave_slots(g, 2))) {
     epl = 2;
-    G = lanes_for(n_e, 2);
+    G = G2;
   }
 }
 
@@ -2579,6 +2587,7 @@ struct qc_batch {
   // blocks of the passes around the sweep (in d_tiles, after the sweep's):
   // packing, interpolation, rotate-back of one and of several components
   int pass_off[4] = {0, 0, 0, 0}, pass_n[4] = {0, 0, 0, 0};
+  int shape = 0;             // energies per lane of the tiles (0: each grain's own)
   std::vector<char> paired;  // the grains' pairing that the tiles were built for
   int* d_counter = nullptr;  // one tile counter per group
   hipStream_t own = nullptr;
@@ -2600,7 +2609,41 @@ namespace {
 // the tiles are sorted by their longest segment, longest first.
 void drop_graph(qc_batch* b);
 
+// lane shape of a grain: the common energies per lane, or its own choice (0,
+// or where its poles do not allow the common number)
+void batch_shape(const qc_batch* b, const qc_grain* g, int& G, int& epl) {
+  lane_shape(g->n_poles, b->shape, g->precision == QC_MIXED, G, epl);
+}
+
+// Energies per lane of a batch that leaves the choice to the library.  Grains
+// of different own shapes are launches of different kernels, one after the
+// other, each with its own tail; one common shape is one launch.  One per lane
+// while that fits one round of the wave slots, two up to two rounds; then four
+// (mixed) or two (FP64), the best common shape, up to ten rounds, where the
+// tails weigh less than what each grain's own shape saves.  An iteration of n
+// grains (s to t cells a side) with own shapes and with the common one:
+//   mixed: 2 (64-96) 132 and 106 us, 8 (64-176) 398 and 246, 12 (100-176) 548
+//   and 405, 24 (64-176) 728 and 663, 32 (100-200, 12 rounds) 1859 with own;
+//   FP64: 126 and 121, 469 and 344, 665 and 612, 1105 and 1061, 3082 with own.
+int auto_batch_epl(const qc_batch* b) {
+  const bool mixed = b->precision == QC_MIXED;
+  auto rounds = [&](int e) {
+    int64_t waves = 0;
+    for (const qc_grain* g : b->grains) {
+      int G, epl;
+      lane_shape(g->n_poles, e, mixed, G, epl);
+      waves += sweep_waves(g->pairing ? g->nseg_pair : g->nseg, G);
+    }
+    return static_cast<double>(waves) / std::max<int64_t>(wave_slots(b->grains[0], e), 1);
+  };
+  if (rounds(1) <= 1.0) return 1;
+  if (rounds(2) <= 2.0) return 2;
+  const int common = mixed ? 4 : 2;
+  return rounds(common) <= 10.0 ? common : 0;
+}
+
 void build_tiles(qc_batch* b) {
+  b->shape = b->epl != 0 ? b->epl : auto_batch_epl(b);
   struct T3 {
     int g, w0, cost;
   };
@@ -2608,7 +2651,7 @@ void build_tiles(qc_batch* b) {
   for (size_t gi = 0; gi < b->grains.size(); ++gi) {
     qc_grain* g = b->grains[gi];
     int G, epl;
-    lane_shape(g->n_poles, b->epl, g->precision == QC_MIXED, G, epl);
+    batch_shape(b, g, G, epl);
     const int64_t nsw = g->pairing ? g->nseg_pair : g->nseg;
     std::vector<int32_t> ord(nsw), n(g->nseg);
     hcheck(hipMemcpy(ord.data(), g->pairing ? g->order_pair : g->order, sizeof(int32_t) * nsw, hipMemcpyDeviceToHost),
@@ -2655,7 +2698,7 @@ void build_tiles(qc_batch* b) {
   int64_t we = 1;
   for (qc_grain* g : b->grains) {
     int G, epl;
-    lane_shape(g->n_poles, b->epl, g->precision == QC_MIXED, G, epl);
+    batch_shape(b, g, G, epl);
     we = std::max(we, static_cast<int64_t>(64 / G) * g->maxn * g->n_poles);
   }
   b->wave_elems = we;
@@ -2677,7 +2720,7 @@ void upload_args(qc_batch* b, hipStream_t st) {
   for (size_t gi = 0; gi < b->grains.size(); ++gi) {
     qc_grain* g = b->grains[gi];
     int G, epl;
-    lane_shape(g->n_poles, b->epl, g->precision == QC_MIXED, G, epl);
+    batch_shape(b, g, G, epl);
     qc::SweepArgs a = sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true);
     a.G = G;
     a.log2g = ilog2(G);
@@ -2708,8 +2751,8 @@ void batch_iteration(qc_batch* b, hipStream_t st, bool upload) {
   if (upload) upload_args(b, st);
   const bool mixed = b->precision == QC_MIXED;
   const auto pass = [&](int k) { return b->d_tiles + b->pass_off[k]; };
-  (mixed ? qc::launch_batch_interp<float> : qc::launch_batch_interp<double>)(b->d_args, pass(0), b->pass_n[0], pass(1),
-                                                                             b->pass_n[1], st);
+  (mixed ? qc::launch_batch_interp<float> : qc::launch_batch_interp<double>)(
+      b->d_args, pass(0), b->pass_n[0], pass(1), b->pass_n[1], b->d_counter, st);
   for (size_t k = 0; k < b->grp_epl.size(); ++k) {
     if (mixed)
       qc::launch_batch_sweep<float>(b->grp_epl[k], b->d_args, b->d_tiles + b->grp_off[k], b->grp_n[k],
@@ -2790,7 +2833,7 @@ qc_status qc_batch_create(qc_grain* const* grains, int n, qc_batch** out) {
       qc::launch_fill(a, 2 * g->ncell, 0.0, nullptr);
     }
     b->d_args = static_cast<qc::BatchGrainDev*>(dalloc(sizeof(qc::BatchGrainDev) * n));
-    b->d_counter = static_cast<int*>(dalloc(8 * sizeof(int)));
+    b->d_counter = static_cast<int*>(dalloc(qc::kBatchCounters * sizeof(int)));
     hcheck(hipStreamCreate(&b->own), "stream");
     build_tiles(b);
     hcheck(hipDeviceSynchronize(), "batch setup");

@@ -673,10 +673,6 @@ batch_sweep_kernel(const BatchGrainDev* __restrict__ grains,
   }
 }
 
-__global__ void reset_counter_kernel(int* counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
-}
-
 // --------------------------------------------------------------------------
 // rotate back + angle sums + gap / current / free energy
 // --------------------------------------------------------------------------
@@ -860,7 +856,10 @@ __global__ void __launch_bounds__(256) batch_pack_kernel(const BatchGrainDev* __
 // (one or several components: without or with the packed cells)
 template <typename T>
 __global__ void __launch_bounds__(256) batch_interp_kernel(const BatchGrainDev* __restrict__ grains,
-                                                           const int2* __restrict__ tiles) {
+                                                           const int2* __restrict__ tiles,
+                                                           int* __restrict__ counters) {
+  // (the tile counters of the sweeps that follow)
+  if (blockIdx.x == 0 && threadIdx.x < kBatchCounters) counters[threadIdx.x] = 0;
   const int2 t = tiles[blockIdx.x];
   const BatchGrainDev& gd = grains[__builtin_amdgcn_readfirstlane(t.x)];
   node4<T>* nodes = static_cast<node4<T>*>(const_cast<void*>(gd.b.nodes));
@@ -1378,7 +1377,6 @@ template int64_t sweep_wave_slots<float>(int);
 template <typename T>
 void launch_batch_sweep(int epl, const BatchGrainDev* grains, const int2* tiles, int ntiles, int* counter, int nblocks,
                         void* spill, int64_t wave_elems, hipStream_t st) {
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, counter);
   cpx<T>* sp = static_cast<cpx<T>*>(spill);
 #define QC_BATCH(E)                                                                                                  \
   hipLaunchKernelGGL((batch_sweep_kernel<T, E>), dim3(nblocks), dim3(128), 0, st, grains, tiles, ntiles, counter, sp, \
@@ -1446,12 +1444,12 @@ void launch_rotate_back(const BackArgs& a, hipStream_t st) {
 }
 template <typename T>
 void launch_batch_interp(const BatchGrainDev* grains, const int2* pack, int npack, const int2* interp, int ninterp,
-                         hipStream_t st) {
+                         int* counters, hipStream_t st) {
   if (npack > 0) hipLaunchKernelGGL(batch_pack_kernel<T>, dim3(npack), dim3(256), 0, st, grains, pack);
-  if (ninterp > 0) hipLaunchKernelGGL(batch_interp_kernel<T>, dim3(ninterp), dim3(256), 0, st, grains, interp);
+  if (ninterp > 0) hipLaunchKernelGGL(batch_interp_kernel<T>, dim3(ninterp), dim3(256), 0, st, grains, interp, counters);
 }
-template void launch_batch_interp<float>(const BatchGrainDev*, const int2*, int, const int2*, int, hipStream_t);
-template void launch_batch_interp<double>(const BatchGrainDev*, const int2*, int, const int2*, int, hipStream_t);
+template void launch_batch_interp<float>(const BatchGrainDev*, const int2*, int, const int2*, int, int*, hipStream_t);
+template void launch_batch_interp<double>(const BatchGrainDev*, const int2*, int, const int2*, int, int*, hipStream_t);
 void launch_batch_back(bool several, const BatchGrainDev* grains, const int2* tiles, int n, hipStream_t st) {
   if (n == 0) return;
   const int w = back_waves(n, several ? 2 : 1);

@@ -117,6 +117,8 @@ struct BackArgs {
   const uint8_t* zero_mask;  // grain mask when the off-grain cells are to be zeroed, or nullptr
 };
 
+constexpr int kBatchCounters = 8;  // tile counters of a batch's sweeps (one per lane shape)
+
 // one grain of a batch: the arguments and buffers of its passes
 struct BatchGrainDev {
   SweepArgs a;
@@ -268,7 +270,7 @@ void launch_rotate_back(const BackArgs& a, hipStream_t st);
 // batched grains; the tiles are (grain, block of the grain)
 template <typename T>
 void launch_batch_interp(const BatchGrainDev* grains, const int2* pack, int npack, const int2* interp, int ninterp,
-                         hipStream_t st);
+                         int* counters, hipStream_t st);
 void launch_batch_back(bool several, const BatchGrainDev* grains, const int2* tiles, int n, hipStream_t st);
 void launch_batch_set(const double* delta, const double* A, const uint8_t* mask, int64_t ncell, int ncomp,
                       double* delta_out, double* A_out, hipStream_t st);
