@@ -523,16 +523,17 @@ qc_status qc_grain_set_adjoint_checkpoint(qc_grain* grain, int every);
 
 /* Launch shape of the sweep kernel: energies handled by each lane (1, 2, 3,
  * 4 or 8; 0 = automatic: the fewest padded energy slots weighted by each
- * variant's measured cost, and 2 instead of 4 in a launch that leaves wave
- * slots empty).  The lanes of one trajectory segment share the
+ * variant's measured cost, and 2 or 1 instead of 3 or 4 in a launch that
+ * leaves wave slots empty).  The lanes of one trajectory segment share the
  * per-node energy sums, so fewer energies per lane means more lanes per
  * segment (a power of two up to 64; a forced value that would need more, or
  * that exceeds the number of energies of a launch, is replaced by the
  * automatic choice).  Results are identical up to rounding order. */
 qc_status qc_grain_set_lanes(qc_grain* grain, int energies_per_lane);
-/* The lane shape the next SCF sweep of this grain will use: energies per
- * lane (1, 2, 3, 4 or 8) and lanes per trajectory segment (a power of two
- * <= 64).  Both outputs are host ints written on success. */
+/* The lane shape of this grain's SCF sweeps: energies per lane (1, 2, 3, 4
+ * or 8) and lanes per trajectory segment (a power of two <= 64); an automatic
+ * choice that leaves wave slots empty is narrowed at the launch.  Both
+ * outputs are host ints written on success. */
 qc_status qc_grain_get_lanes(const qc_grain* grain, int* energies_per_lane, int* lanes_per_segment);
 
 /* Split launch shape of the SCF sweep (Matsubara poles).  Segments are

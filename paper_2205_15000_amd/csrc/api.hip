@@ -358,9 +358,6 @@ struct qc_grain {
   double beta = 0.5;
   double* vel_d = nullptr;
   double* vel_a = nullptr;
-  // CongAcc: per-component dot-product partials [component][kParts][3]
-  double* cpart = nullptr;
-  double* cpart_host = nullptr;
   // CongAcc weights set by bisection and by the anti-parallel rule
   int64_t cong_bisect = 0, cong_anti = 0;
   // angle pairs (k, k + n_theta/2): the sweep of the Matsubara iteration
@@ -438,7 +435,7 @@ static double congacc_weight(double mm, double md, double dd, double smin) {
 // (BB dot products 3 kParts each)
 enum {
   kROmega = 0, kRB2 = 1, kRJx = 2, kRJy = 3, kRDiffD = 4, kRDiffJ = 6, kRDiffA = 8, kRBBD = 10, kRBBA = 13,
-  kRegions = 16
+  kRCong = 16  // CongAcc dot products, 3 kParts for each of the 2 ncomp + 2 components
 };
 
 namespace {
@@ -545,8 +542,6 @@ void free_grain(qc_grain* g) {
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (g->part_host) (void)hipHostFree(g->part_host);
-  if (g->cpart) (void)hipFree(g->cpart);
-  if (g->cpart_host) (void)hipHostFree(g->cpart_host);
   for (auto& e : g->ev) {
     (void)hipEventDestroy(e.first);
     (void)hipEventDestroy(e.second);
@@ -558,10 +553,10 @@ hipStream_t S(void* s) { return static_cast<hipStream_t>(s); }
 
 double* region(qc_grain* g, int r) { return g->part + static_cast<int64_t>(r) * kParts; }
 
-// one copy of every block partial to the host, then wait for the stream
-void fetch_parts(qc_grain* g, hipStream_t st) {
-  hcheck(hipMemcpyAsync(g->part_host, g->part, sizeof(double) * kRegions * kParts, hipMemcpyDeviceToHost, st),
-         "D2H");
+// one copy of the block partials (the first n regions) to the host, then wait
+// for the stream
+void fetch_parts(qc_grain* g, hipStream_t st, int n = kRCong) {
+  hcheck(hipMemcpyAsync(g->part_host, g->part, sizeof(double) * n * kParts, hipMemcpyDeviceToHost, st), "D2H");
   hcheck(hipStreamSynchronize(st), "sync");
 }
 
@@ -812,6 +807,16 @@ double omega_from_parts(const qc_grain* g) {
   return tot;
 }
 
+// block partials of the free energy: its condensation part per cell and, with
+// screening, the square of the induced field
+void omega_partials(qc_grain* g, const double* A, hipStream_t st) {
+  if (g->kappa > 0.0)
+    qc::launch_block_sum2({g->omega_cell, nullptr, g->ncg, region(g, kROmega), 0, 0, 0, 0.0},
+                          {A, nullptr, g->ncell, region(g, kRB2), 1, g->nx, g->ny, g->h}, kParts, st);
+  else
+    qc::launch_block_sum(g->omega_cell, nullptr, g->ncg, region(g, kROmega), kParts, st);
+}
+
 // buffers of the iteration map (gamma at nodes, per-node sums, boundary
 // store), allocated on first use so that LDOS-only grains do not hold them
 // spill: also the gamma spill of single-grain sweeps (batched sweeps keep it
@@ -860,14 +865,7 @@ void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_n
   r.zero_mask = zero_out ? g->mask : nullptr;
   qc::launch_rotate_back(r, st);
   hcheck(hipGetLastError(), "rotate-back launch");
-  // block partials of the free energy (condensation and magnetic parts)
-  if (g->kappa > 0.0) {
-    qc::launch_curl(A, g->bbuf, g->nx, g->ny, g->h, st);
-    qc::launch_block_sum2({g->omega_cell, nullptr, g->ncg, 0, region(g, kROmega)},
-                          {g->bbuf, nullptr, g->ncell, 1, region(g, kRB2)}, kParts, st);
-  } else {
-    qc::launch_block_sum(g->omega_cell, nullptr, g->ncg, 0, region(g, kROmega), kParts, st);
-  }
+  omega_partials(g, A, st);
   if (omega_total) {
     fetch_parts(g, st);
     *omega_total = omega_from_parts(g);
@@ -1160,8 +1158,9 @@ qc_status qc_grain_create(int device, const qc_grain_desc* desc, qc_grain** out)
     }
     // gbuf, node_out and the boundary store are allocated by the first sweep
     g->omega_cell = static_cast<double*>(dalloc(sizeof(double) * g->ncg));
-    g->part = static_cast<double*>(dalloc(sizeof(double) * kRegions * kParts));
-    hcheck(hipHostMalloc(reinterpret_cast<void**>(&g->part_host), sizeof(double) * kRegions * kParts),
+    const size_t part_bytes = sizeof(double) * (kRCong + 3 * (2 * g->ncomp + 2)) * kParts;
+    g->part = static_cast<double*>(dalloc(part_bytes));
+    hcheck(hipHostMalloc(reinterpret_cast<void**>(&g->part_host), part_bytes),
            "hipHostMalloc");
     g->bbuf = static_cast<double*>(dalloc(sizeof(double) * g->ncell));
     g->dnew = static_cast<double*>(dalloc(sizeof(double) * 2 * g->ncomp * g->ncell));
@@ -1354,8 +1353,8 @@ void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipS
     return;
   }
   // mean current over the grain cells, subtracted before the solve (App. D)
-  qc::launch_block_sum2({j, g->grain_cells, g->ncg, 0, region(g, kRJx)},
-                        {j + g->ncell, g->grain_cells, g->ncg, 0, region(g, kRJy)}, kParts, st);
+  qc::launch_block_sum2({j, g->grain_cells, g->ncg, region(g, kRJx), 0, 0, 0, 0.0},
+                        {j + g->ncell, g->grain_cells, g->ncg, region(g, kRJy), 0, 0, 0, 0.0}, kParts, st);
   const double inv_n = 1.0 / static_cast<double>(g->ncg);
   if (g->a_nmodes > 0) {
     // the separable kernel kept to its largest modes: two MFMA contractions
@@ -1503,11 +1502,7 @@ qc_status qc_free_energy_lw(qc_grain* g, const double* delta, const double* A_in
     if (omega_density) qc::launch_fill(omega_density, g->ncell, 0.0, st);
     qc::launch_lw_finish(delta, g->grain_cells, g->ncg, g->ncomp, g->ncell, g->n_theta, g->eta, g->wk, g->logt,
                          g->twopi_rz, g->lw_acc, g->omega_cell, omega_density, st);
-    qc::launch_block_sum(g->omega_cell, nullptr, g->ncg, 0, region(g, kROmega), kParts, st);
-    if (g->kappa > 0.0) {
-      qc::launch_curl(A_ind, g->bbuf, g->nx, g->ny, g->h, st);
-      qc::launch_block_sum(g->bbuf, nullptr, g->ncell, 1, region(g, kRB2), kParts, st);
-    }
+    omega_partials(g, A_ind, st);
     fetch_parts(g, st);
     *omega_total = omega_from_parts(g);
     // restore the store the caller's next sweep expects
@@ -1590,7 +1585,7 @@ qc_status qc_magnetic_moment(qc_grain* g, const double* j, double* m_out, void* 
     hipStream_t st = S(stream);
     hcheck(hipSetDevice(g->device), "hipSetDevice");
     qc::launch_torque(j, g->grain_cells, g->ncg, g->ncell, g->nx, g->x0, g->y0, g->h, g->cx, g->cy, g->bbuf, st);
-    qc::launch_block_sum(g->bbuf, nullptr, g->ncg, 0, region(g, kRJx), kParts, st);
+    qc::launch_block_sum(g->bbuf, nullptr, g->ncg, region(g, kRJx), kParts, st);
     fetch_parts(g, st);
     *m_out = region_sum(g, kRJx) / (2.0 * static_cast<double>(g->ncg));
     return QC_OK;
@@ -1641,11 +1636,8 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
     const int ncx = 2 * g->ncomp + 2;
     std::vector<double> cg_a(ncx, alpha), cg_w(ncx, 0.0);
     bool cg_first = true;
-    if (cong && !g->cpart) {
-      g->cpart = static_cast<double*>(dalloc(sizeof(double) * 3 * kParts * ncx));
-      hcheck(hipHostMalloc(reinterpret_cast<void**>(&g->cpart_host), sizeof(double) * 3 * kParts * ncx),
-             "hipHostMalloc");
-    }
+    const qc::CongFields cf{delta_io, A_io, g->dnew, g->anew, g->vel_d, g->vel_a, g->grain_cells, g->ncg, g->ncell,
+                            g->ncomp};
     const double ksc = g->kappa > 0.0 ? g->kappa * g->kappa : 1.0;  // x holds kappa^2 A
     double om_old = 0.0;
     bool have_old = false;
@@ -1678,17 +1670,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
         qc::launch_diff_norm_n(da, nd, kParts, st);
       }
       if (cong && !cg_first) {
-        for (int c = 0; c < ncx; ++c) {
-          double* pc = g->cpart + static_cast<int64_t>(c) * 3 * kParts;
-          if (c < 2 * g->ncomp)
-            qc::launch_congacc_dots(g->dnew, delta_io, g->grain_cells, g->ncg, static_cast<int64_t>(c / 2) * g->ncell,
-                                    2, c % 2, g->vel_d, pc, kParts, st);
-          else
-            qc::launch_congacc_dots(g->anew, A_io, nullptr, g->ncell,
-                                    static_cast<int64_t>(c - 2 * g->ncomp) * g->ncell, 1, 0, g->vel_a, pc, kParts, st);
-        }
-        hcheck(hipMemcpyAsync(g->cpart_host, g->cpart, sizeof(double) * 3 * kParts * ncx, hipMemcpyDeviceToHost, st),
-               "D2H");
+        qc::launch_congacc_dots(cf, region(g, kRCong), kParts, st);
       }
       if (bb) {
         qc::launch_bb_dots(g->dnew, delta_io, g->grain_cells, g->ncg, g->ncomp, g->ncell, 2, 1.0, g->vel_d,
@@ -1697,7 +1679,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
                            st);
       }
       std::swap(g->jold, g->jcur);
-      fetch_parts(g, st);
+      fetch_parts(g, st, cong && !cg_first ? kRCong + 3 * ncx : kRCong);
       if (bb) {
         if (i_bb > 0) {
           double pp = 0.0, pd = 0.0, dd = 0.0;
@@ -1722,7 +1704,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
         for (int c = 0; c < ncx; ++c) {
           if (cg_first) continue;
           double mm = 0.0, md = 0.0, dd = 0.0;
-          const double* q = g->cpart_host + static_cast<int64_t>(c) * 3 * kParts;
+          const double* q = g->part_host + static_cast<int64_t>(kRCong + 3 * c) * kParts;
           for (int b = 0; b < kParts; ++b) {
             mm += q[3 * b];
             md += q[3 * b + 1];
@@ -1740,17 +1722,12 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
             }
           }
         }
-        qc::CongCoef cd{}, ca{};
-        for (int c = 0; c < 2 * g->ncomp; ++c) {
-          cd.a[c] = cg_a[c];
-          cd.w[c] = cg_first ? 0.0 : cg_w[c];
+        qc::CongCoef cc{};
+        for (int c = 0; c < ncx; ++c) {
+          cc.a[c] = cg_a[c];
+          cc.w[c] = cg_first ? 0.0 : cg_w[c];
         }
-        for (int c = 0; c < 2; ++c) {
-          ca.a[c] = cg_a[2 * g->ncomp + c];
-          ca.w[c] = cg_first ? 0.0 : cg_w[2 * g->ncomp + c];
-        }
-        qc::launch_congacc_update(delta_io, g->dnew, g->vel_d, g->grain_cells, g->ncg, g->ncomp, g->ncell, 2, cd, st);
-        qc::launch_congacc_update(A_io, g->anew, g->vel_a, nullptr, g->ncell, 2, g->ncell, 1, ca, st);
+        qc::launch_congacc_update(cf, cc, st);
       }
       const double om = omega_from_parts(g);
       double res[5];
@@ -2517,7 +2494,10 @@ qc_status qc_grain_get_split(qc_grain* g, double* frac, int64_t* n_wide) {
     if (frac) *frac = g->split_frac;
     if (n_wide) {
       hcheck(hipSetDevice(g->device), "hipSetDevice");
-      *n_wide = split_count(g, sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true));
+      int G = 1, epl = 1;
+      lane_shape(g->n_poles, g->epl_override, g->precision == QC_MIXED, G, epl);
+      // (an odd shape has no split, also where the launch narrows it: all segments alike)
+      *n_wide = epl % 2 ? 0 : split_count(g, sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true));
     }
     return QC_OK;
   });
@@ -2526,14 +2506,11 @@ qc_status qc_grain_get_split(qc_grain* g, double* frac, int64_t* n_wide) {
 qc_status qc_grain_get_lanes(const qc_grain* g, int* energies_per_lane, int* lanes_per_segment) {
   if (!g) return fail(QC_ERR_INVALID, "grain is NULL");
   if (!energies_per_lane || !lanes_per_segment) return fail(QC_ERR_INVALID, "output pointers are required");
-  return guarded([&]() -> qc_status {
-    hcheck(hipSetDevice(g->device), "hipSetDevice");
-    int G = 1, epl = 1;
-    grain_shape(g, g->n_poles, g->pairing ? g->nseg_pair : g->nseg, G, epl);
-    *energies_per_lane = epl;
-    *lanes_per_segment = G;
-    return QC_OK;
-  });
+  int G = 1, epl = 1;
+  lane_shape(g->n_poles, g->epl_override, g->precision == QC_MIXED, G, epl);
+  *energies_per_lane = epl;
+  *lanes_per_segment = G;
+  return QC_OK;
 }
 
 qc_status qc_profile_enable(qc_grain* g, int enable) {

@@ -998,10 +998,7 @@ __global__ void fill_kernel(double* __restrict__ p, int64_t n, double v) {
   if (i < n) p[i] = v;
 }
 
-__global__ void __launch_bounds__(256) curl_kernel(const double* __restrict__ A, double* __restrict__ B,
-                                                   int nx, int ny, double h) {
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (c >= static_cast<int64_t>(nx) * ny) return;
+__device__ __forceinline__ double curl_at(const double* __restrict__ A, int64_t c, int nx, int ny, double h) {
   const int i = static_cast<int>(c % nx), j = static_cast<int>(c / nx);
   const double* ax = A;
   const double* ay = A + static_cast<int64_t>(nx) * ny;
@@ -1018,27 +1015,31 @@ __global__ void __launch_bounds__(256) curl_kernel(const double* __restrict__ A,
     dxy = (ax[c] - ax[c - nx]) / h;
   else
     dxy = (ax[c + nx] - ax[c - nx]) / (2 * h);
-  B[c] = dyx - dxy;
+  return dyx - dxy;
+}
+__global__ void __launch_bounds__(256) curl_kernel(const double* __restrict__ A, double* __restrict__ B,
+                                                   int nx, int ny, double h) {
+  const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (c < static_cast<int64_t>(nx) * ny) B[c] = curl_at(A, c, nx, ny, h);
 }
 
-// Block partial sums of f(x) (x gathered through idx when given): mode 0
-// sum x, mode 1 sum x^2.  One partial per block written to part[blockIdx.x];
-// the host adds them in order.
+// Block partial sums: kind 0 of x (gathered through idx when given), kind 1
+// of the square of curl A (x = A), formed where it is summed.  One partial
+// per block written to part[blockIdx.x]; the host adds them in order.
 // Up to two sums per launch: blockIdx.y picks the row (BlockSumRow r0, r1);
 // each row's partials are those a launch of its own would give.
 __global__ void __launch_bounds__(256) block_sum_kernel(BlockSumRow r0, BlockSumRow r1) {
   const BlockSumRow& r = blockIdx.y == 0 ? r0 : r1;
-  const double* __restrict__ x = r.x;
-  const int32_t* __restrict__ idx = r.idx;
-  const int64_t n = r.n;
-  const int mode = r.mode;
-  double* __restrict__ part = r.part;
   __shared__ double sh[256];
   double acc = 0.0;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < r.n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const double v = x[idx ? idx[i] : i];
-    acc += mode == 1 ? v * v : v;
+    if (r.mode == 1) {
+      const double v = curl_at(r.x, i, r.nx, r.ny, r.h);
+      acc += v * v;
+    } else {
+      acc += r.x[r.idx ? r.idx[i] : i];
+    }
   }
   sh[threadIdx.x] = acc;
   __syncthreads();
@@ -1046,7 +1047,7 @@ __global__ void __launch_bounds__(256) block_sum_kernel(BlockSumRow r0, BlockSum
     if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+  if (threadIdx.x == 0) r.part[blockIdx.x] = sh[0];
 }
 
 // Luttinger-Ward free energy (Sec. II): the propagator term at one
@@ -1225,14 +1226,16 @@ __global__ void __launch_bounds__(256) bb_dots_kernel(const double* __restrict__
     for (int c = 0; c < 3; ++c) part[3 * blockIdx.x + c] = sm[c][0];
 }
 
-// CongAcc (App. E): dot products m.m, m.d, d.d of one component of x, with
-// d = xnew - xold and m the component's moving average.
-__global__ void __launch_bounds__(256) congacc_dots_kernel(const double* __restrict__ xnew,
-                                                           const double* __restrict__ xold,
-                                                           const int32_t* __restrict__ idx, int64_t n, int64_t base,
-                                                           int stride, int c, const double* __restrict__ m,
-                                                           double* __restrict__ part) {
+// CongAcc (App. E): dot products m.m, m.d, d.d of every component of x
+// (blockIdx.y), with d = xnew - xold and m the component's moving average.
+__global__ void __launch_bounds__(256) congacc_dots_kernel(CongFields f, double* __restrict__ part) {
   __shared__ double sm[3][256];
+  const int comp = blockIdx.y, nd = 2 * f.ncomp;
+  const bool in_a = comp >= nd;  // components 2 G + (0 re, 1 im) of Delta, then A_x, A_y
+  const int64_t n = in_a ? f.ncell : f.ncg, base = (in_a ? comp - nd : comp / 2) * f.ncell;
+  const int stride = in_a ? 1 : 2, c = in_a ? 0 : comp & 1;
+  const int32_t* idx = in_a ? nullptr : f.grain_cells;
+  const double *xnew = in_a ? f.anew : f.dnew, *xold = in_a ? f.a : f.delta, *m = in_a ? f.ma : f.md;
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -1252,26 +1255,27 @@ __global__ void __launch_bounds__(256) congacc_dots_kernel(const double* __restr
     __syncthreads();
   }
   if (threadIdx.x == 0)
-    for (int j = 0; j < 3; ++j) part[3 * blockIdx.x + j] = sm[j][0];
+    for (int j = 0; j < 3; ++j) part[3 * (static_cast<int64_t>(comp) * gridDim.x + blockIdx.x) + j] = sm[j][0];
 }
 
-// CongAcc step: m <- w m + (1 - w) d, x += a m, with d = gx - x and the
-// coefficients of component r * stride + c.
-__global__ void __launch_bounds__(256) congacc_update_kernel(double* __restrict__ x, const double* __restrict__ gx,
-                                                             double* __restrict__ m, const int32_t* __restrict__ idx,
-                                                             int64_t n, int nrep, int64_t field_stride, int stride,
-                                                             CongCoef cf) {
+// CongAcc step of every component: m <- w m + (1 - w) d, x += a m, with
+// d = gx - x; Delta on the grain cells, then A everywhere.
+__global__ void __launch_bounds__(256) congacc_update_kernel(CongFields f, CongCoef cf) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= n * nrep) return;
-  const int64_t r = t / n, i = t - r * n;
-  const int64_t e = r * field_stride + (idx ? idx[i] : i);
-  for (int c = 0; c < stride; ++c) {
-    const int comp = static_cast<int>(r) * stride + c;
-    const int64_t k = e * stride + c;
+  const int64_t nd = f.ncg * f.ncomp;
+  if (t >= nd + 2 * f.ncell) return;
+  auto step = [&](int comp, int64_t k, double* x, const double* gx, double* m) {
     const double w = cf.w[comp];
     const double mn = w * m[k] + (1.0 - w) * (gx[k] - x[k]);
     m[k] = mn;
     x[k] += cf.a[comp] * mn;
+  };
+  if (t < nd) {
+    const int64_t r = t / f.ncg, e = r * f.ncell + f.grain_cells[t - r * f.ncg];
+    for (int c = 0; c < 2; ++c) step(2 * static_cast<int>(r) + c, 2 * e + c, f.delta, f.dnew, f.md);
+  } else {
+    const int64_t k = t - nd;
+    step(2 * f.ncomp + (k >= f.ncell ? 1 : 0), k, f.a, f.anew, f.ma);
   }
 }
 
@@ -1514,9 +1518,8 @@ void launch_fill(double* p, int64_t n, double v, hipStream_t st) {
 void launch_curl(const double* A, double* B, int nx, int ny, double h, hipStream_t st) {
   hipLaunchKernelGGL(curl_kernel, dim3(nblk(static_cast<int64_t>(nx) * ny)), dim3(256), 0, st, A, B, nx, ny, h);
 }
-void launch_block_sum(const double* x, const int32_t* idx, int64_t n, int mode, double* part, int nparts,
-                      hipStream_t st) {
-  const BlockSumRow r{x, idx, n, mode, part};
+void launch_block_sum(const double* x, const int32_t* idx, int64_t n, double* part, int nparts, hipStream_t st) {
+  const BlockSumRow r{x, idx, n, part, 0, 0, 0, 0.0};
   hipLaunchKernelGGL(block_sum_kernel, dim3(nparts), dim3(256), 0, st, r, r);
 }
 void launch_block_sum2(const BlockSumRow& r0, const BlockSumRow& r1, int nparts, hipStream_t st) {
@@ -1530,16 +1533,12 @@ void launch_diff_norm_n(const DiffNormArgs* a, int count, int nparts, hipStream_
   hipLaunchKernelGGL(diff_norm_kernel, dim3(nparts, count), dim3(256), 0, st, a[0], a[count > 1 ? 1 : 0],
                      a[count > 2 ? 2 : 0]);
 }
-void launch_congacc_dots(const double* xnew, const double* xold, const int32_t* idx, int64_t n, int64_t base,
-                         int stride, int c, const double* m, double* part, int nparts, hipStream_t st) {
-  hipLaunchKernelGGL(congacc_dots_kernel, dim3(nparts), dim3(256), 0, st, xnew, xold, idx, n, base, stride, c, m,
-                     part);
+void launch_congacc_dots(const CongFields& f, double* part, int nparts, hipStream_t st) {
+  hipLaunchKernelGGL(congacc_dots_kernel, dim3(nparts, 2 * f.ncomp + 2), dim3(256), 0, st, f, part);
 }
-void launch_congacc_update(double* x, const double* gx, double* m, const int32_t* idx, int64_t n, int nrep,
-                           int64_t field_stride, int stride, const CongCoef& cf, hipStream_t st) {
-  if (n * nrep > 0)
-    hipLaunchKernelGGL(congacc_update_kernel, dim3(nblk(n * nrep)), dim3(256), 0, st, x, gx, m, idx, n, nrep,
-                       field_stride, stride, cf);
+void launch_congacc_update(const CongFields& f, const CongCoef& cf, hipStream_t st) {
+  const int64_t n = f.ncg * f.ncomp + 2 * f.ncell;
+  if (n > 0) hipLaunchKernelGGL(congacc_update_kernel, dim3(nblk(n)), dim3(256), 0, st, f, cf);
 }
 void launch_bb_dots(const double* xnew, const double* xold, const int32_t* idx, int64_t n, int nrep,
                     int64_t field_stride, int stride, double scale, double* dprev, double* part, int nparts,

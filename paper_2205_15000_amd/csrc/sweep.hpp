@@ -302,28 +302,34 @@ struct BlockSumRow {
   const double* x;
   const int32_t* idx;
   int64_t n;
-  int mode;
   double* part;
+  int mode;       // 0: sum of x, 1: sum of (curl x)^2 over an nx x ny grid
+  int nx, ny;
+  double h;
 };
 // two independent sums in one launch
 void launch_block_sum2(const BlockSumRow& r0, const BlockSumRow& r1, int nparts, hipStream_t st);
-void launch_block_sum(const double* x, const int32_t* idx, int64_t n, int mode, double* part, int nparts,
-                      hipStream_t st);
+void launch_block_sum(const double* x, const int32_t* idx, int64_t n, double* part, int nparts, hipStream_t st);
 void launch_diff_norm(const DiffNormArgs& a, int nparts, hipStream_t st);
 // 1 to 3 independent fields in one launch (blockIdx.y picks the field)
 void launch_diff_norm_n(const DiffNormArgs* a, int count, int nparts, hipStream_t st);
 // CongAcc (App. E): per-component step sizes and weights of one field
-constexpr int kCongMaxComp = 8;
+constexpr int kCongMaxComp = 10;
 struct CongCoef {
   double a[kCongMaxComp], w[kCongMaxComp];
 };
-// partials [nparts][3] of m.m, m.d, d.d over component c of the elements
-// (base + idx[i] or base + i) * stride + c, d = xnew - xold
-void launch_congacc_dots(const double* xnew, const double* xold, const int32_t* idx, int64_t n, int64_t base,
-                         int stride, int c, const double* m, double* part, int nparts, hipStream_t st);
-// m <- w m + (1 - w) d, x += a m with the coefficients of component r * stride + c
-void launch_congacc_update(double* x, const double* gx, double* m, const int32_t* idx, int64_t n, int nrep,
-                           int64_t field_stride, int stride, const CongCoef& cf, hipStream_t st);
+// the fields of a CongAcc step: x, g(x) and the moving average of each
+struct CongFields {
+  double *delta, *a;          // Delta [ncomp][ncell] complex, A [2][ncell]
+  const double *dnew, *anew;
+  double *md, *ma;
+  const int32_t* grain_cells;
+  int64_t ncg, ncell;
+  int ncomp;
+};
+// partials [2 ncomp + 2][nparts][3] of m.m, m.d, d.d per component
+void launch_congacc_dots(const CongFields& f, double* part, int nparts, hipStream_t st);
+void launch_congacc_update(const CongFields& f, const CongCoef& cf, hipStream_t st);
 // partials [nparts][3] of dp.dp, dp.(d - dp), (d - dp).(d - dp), d = scale (xnew - xold); dprev <- d
 void launch_bb_dots(const double* xnew, const double* xold, const int32_t* idx, int64_t n, int nrep,
                     int64_t field_stride, int stride, double scale, double* dprev, double* part, int nparts,
