@@ -364,10 +364,9 @@ struct qc_grain {
   // runs the lower angles only (see build_pairs); pair_ok when the tables
   // allow it, pairing when it is in use
   bool pair_ok = false, pairing = false, rb_fold = false;
-  int64_t nseg_pair = 0, nslot_pair = 0, npairs = 0;
+  int64_t nseg_pair = 0, nslot_pair = 0;
   int32_t* order_pair = nullptr;
   int4* rb4_pair = nullptr;
-  int2* mirror_pairs = nullptr;
   int32_t* seg_upper = nullptr;  // upper segment of each lower one
   // transposed rotate-back of the paired reverse mode: the entries of the
   // upper angles moved onto their mirror slots
@@ -538,7 +537,7 @@ void free_grain(qc_grain* g) {
                   g->ghat, g->twx, g->twy, g->dnew, g->jcur, g->jold, g->anew, g->vel_d, g->vel_a, g->gtbuf, g->gS, g->gC, g->gV, g->itp_dend, g->itp_aend,
                   g->bt_ptr, g->bt_c, g->bt_w, g->it_dptr, g->it_ds, g->it_dw, g->it_aptr, g->it_as, g->it_aw,
                   g->ckbase, g->ckg, g->ckgt, g->ckscr, g->lw_acc, g->lw_dl, g->lw_save, g->order_pair, g->rb4_pair,
-                  g->mirror_pairs, g->seg_upper, g->a_lam, g->a_vk, g->a_jp, g->a_y, g->btp_ptr, g->btp_c, g->btp_w};
+                  g->seg_upper, g->a_lam, g->a_vk, g->a_jp, g->a_y, g->btp_ptr, g->btp_c, g->btp_w};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (g->part_host) (void)hipHostFree(g->part_host);
@@ -749,6 +748,7 @@ qc::SweepArgs sweep_args(qc_grain* g, int n_e, int n_e_tot, int e_off, const dou
   a.maxn = g->maxn;
   a.nlong = 0;
   a.mirror = pair ? g->seg_upper : nullptr;
+  a.partner = nullptr;
   return a;
 }
 
@@ -832,13 +832,9 @@ void ensure_sweep_buffers(qc_grain* g, bool spill = true) {
     for (int b = 0; b < 2; ++b) g->bc[a][b] = dalloc(2 * rb * g->nseg * g->n_poles);
 }
 
-// steps 3-8 of one iteration; omega_total (host) optional (synchronises)
-// zero_out: also write zeros to delta_new, j (and omega) off the grain; a
-// caller that keeps those cells at zero itself may skip it
-void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_new, double* j, double* omega,
-              double* omega_total, hipStream_t st, bool zero_out = true) {
-  ensure_sweep_buffers(g);
-  do_interp(g, delta, A, st, true);
+// one march of every segment over the interpolated nodes into the other half
+// of the boundary store: with the node sums, or (bc_only) the end values alone
+void march_sweep(qc_grain* g, bool bc_only, hipStream_t st) {
   qc::SweepArgs a = sweep_args(g, g->n_poles, g->n_poles, 0, g->eps, g->rpd, true);
   a.bc_valid = g->bc_valid;
   a.nlong = split_count(g, a);
@@ -848,19 +844,29 @@ void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_n
     ++a.log2g;
     a.nlong = 0;
   }
+  if (bc_only) a.nlong = 0;
   qc::SweepBufs b;
   b.nodes = g->nodes;
   b.bc_g_prev = g->bc[g->bc_cur][0];
   b.bc_gt_prev = g->bc[g->bc_cur][1];
   b.bc_g_next = g->bc[1 - g->bc_cur][0];
   b.bc_gt_next = g->bc[1 - g->bc_cur][1];
-  b.gbuf = g->gbuf;
+  b.gbuf = bc_only ? nullptr : g->gbuf;
   b.ebuf = nullptr;
-  launch_sweep_timed(g, 0, a, b, st);
+  launch_sweep_timed(g, bc_only ? 2 : 0, a, b, st);
   g->last_bc_valid = g->bc_valid;
   g->bc_cur = 1 - g->bc_cur;
   g->bc_valid = 1;
+}
 
+// steps 3-8 of one iteration; omega_total (host) optional (synchronises)
+// zero_out: also write zeros to delta_new, j (and omega) off the grain; a
+// caller that keeps those cells at zero itself may skip it
+void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_new, double* j, double* omega,
+              double* omega_total, hipStream_t st, bool zero_out = true) {
+  ensure_sweep_buffers(g);
+  do_interp(g, delta, A, st, true);
+  march_sweep(g, false, st);
   qc::BackArgs r = back_args(g, delta, delta_new, j, omega);
   r.zero_mask = zero_out ? g->mask : nullptr;
   qc::launch_rotate_back(r, st);
@@ -1141,15 +1147,11 @@ qc_status qc_grain_create(int device, const qc_grain_desc* desc, qc_grain** out)
       g->len_order_pair.resize(ord.size());
       for (size_t k = 0; k < ord.size(); ++k) g->len_order_pair[k] = p.seg_n[ord[k]];
       g->rb4_pair = static_cast<int4*>(upload(p.rb4_pair));
-      std::vector<int2> mp;
-      for (int64_t sg = p.nseg_pair; sg < p.nseg; ++sg) mp.push_back(make_int2(static_cast<int>(sg), p.seg_mirror[sg]));
-      g->mirror_pairs = static_cast<int2*>(upload(mp));
       std::vector<int32_t> upper(static_cast<size_t>(p.nseg_pair), -1);
-      for (const int2& m : mp) upper[m.y] = m.x;
+      for (int64_t sg = p.nseg_pair; sg < p.nseg; ++sg) upper[p.seg_mirror[sg]] = static_cast<int32_t>(sg);
       for (int32_t u : upper)
         if (u < 0) throw std::logic_error("angle pairs: a lower segment without its upper one");
       g->seg_upper = static_cast<int32_t*>(upload(upper));
-      g->npairs = static_cast<int64_t>(mp.size());
       g->nseg_pair = p.nseg_pair;
       g->nslot_pair = p.nslot_pair;
       g->pair_ok = true;
@@ -1494,8 +1496,14 @@ qc_status qc_free_energy_lw(qc_grain* g, const double* delta, const double* A_in
     for (int l = 0; l < n_lambda; ++l) {
       qc::launch_scale(delta, lam[l], 2 * g->ncomp * g->ncell, g->lw_dl, st);
       g->bc_valid = 0;  // each coupling starts from bulk roots of lambda Delta
-      for (int it = 0; it <= bc_iters; ++it)
-        do_sweep(g, g->lw_dl, A_ind, g->dnew, g->jcur, nullptr, nullptr, st, false);
+      // The first sweeps serve the boundary values only: the nodes are the
+      // same for all of them, and the sums of the last alone are read.  With
+      // whole sweeps a coupling of 101 x 97, two components, took three of
+      // interpolation (9.6 us), sweep (48), rotate-back (18) and sums (4.7).
+      do_interp(g, g->lw_dl, A_ind, st, true);
+      for (int it = 0; it <= bc_iters; ++it) march_sweep(g, it < bc_iters, st);
+      qc::launch_rotate_back(back_args(g, g->lw_dl, g->dnew, g->jcur, nullptr), st);
+      hcheck(hipGetLastError(), "rotate-back launch");
       qc::launch_lw_accumulate(delta, g->dnew, g->grain_cells, g->ncg, g->ncomp, g->ncell, g->den, wl[l], l == 0,
                                g->lw_acc, st);
     }
@@ -1872,17 +1880,12 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
         const int ne = std::min(blk_all, n_e - e0);
         qc::SweepArgs a = sweep_args(g, ne, n_e, e0, deps, nullptr, pair);
         a.bc_valid = it > 0;
+        a.partner = dpart;  // (read where angles are paired)
         b.bc_g_prev = bcl[cur][0];
         b.bc_gt_prev = bcl[cur][1];
         b.bc_g_next = bcl[1 - cur][0];
         b.bc_gt_next = bcl[1 - cur][1];
         launch_sweep_timed(g, 2, a, b, st);
-      }
-      if (pair) {
-        if (g->precision == QC_MIXED)
-          qc::launch_mirror_fill<float>(g->mirror_pairs, g->npairs, n_e, dpart, bcl[1 - cur][0], bcl[1 - cur][1], st);
-        else
-          qc::launch_mirror_fill<double>(g->mirror_pairs, g->npairs, n_e, dpart, bcl[1 - cur][0], bcl[1 - cur][1], st);
       }
       cur = 1 - cur;
     }

@@ -582,11 +582,14 @@ __device__ __forceinline__ void sweep_march(const SweepArgs& a, bool live, int64
     for (int i = 0; i < EPL; ++i)
       if (own[i]) dst[i] = g[i];
     // gamma~ along a line is the conjugate of gamma along the reversed line
-    // (even order parameter): the end values of the upper angle of a pair
-    if (MODE == 0 && a.mirror) {
-      cpx<T>* mdst = bc_mirror + static_cast<int64_t>(a.mirror[seg]) * a.n_e_tot + a.e_off + es;
-      for (int i = 0; i < EPL; ++i)
-        if (own[i]) mdst[i] = mk(g[i].x, -g[i].y);
+    // (even order parameter), at a real energy e of gamma at -e: the end
+    // values of the upper angle of a pair
+    if (MODE != 1 && a.mirror) {
+      cpx<T>* mdst = bc_mirror + static_cast<int64_t>(a.mirror[seg]) * a.n_e_tot;
+      for (int i = 0; i < EPL; ++i) {
+        const int e = a.e_off + es + i;
+        if (own[i]) mdst[MODE == 2 && a.partner ? a.partner[e] : e] = mk(g[i].x, -g[i].y);
+      }
     }
   }
 }
@@ -889,26 +892,6 @@ __global__ void __launch_bounds__(256) batch_set_kernel(const double2* __restric
     delta_out[g * ncell + i] = mask[i] ? delta[g * ncell + i] : make_double2(0.0, 0.0);
   A_out[i] = A ? A[i] : 0.0;
   A_out[ncell + i] = A ? A[ncell + i] : 0.0;
-}
-
-// End values of the upper angles of pairs at real energies, from their mirror
-// segments' values at the partner energies (see sweep_march for the relation;
-// a Matsubara sweep writes them itself)
-template <typename T>
-__global__ void __launch_bounds__(256) mirror_fill_kernel(const int2* __restrict__ pairs, int64_t npairs, int n_e,
-                                                          const int32_t* __restrict__ partner,
-                                                          cpx<T>* __restrict__ bc_g, cpx<T>* __restrict__ bc_gt) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= npairs * n_e) return;
-  const int64_t q = t / n_e;
-  const int e = static_cast<int>(t - q * n_e);
-  const int2 pr = pairs[q];
-  // the reversed direction at e mirrors energy -e (partner)
-  const int es = partner[e];
-  const int64_t dst = static_cast<int64_t>(pr.x) * n_e + e, src = static_cast<int64_t>(pr.y) * n_e + es;
-  const cpx<T> g = bc_g[src], gt = bc_gt[src];
-  bc_g[dst] = mk(gt.x, -gt.y);
-  bc_gt[dst] = mk(g.x, -g.y);
 }
 
 // Rotate-back and angle sums of the per-node, per-energy values of sweep mode
@@ -1407,16 +1390,6 @@ void launch_valu_rate(int op, float* out, int nblocks, int iters, hipStream_t st
     default: hipLaunchKernelGGL(valu_rate_kernel<3>, dim3(nblocks), dim3(256), 0, st, out, iters, 0.999f); break;
   }
 }
-
-template <typename T>
-void launch_mirror_fill(const int2* pairs, int64_t npairs, int n_e, const int32_t* partner, void* bc_g, void* bc_gt,
-                        hipStream_t st) {
-  if (npairs * n_e > 0)
-    hipLaunchKernelGGL(mirror_fill_kernel<T>, dim3(nblk(npairs * n_e)), dim3(256), 0, st, pairs, npairs, n_e, partner,
-                       static_cast<cpx<T>*>(bc_g), static_cast<cpx<T>*>(bc_gt));
-}
-template void launch_mirror_fill<float>(const int2*, int64_t, int, const int32_t*, void*, void*, hipStream_t);
-template void launch_mirror_fill<double>(const int2*, int64_t, int, const int32_t*, void*, void*, hipStream_t);
 
 template <int W>
 static void launch_back_w(const BackArgs& a, hipStream_t st) {

@@ -68,9 +68,11 @@ struct SweepArgs {
   // segments of the launch order take 2G lanes and EPL/2 energies per lane,
   // the rest G lanes and EPL; nlong * 2G is a multiple of 64 (0: one shape)
   int64_t nlong;
-  // Matsubara sweeps over the lower angles of pairs: the upper angle's segment
-  // on the same line, by segment (nullptr: no pairs)
+  // sweeps over the lower angles of pairs: the upper angle's segment on the
+  // same line, by segment (nullptr: no pairs), and at real energies the index
+  // of -e for every e (partner of partner: e itself)
   const int32_t* mirror;
+  const int32_t* partner;
 };
 
 struct SweepBufs {
@@ -277,12 +279,6 @@ void launch_batch_set(const double* delta, const double* A, const uint8_t* mask,
 // End values of the upper angle of each pair from its mirror segment:
 // gamma_end(s') = conj(gamma~_end(s)), gamma~_end(s') = conj(gamma_end(s))
 // for each (s', s) in pairs, n_e energies per segment (T = float or double)
-template <typename T>
-// partner: for real energies, the index of -e for each energy e of the
-// store (the reversed direction at e mirrors energy -e); nullptr for the
-// Matsubara poles (each its own partner)
-void launch_mirror_fill(const int2* pairs, int64_t npairs, int n_e, const int32_t* partner, void* bc_g, void* bc_gt,
-                        hipStream_t st);
 // blocks of 256 lanes, each lane writes out[lane]: out holds nblocks * 256 floats
 void launch_valu_rate(int op, float* out, int nblocks, int iters, hipStream_t st);
 template <typename T>
