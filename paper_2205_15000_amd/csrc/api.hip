@@ -616,6 +616,9 @@ qc::BackArgs back_args(qc_grain* g, const double* delta, double* dnew, double* j
   r.omega = omega;
   r.omega_cell = g->omega_cell;
   r.zero_mask = nullptr;
+  r.sums = nullptr;
+  r.curl_A = nullptr;
+  r.nparts = kParts;
   return r;
 }
 
@@ -817,6 +820,13 @@ void omega_partials(qc_grain* g, const double* A, hipStream_t st) {
     qc::launch_block_sum(g->omega_cell, nullptr, g->ncg, region(g, kROmega), kParts, st);
 }
 
+// Whether the rotate-back of a sweep also leaves the partial sums of the free
+// energy and of the current: where its blocks of 64 cells, and those of 512
+// and more over the grid, have a partial each.  On such grids the launches
+// that these sums would take weigh more than the sums (two of 14 of an SCF
+// iteration; ten on 40 x 40: 1.11 -> 1.00 ms, with the packing saved too).
+bool fused_sums(const qc_grain* g) { return (g->ncg + 63) / 64 <= kParts && (g->ncell + 511) / 512 <= kParts; }
+
 // buffers of the iteration map (gamma at nodes, per-node sums, boundary
 // store), allocated on first use so that LDOS-only grains do not hold them
 // spill: also the gamma spill of single-grain sweeps (batched sweeps keep it
@@ -869,16 +879,20 @@ void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_n
   march_sweep(g, false, st);
   qc::BackArgs r = back_args(g, delta, delta_new, j, omega);
   r.zero_mask = zero_out ? g->mask : nullptr;
+  if (fused_sums(g)) {
+    r.sums = g->part;
+    r.curl_A = g->kappa > 0.0 ? A : nullptr;
+  }
   qc::launch_rotate_back(r, st);
   hcheck(hipGetLastError(), "rotate-back launch");
-  omega_partials(g, A, st);
+  if (!fused_sums(g)) omega_partials(g, A, st);
   if (omega_total) {
     fetch_parts(g, st);
     *omega_total = omega_from_parts(g);
   }
 }
 
-void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipStream_t st);
+void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipStream_t st, bool j_summed = false);
 
 }  // namespace
 
@@ -1348,15 +1362,17 @@ qc_status qc_sweep_static_bytes(const qc_grain* g, size_t* needed, size_t* avail
 
 namespace {
 
-void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipStream_t st) {
+// (j_summed: the partial sums of j are there, from the sweep that gave it)
+void do_solve_A(qc_grain* g, const double* j, double* A_out, double* B_out, hipStream_t st, bool j_summed) {
   if (g->kappa <= 0.0) {
     qc::launch_fill(A_out, 2 * g->ncell, 0.0, st);
     if (B_out) qc::launch_fill(B_out, g->ncell, 0.0, st);
     return;
   }
   // mean current over the grain cells, subtracted before the solve (App. D)
-  qc::launch_block_sum2({j, g->grain_cells, g->ncg, region(g, kRJx), 0, 0, 0, 0.0},
-                        {j + g->ncell, g->grain_cells, g->ncg, region(g, kRJy), 0, 0, 0, 0.0}, kParts, st);
+  if (!j_summed)
+    qc::launch_block_sum2({j, g->grain_cells, g->ncg, region(g, kRJx), 0, 0, 0, 0.0},
+                          {j + g->ncell, g->grain_cells, g->ncg, region(g, kRJy), 0, 0, 0, 0.0}, kParts, st);
   const double inv_n = 1.0 / static_cast<double>(g->ncg);
   if (g->a_nmodes > 0) {
     // the separable kernel kept to its largest modes: two MFMA contractions
@@ -1663,7 +1679,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
         if (residuals_out) std::memcpy(residuals_out + 5 * it, res, sizeof(res));
         continue;
       }
-      do_solve_A(g, g->jcur, g->anew, nullptr, st);
+      do_solve_A(g, g->jcur, g->anew, nullptr, st, fused_sums(g));
       // residuals of Delta and A with their Picard steps fused in
       // (BB: norms and dot products first; the step follows once its size is known)
       // (the three fields in one launch)

@@ -70,14 +70,17 @@ __global__ void __launch_bounds__(256) interp_kernel(InterpArgs a, node4<T>* __r
 // outside the grain carry a NaN in Re Delta: the masked interpolation reads
 // the mask from the same record instead of a separate dependent load.
 template <typename T>
-__device__ __forceinline__ void pack_cell(const InterpArgs& a, int64_t i, cell4<T>* __restrict__ cells) {
-  if (i >= a.ncell) return;
+__device__ __forceinline__ cell4<T> cell_values(const InterpArgs& a, int64_t i) {
   cell4<T> c;
   c.dx = a.geom.mask[i] ? static_cast<T>(a.delta[2 * i]) : __builtin_nan("");
   c.dy = static_cast<T>(a.delta[2 * i + 1]);
   c.ax = static_cast<T>(a.A[i]);
   c.ay = static_cast<T>(a.A[a.ncell + i]);
-  cells[i] = c;
+  return c;
+}
+template <typename T>
+__device__ __forceinline__ void pack_cell(const InterpArgs& a, int64_t i, cell4<T>* __restrict__ cells) {
+  if (i < a.ncell) cells[i] = cell_values<T>(a, i);
 }
 template <typename T>
 __global__ void __launch_bounds__(256) pack_cells_kernel(InterpArgs a, cell4<T>* __restrict__ cells) {
@@ -88,9 +91,15 @@ __global__ void __launch_bounds__(256) pack_cells_kernel(InterpArgs a, cell4<T>*
 // weights): masked bilinear for Delta with the nearest-grain-cell fallback,
 // clamped bilinear for A_ind.  Away from the array edge the two stencils
 // share their corners, and the four records serve both.
-template <typename T>
+// PACKED: the cells from the packed records, or straight from the fields (the
+// same values).
+template <typename T, bool PACKED>
 __device__ __forceinline__ void interp1_block(const InterpArgs& a, int block, const cell4<T>* __restrict__ cells,
                                               node4<T>* __restrict__ nodes) {
+  auto cell_at = [&](int64_t i) {
+    if constexpr (PACKED) return cells[i];
+    return cell_values<T>(a, i);
+  };
   // one wave per segment: its record is read once (scalar loads), and each
   // lane takes every 64th slot of the segment
   const int64_t seg = __builtin_amdgcn_readfirstlane(block * 4 + static_cast<int>(threadIdx.x >> 6));
@@ -122,7 +131,7 @@ __device__ __forceinline__ void interp1_block(const InterpArgs& a, int block, co
       const int ci = i0 + (c & 1), cj = j0 + (c >> 1);
       const bool in = ci >= 0 && ci < gg.nx && cj >= 0 && cj < gg.ny;
       const int lc = min(max(ci, 0), gg.nx - 1), lj = min(max(cj, 0), gg.ny - 1);
-      v[c] = cells[static_cast<int64_t>(lj) * gg.nx + lc];
+      v[c] = cell_at(static_cast<int64_t>(lj) * gg.nx + lc);
       const bool ok = in && v[c].dx == v[c].dx;  // NaN marks cells outside the grain
       if (!ok) w[c] = 0.0;
       tot += w[c];
@@ -130,7 +139,7 @@ __device__ __forceinline__ void interp1_block(const InterpArgs& a, int block, co
     const double ex = a.eta[2 * k], ey = a.eta[2 * k + 1];
     double dx = 0.0, dy = 0.0;
     if (fb >= 0) {
-      const cell4<T> f = cells[fb];
+      const cell4<T> f = cell_at(fb);
       const double fx0 = static_cast<double>(f.dx), fy0 = static_cast<double>(f.dy);
       dx = ex * fx0 - ey * fy0;
       dy = ex * fy0 + ey * fx0;
@@ -164,7 +173,7 @@ __device__ __forceinline__ void interp1_block(const InterpArgs& a, int block, co
     } else {
       const int64_t b0 = static_cast<int64_t>(j0a) * gg.nx + i0a;
       for (int c = 0; c < 4; ++c) {
-        const cell4<T> u = cells[b0 + (c & 1) + (c >> 1) * gg.nx];
+        const cell4<T> u = cell_at(b0 + (c & 1) + (c >> 1) * gg.nx);
         ax += static_cast<double>(u.ax) * aw[c];
         ay += static_cast<double>(u.ay) * aw[c];
       }
@@ -192,10 +201,10 @@ __device__ __forceinline__ void interp1_block(const InterpArgs& a, int block, co
     nodes[s] = o;
   }
 }
-template <typename T>
+template <typename T, bool PACKED>
 __global__ void __launch_bounds__(256) interp1_kernel(InterpArgs a, const cell4<T>* __restrict__ cells,
                                                       node4<T>* __restrict__ nodes) {
-  interp1_block<T>(a, static_cast<int>(blockIdx.x), cells, nodes);
+  interp1_block<T, PACKED>(a, static_cast<int>(blockIdx.x), cells, nodes);
 }
 
 // --------------------------------------------------------------------------
@@ -676,6 +685,27 @@ batch_sweep_kernel(const BatchGrainDev* __restrict__ grains,
   }
 }
 
+// (curl A)_z by central differences, one-sided at the grid's edges
+__device__ __forceinline__ double curl_at(const double* __restrict__ A, int64_t c, int nx, int ny, double h) {
+  const int i = static_cast<int>(c % nx), j = static_cast<int>(c / nx);
+  const double* ax = A;
+  const double* ay = A + static_cast<int64_t>(nx) * ny;
+  double dyx, dxy;  // d_x A_y, d_y A_x
+  if (i == 0)
+    dyx = (ay[c + 1] - ay[c]) / h;
+  else if (i == nx - 1)
+    dyx = (ay[c] - ay[c - 1]) / h;
+  else
+    dyx = (ay[c + 1] - ay[c - 1]) / (2 * h);
+  if (j == 0)
+    dxy = (ax[c + nx] - ax[c]) / h;
+  else if (j == ny - 1)
+    dxy = (ax[c] - ax[c - nx]) / h;
+  else
+    dxy = (ax[c + nx] - ax[c - nx]) / (2 * h);
+  return dyx - dxy;
+}
+
 // --------------------------------------------------------------------------
 // rotate back + angle sums + gap / current / free energy
 // --------------------------------------------------------------------------
@@ -798,40 +828,72 @@ __device__ __forceinline__ void rotate_back_block(const BackArgs& a, int64_t blo
     p[64 * 11] = d2avg;
   }
   __syncthreads();
-  if (wv > 0 || !live) return;
-  for (int w = 0; w < W - 1; ++w) {
-    const double* p = &part[w][0][lane];
-    for (int g = 0; g < ncomp; ++g) {
-      nx_[g] += p[64 * (2 * g)];
-      ny_[g] += p[64 * (2 * g + 1)];
-    }
-    jx += p[64 * 8];
-    jy += p[64 * 9];
-    icell += p[64 * 10];
-    d2avg += p[64 * 11];
-  }
+  if (wv > 0) return;
   double om = 0.0;
-  for (int g = 0; g < ncomp; ++g) {
-    const double vx = nx_[g] / a.den[g], vy = ny_[g] / a.den[g];
-    double* const o = a.delta_new + 2 * (static_cast<int64_t>(g) * a.ncell + cell);
-    o[0] = UPDATE ? dx_[g] + (vx - dx_[g]) : vx;
-    o[1] = UPDATE ? dy_[g] + (vy - dy_[g]) : vy;
-    om += (dx_[g] * dx_[g] + dy_[g] * dy_[g]) * a.logt[g];
+  if (live) {
+    for (int w = 0; w < W - 1; ++w) {
+      const double* p = &part[w][0][lane];
+      for (int g = 0; g < ncomp; ++g) {
+        nx_[g] += p[64 * (2 * g)];
+        ny_[g] += p[64 * (2 * g + 1)];
+      }
+      jx += p[64 * 8];
+      jy += p[64 * 9];
+      icell += p[64 * 10];
+      d2avg += p[64 * 11];
+    }
+    for (int g = 0; g < ncomp; ++g) {
+      const double vx = nx_[g] / a.den[g], vy = ny_[g] / a.den[g];
+      double* const o = a.delta_new + 2 * (static_cast<int64_t>(g) * a.ncell + cell);
+      o[0] = UPDATE ? dx_[g] + (vx - dx_[g]) : vx;
+      o[1] = UPDATE ? dy_[g] + (vy - dy_[g]) : vy;
+      om += (dx_[g] * dx_[g] + dy_[g] * dy_[g]) * a.logt[g];
+    }
+    om += a.twopi_rz * d2avg - icell;
+    a.j[cell] = jx;
+    a.j[a.ncell + cell] = jy;
+    if (a.omega) a.omega[cell] = om;
+    a.omega_cell[c] = om;
   }
-  om += a.twopi_rz * d2avg - icell;
-  a.j[cell] = jx;
-  a.j[a.ncell + cell] = jy;
-  if (a.omega) a.omega[cell] = om;
-  a.omega_cell[c] = om;
+  if (a.sums) {
+    const double so = group_sum(om, 64), sx = group_sum(live ? jx : 0.0, 64), sy = group_sum(live ? jy : 0.0, 64);
+    if (lane == 0) {
+      a.sums[block] = so;
+      a.sums[2 * a.nparts + block] = sx;
+      a.sums[3 * a.nparts + block] = sy;
+    }
+  }
 }
 
 template <int NC, int W>
 __global__ void __launch_bounds__(64 * W) rotate_back_kernel(BackArgs a) {
   __shared__ double part[W - 1][kBackFields][64];
   const int nblk = static_cast<int>((a.ncg + 63) / 64);
-  if (static_cast<int>(blockIdx.x) >= nblk) {  // zeros off the grain
-    const int64_t cell = static_cast<int64_t>(blockIdx.x - nblk) * (64 * W) + threadIdx.x;
-    if (cell >= a.ncell || a.zero_mask[cell]) return;
+  if (static_cast<int>(blockIdx.x) >= nblk) {  // zeros off the grain, partial sums over the grid
+    const int b = blockIdx.x - nblk;
+    const int64_t cell = static_cast<int64_t>(b) * (64 * W) + threadIdx.x;
+    if (a.sums) {
+      // (every block of these leaves its share of the entries without one at zero)
+      const int others = gridDim.x - nblk;
+      for (int i = static_cast<int>(cell); i < a.nparts; i += others * 64 * W) {
+        for (int r = 0; r < 4; ++r)
+          if (i >= (r == 1 ? others : nblk)) a.sums[r * a.nparts + i] = 0.0;
+      }
+      double v = 0.0;
+      if (a.curl_A && cell < a.ncell) {
+        v = curl_at(a.curl_A, cell, a.nx, static_cast<int>(a.ncell / a.nx), a.h);
+        v *= v;
+      }
+      v = group_sum(v, 64);
+      double* const sh = &part[0][0][0];
+      if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        for (int w = 1; w < W; ++w) v += sh[w];
+        a.sums[a.nparts + b] = v;
+      }
+    }
+    if (!a.zero_mask || cell >= a.ncell || a.zero_mask[cell]) return;
     for (int g = 0; g < a.ncomp; ++g)
       reinterpret_cast<double2*>(a.delta_new)[g * a.ncell + cell] = make_double2(0.0, 0.0);
     a.j[cell] = 0.0;
@@ -867,7 +929,7 @@ __global__ void __launch_bounds__(256) batch_interp_kernel(const BatchGrainDev* 
   const BatchGrainDev& gd = grains[__builtin_amdgcn_readfirstlane(t.x)];
   node4<T>* nodes = static_cast<node4<T>*>(const_cast<void*>(gd.b.nodes));
   if (gd.cells)
-    interp1_block<T>(gd.ia, __builtin_amdgcn_readfirstlane(t.y), static_cast<const cell4<T>*>(gd.cells), nodes);
+    interp1_block<T, true>(gd.ia, __builtin_amdgcn_readfirstlane(t.y), static_cast<const cell4<T>*>(gd.cells), nodes);
   else
     interp_slot<T>(gd.ia, static_cast<int64_t>(t.y) * 256 + threadIdx.x, nodes);
 }
@@ -981,25 +1043,6 @@ __global__ void fill_kernel(double* __restrict__ p, int64_t n, double v) {
   if (i < n) p[i] = v;
 }
 
-__device__ __forceinline__ double curl_at(const double* __restrict__ A, int64_t c, int nx, int ny, double h) {
-  const int i = static_cast<int>(c % nx), j = static_cast<int>(c / nx);
-  const double* ax = A;
-  const double* ay = A + static_cast<int64_t>(nx) * ny;
-  double dyx, dxy;  // d_x A_y, d_y A_x
-  if (i == 0)
-    dyx = (ay[c + 1] - ay[c]) / h;
-  else if (i == nx - 1)
-    dyx = (ay[c] - ay[c - 1]) / h;
-  else
-    dyx = (ay[c + 1] - ay[c - 1]) / (2 * h);
-  if (j == 0)
-    dxy = (ax[c + nx] - ax[c]) / h;
-  else if (j == ny - 1)
-    dxy = (ax[c] - ax[c - nx]) / h;
-  else
-    dxy = (ax[c + nx] - ax[c - nx]) / (2 * h);
-  return dyx - dxy;
-}
 __global__ void __launch_bounds__(256) curl_kernel(const double* __restrict__ A, double* __restrict__ B,
                                                    int nx, int ny, double h) {
   const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1292,11 +1335,21 @@ static inline unsigned nblk(int64_t n, int b = 256) { return static_cast<unsigne
 template <typename T>
 void launch_interp(const InterpArgs& a, void* cells, void* nodes, hipStream_t st) {
   if (a.nslot == 0) return;
+  // One component: over packed cells, or on small grids, where a launch costs
+  // more than the packing saves, straight from the fields (a sweep, FP64 and
+  // mixed, packed and straight: 60.3 / 57.6 and 58.9 / 57.4 us on 32 x 32, 72.5
+  // / 68 and 70.6 / 66.9 on 64 x 64, 91.5 / 79 on 96 x 96 either way, 111 / 91
+  // and 111 / 92.4 on 128 x 128, 161 / 128 and 167 / 139 on 200 x 200).
   if (cells && a.ncomp == 1) {
-    hipLaunchKernelGGL(pack_cells_kernel<T>, dim3(nblk(a.ncell)), dim3(256), 0, st, a,
-                       static_cast<cell4<T>*>(cells));
-    hipLaunchKernelGGL(interp1_kernel<T>, dim3(static_cast<unsigned>((a.nseg + 3) / 4)), dim3(256), 0, st, a,
-                       static_cast<const cell4<T>*>(cells), static_cast<node4<T>*>(nodes));
+    const dim3 grid(static_cast<unsigned>((a.nseg + 3) / 4));
+    auto* out = static_cast<node4<T>*>(nodes);
+    if (a.ncell > 96 * 96) {
+      hipLaunchKernelGGL(pack_cells_kernel<T>, dim3(nblk(a.ncell)), dim3(256), 0, st, a,
+                         static_cast<cell4<T>*>(cells));
+      hipLaunchKernelGGL((interp1_kernel<T, true>), grid, dim3(256), 0, st, a, static_cast<const cell4<T>*>(cells), out);
+    } else {
+      hipLaunchKernelGGL((interp1_kernel<T, false>), grid, dim3(256), 0, st, a, nullptr, out);
+    }
   } else {
     hipLaunchKernelGGL(interp_kernel<T>, dim3(nblk(a.nslot)), dim3(256), 0, st, a, static_cast<node4<T>*>(nodes));
   }
@@ -1394,7 +1447,7 @@ void launch_valu_rate(int op, float* out, int nblocks, int iters, hipStream_t st
 template <int W>
 static void launch_back_w(const BackArgs& a, hipStream_t st) {
   int64_t nb = (a.ncg + 63) / 64;
-  if (a.zero_mask) nb += (a.ncell + 64 * W - 1) / (64 * W);
+  if (a.zero_mask || a.sums) nb += (a.ncell + 64 * W - 1) / (64 * W);
   const dim3 grid(static_cast<unsigned>(nb));
   if (a.ncomp == 1)
     hipLaunchKernelGGL((rotate_back_kernel<1, W>), grid, dim3(64 * W), 0, st, a);
@@ -1412,7 +1465,7 @@ static void launch_back_w(const BackArgs& a, hipStream_t st) {
 // and 8 at 100 blocks).
 static int back_waves(int64_t blocks, int ncomp) { return blocks >= 1024 ? 4 : blocks > 256 || ncomp > 1 ? 8 : 16; }
 void launch_rotate_back(const BackArgs& a, hipStream_t st) {
-  if (a.ncg == 0 && !a.zero_mask) return;
+  if (a.ncg == 0 && !a.zero_mask && !a.sums) return;
   switch (back_waves((a.ncg + 63) / 64, a.ncomp)) {
     case 4: launch_back_w<4>(a, st); break;
     case 8: launch_back_w<8>(a, st); break;

@@ -117,6 +117,12 @@ struct BackArgs {
   // lattice points), so each gather of a lower angle serves both
   int pair_fold;
   const uint8_t* zero_mask;  // grain mask when the off-grain cells are to be zeroed, or nullptr
+  // partial sums, nparts each, of the free energy, (curl curl_A)^2 (zeros
+  // without curl_A), jx and jy, or nullptr; needs both block counts of the
+  // launch within nparts
+  double* sums;
+  const double* curl_A;
+  int nparts;
 };
 
 constexpr int kBatchCounters = 8;  // tile counters of a batch's sweeps (one per lane shape)

@@ -38,3 +38,39 @@ def test_rotate_back_matches_oracle(side, comps, n_theta):
     assert rel_err(j[:, m], ref["j"][:, m]) <= 1e-10
     assert np.all(dn[:, ~m] == 0.0) and np.all(j[:, ~m] == 0.0)
     g.close()
+
+
+# partial sums in the rotate-back (up to 256 blocks of 64 grain cells and 256
+# of 512 cells of the grid) and in launches of their own beyond either count;
+# nodes straight from the fields (up to 9216 cells) and from packed cells
+@pytest.mark.parametrize("grid,side", [((9, 8), (6, 5)), ((96, 96), (94, 90)), ((97, 96), (94, 90)),
+                                       ((131, 130), (128, 128)), ((132, 132), (128, 129)), ((362, 363), (9, 9))])
+@pytest.mark.parametrize("kappa", [0.0, 2.3])
+def test_partial_sums_match_oracle(grid, side, kappa):
+    """Free energy against the oracle's (1e-10, the bound of the FP64 sweeps),
+    and one Picard step of A, which takes the mean current off, against the
+    A-solve of the same current (1e-12: sums in another order)."""
+    import paper_2205_15000_amd as qs
+    nx, ny = grid
+    mask = np.zeros((ny, nx), dtype=np.uint8)
+    mask[1:1 + side[1], 1:1 + side[0]] = 1
+    sp = dict(nx=nx, ny=ny, h=0.4, shapes=[{"kind": "mask", "mask": mask, "add": True}], n_theta=4, n_poles=2, t=0.5,
+              components=[("s", 1.0)], kappa=kappa, flux_quanta=0.4, gauge="symmetric", charge_sign=-1)
+    print("case grid %s grain %s kappa %g" % (grid, side, kappa), flush=True)
+    rng = np.random.default_rng(11)
+    y, x = np.mgrid[:ny, :nx]
+    d = (1.0 + 0.2 * rng.standard_normal((1, ny, nx)) + 0.3j) * mask
+    a = 0.05 * np.stack([np.sin(0.1 * y), np.cos(0.07 * x)]) * (kappa > 0.0)
+    g = qs.Grain(sp, "fp64")
+    dd, ad = torch.as_tensor(d).cuda(), torch.as_tensor(a).cuda()
+    om = g.sweep(dd, ad)[2]
+    ref = oracle_grain(sp).iterate(d, a)["omega_total"]
+    assert abs(float(om) - ref) <= 1e-10 * abs(ref)
+    if kappa > 0.0:
+        g.reset_bc()
+        want = g.solve_A(g.sweep(dd, 0.0 * ad)[1], B=False)[0].cpu().numpy()
+        g.reset_bc()
+        d1, a1 = dd.clone(), 0.0 * ad
+        g.scf(d1, a1, alpha=1.0, tol=0.0, max_iter=1)
+        assert np.max(np.abs(a1.cpu().numpy() - want)) <= 1e-12 * np.max(np.abs(want))
+    g.close()
