@@ -554,8 +554,9 @@ double* region(qc_grain* g, int r) { return g->part + static_cast<int64_t>(r) * 
 
 // one copy of the block partials (the first n regions) to the host, then wait
 // for the stream
-void fetch_parts(qc_grain* g, hipStream_t st, int n = kRCong) {
-  hcheck(hipMemcpyAsync(g->part_host, g->part, sizeof(double) * n * kParts, hipMemcpyDeviceToHost, st), "D2H");
+void fetch_parts(qc_grain* g, hipStream_t st, int n) {
+  qc::launch_parts_to_host(g->part, n * kParts, g->part_host, st);
+  hcheck(hipGetLastError(), "partials launch");
   hcheck(hipStreamSynchronize(st), "sync");
 }
 
@@ -887,7 +888,7 @@ void do_sweep(qc_grain* g, const double* delta, const double* A, double* delta_n
   hcheck(hipGetLastError(), "rotate-back launch");
   if (!fused_sums(g)) omega_partials(g, A, st);
   if (omega_total) {
-    fetch_parts(g, st);
+    fetch_parts(g, st, kRJx);
     *omega_total = omega_from_parts(g);
   }
 }
@@ -1527,7 +1528,7 @@ qc_status qc_free_energy_lw(qc_grain* g, const double* delta, const double* A_in
     qc::launch_lw_finish(delta, g->grain_cells, g->ncg, g->ncomp, g->ncell, g->n_theta, g->eta, g->wk, g->logt,
                          g->twopi_rz, g->lw_acc, g->omega_cell, omega_density, st);
     omega_partials(g, A_ind, st);
-    fetch_parts(g, st);
+    fetch_parts(g, st, kRJx);
     *omega_total = omega_from_parts(g);
     // restore the store the caller's next sweep expects
     g->bc_cur = saved_cur;
@@ -1610,7 +1611,7 @@ qc_status qc_magnetic_moment(qc_grain* g, const double* j, double* m_out, void* 
     hcheck(hipSetDevice(g->device), "hipSetDevice");
     qc::launch_torque(j, g->grain_cells, g->ncg, g->ncell, g->nx, g->x0, g->y0, g->h, g->cx, g->cy, g->bbuf, st);
     qc::launch_block_sum(g->bbuf, nullptr, g->ncg, region(g, kRJx), kParts, st);
-    fetch_parts(g, st);
+    fetch_parts(g, st, kRJy);
     *m_out = region_sum(g, kRJx) / (2.0 * static_cast<double>(g->ncg));
     return QC_OK;
   });
@@ -1671,7 +1672,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
       do_sweep(g, delta_io, A_io, g->dnew, g->jcur, nullptr, nullptr, st, false);
       if (it < burnin) {
         std::swap(g->jold, g->jcur);
-        fetch_parts(g, st);
+        fetch_parts(g, st, kRJx);
         const double om = omega_from_parts(g);
         const double res[5] = {0.0, 0.0, 0.0, 0.0, om};
         om_old = om;
@@ -1682,7 +1683,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
       do_solve_A(g, g->jcur, g->anew, nullptr, st, fused_sums(g));
       // residuals of Delta and A with their Picard steps fused in
       // (BB: norms and dot products first; the step follows once its size is known)
-      // (the three fields in one launch)
+      // (the fields, and CongAcc's dot products, in one launch)
       {
         qc::DiffNormArgs da[3];
         int nd = 0;
@@ -1691,10 +1692,7 @@ qc_status qc_scf_run(qc_grain* g, double* delta_io, double* A_io, int max_iter, 
         if (have_old) da[nd++] = diff_args(g, g->jcur, g->jold, nullptr, 2 * g->ncell, 1, 0, 1, norm_p, kRDiffJ);
         da[nd++] = diff_args(g, g->anew, A_io, nullptr, 2 * g->ncell, 1, 0, 1, norm_p, kRDiffA, !bb && !cong, alpha,
                              polyak ? g->vel_a : nullptr);
-        qc::launch_diff_norm_n(da, nd, kParts, st);
-      }
-      if (cong && !cg_first) {
-        qc::launch_congacc_dots(cf, region(g, kRCong), kParts, st);
+        qc::launch_diff_norm(da, nd, cong && !cg_first ? &cf : nullptr, region(g, kRCong), kParts, st);
       }
       if (bb) {
         qc::launch_bb_dots(g->dnew, delta_io, g->grain_cells, g->ncg, g->ncomp, g->ncell, 2, 1.0, g->vel_d,
@@ -2030,8 +2028,8 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
         dn.alpha = 1.0;
         dn.vel = nullptr;
         dn.beta = 0.0;
-        qc::launch_diff_norm(dn, kParts, st);
-        fetch_parts(g, st);
+        qc::launch_diff_norm(&dn, 1, nullptr, nullptr, kParts, st);
+        fetch_parts(g, st, kRDiffJ);
         if (rel_from_parts(g, kRDiffD, 2) < tol) {
           ++it;
           break;

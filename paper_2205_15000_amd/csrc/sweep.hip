@@ -1076,6 +1076,15 @@ __global__ void __launch_bounds__(256) block_sum_kernel(BlockSumRow r0, BlockSum
   if (threadIdx.x == 0) r.part[blockIdx.x] = sh[0];
 }
 
+// Block partials to pinned host memory, visible there when the stream has been
+// waited for.  A launch: as a copy call these few KB took some 8 us more (sweep of
+// the 32 x 32 disc 59 -> 51 us, ten iterations on 40 x 40 983 -> 819 us).
+__global__ void __launch_bounds__(256) parts_to_host_kernel(const double* __restrict__ part, int n,
+                                                            double* __restrict__ host) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) host[i] = part[i];
+}
+
 // Luttinger-Ward free energy (Sec. II): the propagator term at one
 // coupling lambda, 2 sum_G den_G Re(conj(Delta_G) Delta_new_G[lambda Delta])
 // with den_G the gap-equation denominator, weighted into acc per grain cell
@@ -1136,14 +1145,53 @@ __global__ void __launch_bounds__(256) scale_kernel(const double* __restrict__ x
   if (i < n) y[i] = s * x[i];
 }
 
+// CongAcc (App. E): dot products m.m, m.d, d.d of component comp of x, with
+// d = xnew - xold and m the component's moving average.
+__device__ __forceinline__ void congacc_dots_block(const CongFields& f, int comp, double (*__restrict__ sm)[256],
+                                                   double* __restrict__ part) {
+  const int nd = 2 * f.ncomp;
+  const bool in_a = comp >= nd;  // components 2 G + (0 re, 1 im) of Delta, then A_x, A_y
+  const int64_t n = in_a ? f.ncell : f.ncg, base = (in_a ? comp - nd : comp / 2) * f.ncell;
+  const int stride = in_a ? 1 : 2, c = in_a ? 0 : comp & 1;
+  const int32_t* idx = in_a ? nullptr : f.grain_cells;
+  const double *xnew = in_a ? f.anew : f.dnew, *xold = in_a ? f.a : f.delta, *m = in_a ? f.ma : f.md;
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
+       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    const int64_t k = (base + (idx ? idx[i] : i)) * stride + c;
+    const double d = xnew[k] - xold[k], mv = m[k];
+    a0 += mv * mv;
+    a1 += mv * d;
+    a2 += d * d;
+  }
+  sm[0][threadIdx.x] = a0;
+  sm[1][threadIdx.x] = a1;
+  sm[2][threadIdx.x] = a2;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w)
+      for (int j = 0; j < 3; ++j) sm[j][threadIdx.x] += sm[j][threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0)
+    for (int j = 0; j < 3; ++j) part[3 * (static_cast<int64_t>(comp) * gridDim.x + blockIdx.x) + j] = sm[j][0];
+}
+
 // Partial p-norms of (new - old) and of old over `n` elements of `stride`
 // doubles each (stride 2: complex modulus).  p = 1, 2, or 0 (max).
 // Elements may be gathered through idx (grain cells) when idx != nullptr,
 // for `nrep` consecutive fields of `field_stride` elements.
-// up to three independent fields per launch, picked by blockIdx.y
-__global__ void __launch_bounds__(256) diff_norm_kernel(DiffNormArgs a0, DiffNormArgs a1, DiffNormArgs a2) {
+// nf (up to three) independent fields per launch, picked by blockIdx.y, and
+// after them the CongAcc dot products of every component
+__global__ void __launch_bounds__(256) diff_norm_kernel(int nf, DiffNormArgs a0, DiffNormArgs a1, DiffNormArgs a2,
+                                                        CongFields f, double* __restrict__ cong_part) {
+  __shared__ double sm[3][256];
+  if (static_cast<int>(blockIdx.y) >= nf) {
+    congacc_dots_block(f, blockIdx.y - nf, sm, cong_part);
+    return;
+  }
   const DiffNormArgs& a = blockIdx.y == 0 ? a0 : (blockIdx.y == 1 ? a1 : a2);
-  __shared__ double s0[256], s1[256];
+  double *const s0 = sm[0], *const s1 = sm[1];
   double acc0 = 0.0, acc1 = 0.0;
   const int64_t total = a.n * a.nrep;
   for (int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; t < total;
@@ -1250,38 +1298,6 @@ __global__ void __launch_bounds__(256) bb_dots_kernel(const double* __restrict__
   }
   if (threadIdx.x == 0)
     for (int c = 0; c < 3; ++c) part[3 * blockIdx.x + c] = sm[c][0];
-}
-
-// CongAcc (App. E): dot products m.m, m.d, d.d of every component of x
-// (blockIdx.y), with d = xnew - xold and m the component's moving average.
-__global__ void __launch_bounds__(256) congacc_dots_kernel(CongFields f, double* __restrict__ part) {
-  __shared__ double sm[3][256];
-  const int comp = blockIdx.y, nd = 2 * f.ncomp;
-  const bool in_a = comp >= nd;  // components 2 G + (0 re, 1 im) of Delta, then A_x, A_y
-  const int64_t n = in_a ? f.ncell : f.ncg, base = (in_a ? comp - nd : comp / 2) * f.ncell;
-  const int stride = in_a ? 1 : 2, c = in_a ? 0 : comp & 1;
-  const int32_t* idx = in_a ? nullptr : f.grain_cells;
-  const double *xnew = in_a ? f.anew : f.dnew, *xold = in_a ? f.a : f.delta, *m = in_a ? f.ma : f.md;
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t k = (base + (idx ? idx[i] : i)) * stride + c;
-    const double d = xnew[k] - xold[k], mv = m[k];
-    a0 += mv * mv;
-    a1 += mv * d;
-    a2 += d * d;
-  }
-  sm[0][threadIdx.x] = a0;
-  sm[1][threadIdx.x] = a1;
-  sm[2][threadIdx.x] = a2;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-      for (int j = 0; j < 3; ++j) sm[j][threadIdx.x] += sm[j][threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0)
-    for (int j = 0; j < 3; ++j) part[3 * (static_cast<int64_t>(comp) * gridDim.x + blockIdx.x) + j] = sm[j][0];
 }
 
 // CongAcc step of every component: m <- w m + (1 - w) d, x += a m, with
@@ -1548,19 +1564,18 @@ void launch_block_sum(const double* x, const int32_t* idx, int64_t n, double* pa
   const BlockSumRow r{x, idx, n, part, 0, 0, 0, 0.0};
   hipLaunchKernelGGL(block_sum_kernel, dim3(nparts), dim3(256), 0, st, r, r);
 }
+void launch_parts_to_host(const double* part, int n, double* host, hipStream_t st) {
+  hipLaunchKernelGGL(parts_to_host_kernel, dim3(nblk(n)), dim3(256), 0, st, part, n, host);
+}
 void launch_block_sum2(const BlockSumRow& r0, const BlockSumRow& r1, int nparts, hipStream_t st) {
   hipLaunchKernelGGL(block_sum_kernel, dim3(nparts, 2), dim3(256), 0, st, r0, r1);
 }
-void launch_diff_norm(const DiffNormArgs& a, int nparts, hipStream_t st) {
-  hipLaunchKernelGGL(diff_norm_kernel, dim3(nparts), dim3(256), 0, st, a, a, a);
-}
-void launch_diff_norm_n(const DiffNormArgs* a, int count, int nparts, hipStream_t st) {
+void launch_diff_norm(const DiffNormArgs* a, int count, const CongFields* f, double* cong_part, int nparts,
+                      hipStream_t st) {
   if (count < 1 || count > 3) return;
-  hipLaunchKernelGGL(diff_norm_kernel, dim3(nparts, count), dim3(256), 0, st, a[0], a[count > 1 ? 1 : 0],
-                     a[count > 2 ? 2 : 0]);
-}
-void launch_congacc_dots(const CongFields& f, double* part, int nparts, hipStream_t st) {
-  hipLaunchKernelGGL(congacc_dots_kernel, dim3(nparts, 2 * f.ncomp + 2), dim3(256), 0, st, f, part);
+  const int rows = count + (f ? 2 * f->ncomp + 2 : 0);
+  hipLaunchKernelGGL(diff_norm_kernel, dim3(nparts, rows), dim3(256), 0, st, count, a[0], a[count > 1 ? 1 : 0],
+                     a[count > 2 ? 2 : 0], f ? *f : CongFields{}, cong_part);
 }
 void launch_congacc_update(const CongFields& f, const CongCoef& cf, hipStream_t st) {
   const int64_t n = f.ncg * f.ncomp + 2 * f.ncell;

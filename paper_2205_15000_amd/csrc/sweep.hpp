@@ -309,12 +309,10 @@ struct BlockSumRow {
   int nx, ny;
   double h;
 };
+void launch_parts_to_host(const double* part, int n, double* host, hipStream_t st);
 // two independent sums in one launch
 void launch_block_sum2(const BlockSumRow& r0, const BlockSumRow& r1, int nparts, hipStream_t st);
 void launch_block_sum(const double* x, const int32_t* idx, int64_t n, double* part, int nparts, hipStream_t st);
-void launch_diff_norm(const DiffNormArgs& a, int nparts, hipStream_t st);
-// 1 to 3 independent fields in one launch (blockIdx.y picks the field)
-void launch_diff_norm_n(const DiffNormArgs* a, int count, int nparts, hipStream_t st);
 // CongAcc (App. E): per-component step sizes and weights of one field
 constexpr int kCongMaxComp = 10;
 struct CongCoef {
@@ -329,8 +327,10 @@ struct CongFields {
   int64_t ncg, ncell;
   int ncomp;
 };
-// partials [2 ncomp + 2][nparts][3] of m.m, m.d, d.d per component
-void launch_congacc_dots(const CongFields& f, double* part, int nparts, hipStream_t st);
+// norms of one to three fields and, with f, the partials [2 ncomp + 2][nparts][3]
+// of m.m, m.d, d.d per component, in one launch
+void launch_diff_norm(const DiffNormArgs* a, int count, const CongFields* f, double* cong_part, int nparts,
+                      hipStream_t st);
 void launch_congacc_update(const CongFields& f, const CongCoef& cf, hipStream_t st);
 // partials [nparts][3] of dp.dp, dp.(d - dp), (d - dp).(d - dp), d = scale (xnew - xold); dprev <- d
 void launch_bb_dots(const double* xnew, const double* xold, const int32_t* idx, int64_t n, int nrep,
