@@ -108,62 +108,20 @@ __device__ __forceinline__ cpx<T> csqrt(cpx<T> w) {
   return mk(pos ? t : dabs(yq), pos ? yq : dsign(t, w.y));
 }
 
-// Per-node constants of one implicit-midpoint step (App. C) for the half-step
-// order parameter dm and step length hs: c2 = (i hs/4) conj(dm) and 4 c2.
-template <typename T>
-struct StepNode {
-  T c2x, c2y, c4x, c4y, hs;
-};
-template <typename T>
-__device__ __forceinline__ StepNode<T> step_node(T dmx, T dmy, T hs) {
-  StepNode<T> s;
-  const T hq = T(0.25) * hs;
-  s.c2x = hq * dmy;
-  s.c2y = hq * dmx;
-  s.c4x = T(4) * s.c2x;
-  s.c4y = T(4) * s.c2y;
-  s.hs = hs;
-  return s;
-}
-
-// One implicit-midpoint step of d gamma/ds = i[D* g^2 + 2 z g + D] (App. C,
-// v_F = 1) with z = (zx, zy): g' = 2 c0 / (-c1 + sqrt(c1^2 - 4 c2 c0)) with
-// c1 = 2 c2 g + i h z - 1 and c0 = (c1 - c2 g + 2) g - 4 conj(c2); the root is
-// flipped if it points away from -c1, so that g' -> g as h -> 0.
-template <typename T>
-__device__ __forceinline__ cpx<T> riccati_step(cpx<T> g, const StepNode<T>& s, T zx, T zy) {
-  const T cgx = s.c2x * g.x - s.c2y * g.y;  // c2 g
-  const T cgy = s.c2x * g.y + s.c2y * g.x;
-  const T kx = -s.hs * zy - T(1);            // i h z - 1
-  const T ky = s.hs * zx;
-  const T c1x = T(2) * cgx + kx, c1y = T(2) * cgy + ky;
-  const T px = cgx + kx + T(2), py = cgy + ky;  // c1 - c2 g + 2
-  const T c0x = px * g.x - py * g.y - s.c4x;
-  const T c0y = px * g.y + py * g.x + s.c4y;
-  const T dx = c1x * c1x - c1y * c1y - (s.c4x * c0x - s.c4y * c0y);
-  const T dy = T(2) * c1x * c1y - (s.c4x * c0y + s.c4y * c0x);
-  cpx<T> rt = csqrt(mk(dx, dy));
-  const bool flip = rt.x * c1x + rt.y * c1y > T(0);  // Re(rt conj(-c1)) < 0
-  rt = mk(flip ? -rt.x : rt.x, flip ? -rt.y : rt.y);
-  const T ex = rt.x - c1x, ey = rt.y - c1y;
-  const T rn = T(2) * drcp(ex * ex + ey * ey);
-  return mk((c0x * ex + c0y * ey) * rn, (c0y * ex - c0x * ey) * rn);
-}
-
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// The same implicit-midpoint step as riccati_step, solved for the midpoint
-// value w = (g + g')/2 instead of g'.  With D the half-step order parameter,
-// k = i h z - 1 and the step equation g' - g = i h [D* w^2 + 2 z w + D]:
+// One implicit-midpoint step of d gamma/ds = i[D* g^2 + 2 z g + D] (App. C,
+// v_F = 1), solved for the midpoint value w = (g + g')/2 instead of g'.  With
+// D the half-step order parameter, k = i h z - 1 and the step equation
+// g' - g = i h [D* w^2 + 2 z w + D]:
 //   (i h D*) w^2 + 2 k w + U = 0,   U = 2 g + i h D.
 // With K = k/2 and c2 = (i h/4) conj(D) (so i h D* = 4 c2 and i h D =
 // -4 conj(c2)) the stable root is w = -U / (2 e), e = K + s sqrt(disc),
 //   disc = K^2 - c2 U,
 // the sign s taken so that s sqrt(disc) points along K (|e| is then the
 // larger of the two choices and w -> g as h -> 0).  So g' = 2 w - g =
-// -U conj(e) / |e|^2 - g.  (disc is a quarter of c1^2 - 4 c2 c0 of
-// riccati_step with the terms in g^2 cancelled.)
+// -U conj(e) / |e|^2 - g.
 // The roots of disc = (dx, dy) are +-(a, b) r with v = |disc| + |dx|,
 // r = 1/sqrt(2 v) and (a, b) = (v, dy) for dx >= 0, (dy, v) otherwise
 // ((a + i b)^2 r^2 = disc in both cases); since r > 0 the sign of
