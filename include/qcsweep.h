@@ -237,8 +237,8 @@ qc_status qc_sweep(qc_grain* grain, const double* delta, const double* A_ind,
 /* qc_sweep without allocation, for callers that cannot allocate device
  * memory (code under stream or graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same map, arguments and results as
- * qc_sweep; the per-call work arrays (slot values, the gamma spill between
- * the two marches, per-node sums, packed interpolation cells) live in one
+ * qc_sweep; the per-call work arrays (slot values, the spill between the
+ * halves of the marches, per-node sums, packed interpolation cells) live in one
  * 64 MiB array that the library holds on each device it runs on until the
  * process ends, instead of grain-owned allocations.  Calls on one device
  * share that array, so calls that overlap on one GPU race; nothing in it
@@ -407,7 +407,11 @@ qc_status qc_grain_get_accel_stats(const qc_grain* grain, int64_t* bisected, int
  * from the one of qc_sweep.  With angle pairs on and a set of energies
  * symmetric about zero (to 1e-12 of the largest |e|), the sweeps march half
  * the angles (see qc_grain_set_pairing); the energies may come in any
- * order, and ldos_out keeps the caller's order.
+ * order, and ldos_out keeps the caller's order.  The work memory (end values
+ * of all energies, marches and densities of a block of them) stays with the
+ * grain after the call, up to a sixteenth of the device's memory over all
+ * grains; it is given back when the grain is destroyed or when another
+ * allocation of the library on the device fails without it.
  *   energies host double [n_e]
  *   ldos_out device double [n_e][ny][nx] (0 off-grain) */
 qc_status qc_ldos(qc_grain* grain, const double* delta, const double* A_ind,
@@ -465,15 +469,16 @@ qc_status qc_sweep_adjoint(qc_grain* grain, const double* delta, const double* A
  * replay, one per boundary-store parity).  All grains must share device and
  * precision; each appears once; the batch keeps its own Delta and A per
  * grain and uses the grains' buffers (do not sweep them separately while
- * the batch is in use).  The gamma values between a tile's two marches live
- * in one scratch array with a slice per resident wave (reused tile after
- * tile), sized for the largest tile of the batch: the spill memory depends
+ * the batch is in use).  The values between the halves of a tile's marches
+ * live in one scratch array with a slice per resident block of two waves
+ * (reused tile after tile), sized for the largest tile of the batch: the spill memory depends
  * on the longest trajectory and the pole count, not on the number of grains. */
 typedef struct qc_batch qc_batch;
 qc_status qc_batch_create(qc_grain* const* grains, int n, qc_batch** out);
 void qc_batch_destroy(qc_batch* batch);
 /* trajectory steps of one iteration over all grains; energies per lane
- * (0: each grain its own automatic choice, the default); number of tiles.
+ * (0: automatic, the default: one common number chosen by the batch's size,
+ * or each grain's own in a large batch); number of tiles.
  * Any output pointer may be NULL. */
 qc_status qc_batch_get_info(const qc_batch* batch, int64_t* steps_per_iteration, int* energies_per_lane,
                             int* n_tiles);
@@ -502,8 +507,8 @@ qc_status qc_batch_autotune(qc_batch* batch, int iters_per_trial, int* best_epl,
  * the grain.  delta, A_ind, g_out are device pointers as for qc_sweep.  The
  * start values are the ones the next qc_sweep would use (the boundary store
  * left by the latest sweep, bulk roots before the first); the store is not
- * changed.  Works in pole blocks with temporary device buffers (allocates
- * and frees; QC_ERR_OOM when they do not fit).  Synchronises the stream. */
+ * changed.  Works in pole blocks with work memory that the grain keeps (see
+ * qc_ldos; QC_ERR_OOM when it does not fit).  Synchronises the stream. */
 qc_status qc_green_average(qc_grain* grain, const double* delta, const double* A_ind, double* g_out, void* stream);
 
 /* Boundary-value store of qc_sweep (resume without burn-in, App. B).
@@ -514,11 +519,11 @@ qc_status qc_set_state(qc_grain* grain, const void* state, size_t bytes, void* s
 
 /* Memory mode of qc_sweep_adjoint.  every = C > 0 (default 32):
  * checkpoints every C slots of each trajectory (32 B per C nodes and pole)
- * plus a per-thread scratch of 2 C slots; each block is recomputed from its
- * checkpoint (three extra marches per node) with the same steps on the same
- * inputs.  every = 0: gamma~ and the node-local gamma~ adjoint are stored
- * at every (node, pole) instead (32 B in FP64).  Both modes give the same
- * gradients to rounding. */
+ * plus a per-thread scratch of C slots; each block is recomputed from its
+ * checkpoint (one extra march per node and direction) with the same steps on
+ * the same inputs.  every = 0: gamma and gamma~ are kept at every (node,
+ * pole) instead (32 B in FP64).  Both modes give the same gradients to
+ * rounding. */
 qc_status qc_grain_set_adjoint_checkpoint(qc_grain* grain, int every);
 
 /* Launch shape of the sweep kernel: energies handled by each lane (1, 2, 3,
