@@ -959,21 +959,26 @@ __global__ void __launch_bounds__(256) batch_set_kernel(const double2* __restric
 // Rotate-back and angle sums of the per-node, per-energy values of sweep mode
 // 1 (LDOS) or 3 (CPLX: -i pi times the average of a complex value).  A row of
 // a node holds M = n_e (CPLX: 2 n_e) reals; a thread takes V consecutive ones
-// (16 B loads where the row length allows) of one cell, tpc threads a cell,
-// and forms the corner weights once for all of them, from the 16 B corner
-// records that the sweep's rotate-back reads.  The sums meet in LDS, so that
-// a lower angle's sum reaches its partner energy and the output, energy by
-// energy, is written along the cells.
-// Bound by the gathers of the rows through L2.  With one thread per (cell,
-// energy), stored indices and weights (48 B per angle and thread), and the
-// partner energy gathered as well, the kernel waited on those loads: 926 us
-// for 43264 cells x 64 angle pairs x 64 energies, 247 us now.
+// (16 B loads where the row length allows) of one cell, tpc threads a cell.
+// The corner weights of up to sixteen angles are formed at a time, each by one
+// thread, from the 16 B corner records that the sweep's rotate-back reads, and
+// shared through LDS.  The sums meet in LDS too, so that a lower angle's sum
+// reaches its partner energy and the output, energy by energy, is written
+// along the cells.
+// Bound by VALU (a conversion and an FP64 fma per corner and energy) and the
+// gathers of the rows through L2.  With one thread per (cell, energy), stored
+// indices and weights (48 B per angle and thread), and the partner energy
+// gathered as well, the kernel waited on those loads: 926 us for 43264 cells x
+// 64 angle pairs x 64 energies; 247 us with a thread's own weights, some 40 of
+// its 100 instructions an angle, and 218 us shared (185 and 149 us for 22500
+// cells x 128 angles).
 template <typename T, int V>
 struct __attribute__((aligned(V * sizeof(T) < 16 ? V * sizeof(T) : 16))) vecn {
   T v[V];
 };
 template <typename T, int V, bool CPLX>
-__global__ void __launch_bounds__(256) ldos_back_kernel(LdosBackArgs a, const T* __restrict__ ebuf, int tpc, int cpb) {
+__global__ void __launch_bounds__(256) ldos_back_kernel(LdosBackArgs a, const T* __restrict__ ebuf, int tpc, int cpb,
+                                                        int kpb) {
   extern __shared__ double sums[];
   const int M = (CPLX ? 2 : 1) * a.n_e;
   const int lc = static_cast<int>(threadIdx.x) / tpc, te = static_cast<int>(threadIdx.x) - lc * tpc;
@@ -983,32 +988,53 @@ __global__ void __launch_bounds__(256) ldos_back_kernel(LdosBackArgs a, const T*
   const int width = tpc * V, pitch = width + 1;
   double acc[V], accp[V];
   for (int i = 0; i < V; ++i) acc[i] = accp[i] = 0.0;
-  if (lc < cpb && c < a.ncg && m0 < M) {
-    const int cell = a.grain_cells[c];
-    const double rx = rn_cell_offset(a.x0, static_cast<double>(cell % a.nx), a.h, a.cx);
-    const double ry = rn_cell_offset(a.y0, static_cast<double>(cell / a.nx), a.h, a.cy);
-    // with fold_k0 each lower angle's corners serve its upper angle too, at
-    // the partner energy (N of the reversed direction at e is N at -e)
-    const int kend = fold ? a.fold_k0 : a.n_theta;
-    int4 ixn = a.rb4[c];
-    for (int k = 0; k < kend; ++k) {
-      const int4 ix = ixn;
-      if (k + 1 < kend) ixn = a.rb4[static_cast<int64_t>(k + 1) * a.ncg + c];
+  // corner records of kpb angles x cpb cells, one thread each, read by the
+  // threads of the cell
+  double2* const w01 = reinterpret_cast<double2*>(sums);
+  double2* const w23 = w01 + kpb * cpb;
+  int4* const rows = reinterpret_cast<int4*>(w23 + kpb * cpb);
+  const bool live = lc < cpb && c < a.ncg && m0 < M;
+  // with fold_k0 each lower angle's corners serve its upper angle too, at
+  // the partner energy (N of the reversed direction at e is N at -e)
+  const int kend = fold ? a.fold_k0 : a.n_theta;
+  for (int k0 = 0; k0 < kend; k0 += kpb) {
+    const int nk = min(kpb, kend - k0);
+    if (k0 > 0) __syncthreads();  // (the records before these are read)
+    for (int t = threadIdx.x; t < nk * cpb; t += 256) {
+      const int kk = t / cpb, k = k0 + kk;
+      const int64_t cc = c0 + t - kk * cpb;
+      if (cc >= a.ncg) continue;
+      const int cell = a.grain_cells[cc];
+      const double rx = rn_cell_offset(a.x0, static_cast<double>(cell % a.nx), a.h, a.cx);
+      const double ry = rn_cell_offset(a.y0, static_cast<double>(cell / a.nx), a.h, a.cy);
       double w[4];
       int sl[4];
-      const double rt = back_weights(ix, a.cosk[k], a.sink[k], rx, ry, a.h, a.half, w, sl);
+      const double rt = back_weights(a.rb4[static_cast<int64_t>(k) * a.ncg + cc], a.cosk[k], a.sink[k], rx, ry, a.h,
+                                     a.half, w, sl);
+      w01[t] = make_double2(w[0] * rt, w[1] * rt);
+      w23[t] = make_double2(w[2] * rt, w[3] * rt);
+      rows[t] = make_int4(sl[0], sl[1], sl[2], sl[3]);
+    }
+    __syncthreads();
+    if (!live) continue;
+    for (int kk = 0; kk < nk; ++kk) {
+      const double2 wa = w01[kk * cpb + lc], wb = w23[kk * cpb + lc];
+      const int4 r = rows[kk * cpb + lc];
+      const double w[4] = {wa.x, wa.y, wb.x, wb.y};
+      const int sl[4] = {r.x, r.y, r.z, r.w};
       vecn<T, V> x[4];
       for (int q = 0; q < 4; ++q)
         x[q] = *reinterpret_cast<const vecn<T, V>*>(ebuf + static_cast<int64_t>(sl[q]) * M + m0);
-      const double wk = a.wk[k], wp = fold ? a.wk[k + a.fold_k0] : 0.0;
+      const double wk = a.wk[k0 + kk], wp = fold ? a.wk[k0 + kk + a.fold_k0] : 0.0;
       for (int i = 0; i < V; ++i) {
         double v = 0.0;
-        for (int q = 0; q < 4; ++q) v += static_cast<double>(x[q].v[i]) * (w[q] * rt);
+        for (int q = 0; q < 4; ++q) v += static_cast<double>(x[q].v[i]) * w[q];
         acc[i] += wk * v;
         if (fold) accp[i] += wp * v;
       }
     }
   }
+  __syncthreads();  // (the sums take the records' place)
   if (lc < cpb)
     for (int i = 0; i < V; ++i) {
       sums[lc * pitch + te * V + i] = acc[i];
@@ -1525,8 +1551,12 @@ static void launch_back_v(const LdosBackArgs& a, const void* ebuf, hipStream_t s
   const int M = (CPLX ? 2 : 1) * a.n_e;
   const int tpc = std::min(M / V, 256), cpb = 256 / tpc;
   const dim3 grid(static_cast<unsigned>((a.ncg + cpb - 1) / cpb), static_cast<unsigned>((M / V + tpc - 1) / tpc));
-  const size_t lds = sizeof(double) * cpb * (tpc * V + 1) * (a.fold_k0 > 0 ? 2 : 1);
-  hipLaunchKernelGGL((ldos_back_kernel<T, V, CPLX>), grid, dim3(256), lds, st, a, static_cast<const T*>(ebuf), tpc, cpb);
+  // records of sixteen angles at a time, or as many as leave up to 512 of them
+  const int kpb = std::min(std::max(512 / cpb, 1), 16);
+  const size_t lds = std::max(sizeof(double) * cpb * (tpc * V + 1) * (a.fold_k0 > 0 ? 2 : 1),
+                              static_cast<size_t>(48) * kpb * cpb);
+  hipLaunchKernelGGL((ldos_back_kernel<T, V, CPLX>), grid, dim3(256), lds, st, a, static_cast<const T*>(ebuf), tpc, cpb,
+                     kpb);
 }
 // the widest loads (up to 16 B) that the row length allows
 template <typename T, bool CPLX>
