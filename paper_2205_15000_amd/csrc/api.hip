@@ -756,6 +756,22 @@ qc::SweepArgs sweep_args(qc_grain* g, int n_e, int n_e_tot, int e_off, const dou
   return a;
 }
 
+// Lane shape of a mixed LDOS output sweep (mode 1): two energies per lane where
+// that takes at most 64 lanes, also with lanes left idle.  Its rows of densities and
+// spilled values bound it rather than the lanes, and two per lane keep more
+// waves in flight than four, whose real energies cost registers.  A whole
+// converged LDOS of 150 x 150, mixed, with 1, 2, 3, 4 per lane: 1868, 1822,
+// 1974, 2084 us (24 energies), 2872, 2697, 2739, 2921 (48), 3368, 3113, 3584,
+// 3434 (64).  FP64 keeps the choice by the lanes (100 x 100: 2774, 2396, 2213,
+// 2427 us for 48 energies).
+void output_shape(const qc_grain* g, qc::SweepArgs& a) {
+  const int G2 = lanes_for(a.n_e, 2);
+  if (g->precision != QC_MIXED || a.epl == g->epl_override || a.n_e < 2 || G2 > 64) return;
+  a.epl = 2;
+  a.G = G2;
+  a.log2g = ilog2(G2);
+}
+
 // Segments of a Matsubara sweep that take the wide lane shape (2G lanes,
 // EPL/2 energies per lane; see SweepArgs::nlong).  A launch that leaves wave
 // slots empty takes it for all of them: its time is the chain of one wave's
@@ -1914,6 +1930,7 @@ qc_status qc_ldos(qc_grain* g, const double* delta, const double* A_ind, const d
       b.bc_gt_next = nullptr;
       b.gbuf = lg;
       b.ebuf = le;
+      output_shape(g, a);
       launch_sweep_timed(g, 1, a, b, st);
       qc::LdosBackArgs la = ldos_back_args(g, ne, e0, ldos_out);
       la.e_map = dmap;
@@ -2002,7 +2019,8 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
         b.bc_gt_next = bcl[1 - cur][1];
         b.gbuf = lg;
         b.ebuf = le;
-        launch_sweep_timed(g, 1, a, b, st);
+        output_shape(g, a);
+      launch_sweep_timed(g, 1, a, b, st);
         cur = 1 - cur;
         if (it > 0)
           hcheck(hipMemcpyAsync(prev, out, sizeof(double) * ne * g->ncell, hipMemcpyDeviceToDevice, st), "copy");
