@@ -11,6 +11,7 @@
 // Everything here is built once per grain on the host and uploaded.
 #pragma once
 
+#include <algorithm>
 #include <complex>
 #include <cstdint>
 #include <string>
@@ -78,7 +79,7 @@ struct Plan {
   std::vector<int32_t> rb_idx;         // global slot index
   std::vector<double> rb_w;
   // compact form [n_theta][ncg][4]: slot of each corner or -1; a cell that
-  // takes its nearest node instead holds {slot, -2, -2, -2}
+  // takes its nearest node instead holds {slot, -2, -2, -2} (see record_node)
   std::vector<int32_t> rb4;
 
   // ---- specular boundary taps: [seg][4]
@@ -103,6 +104,14 @@ struct Plan {
 
   int64_t steps_per_sweep() const;
 };
+
+// The slot that the corners of a record of rb4 read, with weight 0, where they
+// are no nodes themselves: a node of the same record, which every record has.
+// Any other slot may be one that no sweep writes (the one slot of a segment
+// without nodes, at slot 0 of many grains), and 0 x NaN is NaN.
+constexpr int32_t record_node(int32_t a, int32_t b, int32_t c, int32_t d) {
+  return std::max(std::max(a, b), std::max(c, d));
+}
 
 // Builds every table; throws std::runtime_error with a message on bad input.
 void build_plan(Plan& p);

@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "kernels.hpp"
+#include "plan.hpp"
 #include "sweep.hpp"
 
 namespace qc {
@@ -716,8 +717,9 @@ __device__ __forceinline__ double curl_at(const double* __restrict__ A, int64_t 
 constexpr int kBackFields = 12;  // 2 x (up to 4 components) + jx, jy, I, <|Delta|^2>
 
 // Bilinear weights and slots of a cell's corner record ix on one angle's
-// lattice; corners that are not nodes read slot 0 with weight 0, so the four
-// gathers issue together.  Returns the factor that renormalises the weights.
+// lattice; corners that are not nodes read one of the record's that is, with
+// weight 0, so the four gathers issue together and only nodes are read.
+// Returns the factor that renormalises the weights.
 __device__ __forceinline__ double back_weights(int4 ix, double epx, double epy, double rx, double ry, double h,
                                                double half, double w[4], int sl[4]) {
   // lattice coordinates (line u, node v) of the cell centre
@@ -736,11 +738,12 @@ __device__ __forceinline__ double back_weights(int4 ix, double epx, double epy, 
     w[0] = 1.0;
     w[1] = w[2] = w[3] = 0.0;
   }
+  const int any = record_node(ix.x, ix.y, ix.z, ix.w);
   double tot = 0.0;
   for (int q = 0; q < 4; ++q) {
     if (sl[q] < 0) {
       w[q] = 0.0;
-      sl[q] = 0;
+      sl[q] = any;
     }
     tot += w[q];
   }
