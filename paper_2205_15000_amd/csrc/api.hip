@@ -57,17 +57,10 @@ qc_status guarded(F&& f) {
 
 constexpr double kPi = 3.14159265358979323846;
 
-template <typename V>
-void* upload(const std::vector<V>& v) {
-  void* p = nullptr;
-  if (v.empty()) return nullptr;
-  hcheck(hipMalloc(&p, v.size() * sizeof(V)), "hipMalloc");
-  hcheck(hipMemcpy(p, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice), "hipMemcpy");
-  return p;
-}
-
 bool release_idle_workspaces();
 
+// every device allocation of the library: where it fails, the idle work
+// memory on the device is given back and it is tried once more
 void* dalloc(size_t bytes) {
   void* p = nullptr;
   if (bytes == 0) return nullptr;
@@ -76,7 +69,18 @@ void* dalloc(size_t bytes) {
     (void)hipGetLastError();
     e = hipMalloc(&p, bytes);
   }
+  if (e != hipSuccess) (void)hipGetLastError();  // (reported by the exception, not by a later launch's check)
   hcheck(e, "hipMalloc");
+  return p;
+}
+
+template <typename V>
+void* upload(const std::vector<V>& v) {
+  void* p = dalloc(v.size() * sizeof(V));
+  if (!p) return nullptr;
+  const hipError_t e = hipMemcpy(p, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice);
+  if (e != hipSuccess) (void)hipFree(p);
+  hcheck(e, "hipMemcpy");
   return p;
 }
 

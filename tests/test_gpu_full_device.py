@@ -1,0 +1,52 @@
+"""Calls on a device whose memory is nearly taken up by others."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2205_15000_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+def _fill(leave):
+    """Takes the device's memory until about `leave` bytes are free."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(8):
+        free = torch.cuda.mem_get_info()[0]
+        if free <= leave + 64 * MIB:
+            break
+        held.append(torch.empty(free - leave, dtype=torch.uint8, device="cuda"))
+    print("free: %d MiB" % (torch.cuda.mem_get_info()[0] // MIB), flush=True)
+    return held
+
+
+def test_grain_tables_take_the_place_of_idle_work_memory():
+    """The LDOS work memory of an idle grain (about 3 GB) gives way to the
+    tables of a new grain (over 1 GB) where about 300 MiB are free."""
+    import paper_2205_15000_amd as qs
+    sp = wl.spec("d_disc_200")
+    d = torch.as_tensor(wl.initial_delta("d_disc_200", sp)).cuda()
+    a = torch.as_tensor(wl.initial_A("d_disc_200", sp)).cuda()
+    g = qs.Grain(sp, "fp64")
+    g.set_pairing(False)
+    en = np.linspace(0.01, 0.4, 64)
+    before = torch.cuda.mem_get_info()[0]
+    out = g.ldos(d, a, en, 0.03, 1)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] > 2048 * MIB
+    big = wl.spec("d110_square_400")
+    full = _fill(300 * MIB)
+    try:
+        h = qs.Grain(big, "fp64")
+        assert h.mask().sum() == h.info["n_grain_cells"]
+        h.close()
+    finally:
+        del full
+        torch.cuda.empty_cache()
+    # the first grain maps its work memory again
+    assert torch.equal(g.ldos(d, a, en, 0.03, 1), out)
+    g.close()
