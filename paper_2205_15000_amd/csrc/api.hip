@@ -476,18 +476,22 @@ bool release_idle_workspaces() {
   return any;
 }
 
+// (Calls on one grain are not meant to overlap, but one that does while the
+// grain's block is in use gets a block of its own for its duration.)
 class Lease {
  public:
   explicit Lease(qc_grain* g) : g_(g) {
     std::lock_guard<std::mutex> lock(g_ws_mu);
-    g_->ws_busy = true;
+    kept_ = !g_->ws_busy;
+    if (kept_) g_->ws_busy = true;
   }
   Lease(const Lease&) = delete;
   Lease& operator=(const Lease&) = delete;
   // bytes already held, which the caller may count as free memory
-  size_t held() const { return g_->ws_bytes; }
-  // the block, at least `bytes` long
+  size_t held() const { return kept_ ? g_->ws_bytes : 0; }
+  // the block, at least `bytes` long; once per lease
   char* get(size_t bytes) {
+    if (!kept_) return static_cast<char*>(own_ = dalloc(bytes));
     if (g_->ws_bytes < bytes) {
       {
         std::lock_guard<std::mutex> lock(g_ws_mu);
@@ -504,17 +508,23 @@ class Lease {
   // the call's work on the block has ended (its stream was waited for)
   void done() { done_ = true; }
   ~Lease() {
+    // (a call that failed may have left work in flight: hipFree waits for it)
+    if (!kept_) {
+      if (own_) (void)hipFree(own_);
+      return;
+    }
     std::lock_guard<std::mutex> lock(g_ws_mu);
     g_->ws_busy = false;
     size_t kept = 0;
     for (const qc_grain* o : g_ws_owners)
       if (o->device == g_->device) kept += o->ws_bytes;
-    // (a call that failed may have left work in flight: hipFree waits for it)
     if (!done_ || kept > g_->device_bytes / 16) drop_workspace(g_);
   }
 
  private:
   qc_grain* g_;
+  bool kept_ = false;  // the lease is on the grain's block
+  void* own_ = nullptr;
   bool done_ = false;
 };
 
