@@ -548,12 +548,13 @@ qc_status qc_grain_get_lanes(const qc_grain* grain, int* energies_per_lane, int*
  * than frac x the longest (at most a 16th of all, a 64th at two energies
  * per lane) then march with twice the lanes and half the energies per lane
  * (rounded up to whole waves), and all of them do in a launch that leaves
- * wave slots empty.  frac in [0, 1]; 0 turns the split
- * off; the default is 0.8.  Results are identical up to the order
- * of the FP64 pole sums.  Errors: QC_ERR_INVALID for frac outside [0, 1]. */
+ * wave slots empty unless the lane shape was forced (qc_grain_set_lanes).
+ * frac in [0, 1]; 0 turns the split off; the default is 0.8.  Results are
+ * identical up to the order of the FP64 pole sums.  Errors: QC_ERR_INVALID for frac outside [0, 1]. */
 qc_status qc_grain_set_split(qc_grain* grain, double frac);
 /* The fraction set and the number of segments the next SCF sweep launches
- * with the wide shape (0 when the split does not apply); either pointer may
+ * with the wide shape (0 when the split does not apply: among others to an
+ * odd number of energies per lane in qc_grain_get_lanes); either pointer may
  * be NULL. */
 qc_status qc_grain_get_split(qc_grain* grain, double* frac, int64_t* n_wide);
 

@@ -586,7 +586,9 @@ class Grain:
         _check(lib.qc_grain_set_lanes(self._g, int(energies_per_lane)))
 
     def lanes(self):
-        """(energies per lane, lanes per segment) of the next SCF sweep."""
+        """(energies per lane, lanes per segment) of the grain's SCF sweeps: a
+        shape set with set_lanes as it runs, the automatic one before a launch
+        that leaves wave slots empty narrows it."""
         e = ctypes.c_int(0)
         G = ctypes.c_int(0)
         _check(lib.qc_grain_get_lanes(self._g, ctypes.byref(e), ctypes.byref(G)))
@@ -594,8 +596,9 @@ class Grain:
 
     def set_split(self, frac):
         """Split launch shape of the SCF sweep: segments longer than frac x
-        the longest march with twice the lanes when the launch is short
-        (0 turns it off; default 0.8)."""
+        the longest (all of them where wave slots stay empty, unless the lanes
+        were set) march with twice the lanes when the launch is short (0 turns
+        it off; default 0.8)."""
         _check(lib.qc_grain_set_split(self._g, float(frac)))
 
     def split(self):

@@ -797,20 +797,23 @@ void output_shape(const qc_grain* g, qc::SweepArgs& a) {
 // four per lane and more (400 x 400 square, mixed: 978 us without, 963 with a
 // 16th, 1018 with a sixth of them wide), a 64th at two per lane, since one
 // per lane costs more per energy (FP64: 2022 us without, 2026 with a 64th,
-// 2068 with an eighth).
+// 2068 with an eighth).  A shape that the caller forced runs as it is for all
+// but these longest ones, also where slots stay empty.
 int64_t split_count(qc_grain* g, const qc::SweepArgs& a) {
   if (!(g->split_frac > 0.0) || a.epl % 2 != 0 || 2 * a.G > 64 || a.nseg == 0) return 0;
   const std::vector<int32_t>& len = a.order == g->order_pair && g->order_pair ? g->len_order_pair : g->len_order;
   if (static_cast<int64_t>(len.size()) != a.nseg) return 0;
   const int64_t slots = wave_slots(g, a.epl), waves = sweep_waves(a.nseg, a.G);
   if (slots <= 0 || waves >= 6 * slots) return 0;
-  if (waves < slots) return a.nseg;
+  const bool forced = a.epl == g->epl_override;
+  if (waves < slots && !forced) return a.nseg;
   const double cut = g->split_frac * len[0];
   int64_t k = 0;
   while (k < a.nseg && len[k] > cut) ++k;
   k = std::min(k, std::max<int64_t>(a.nseg / (a.epl >= 4 ? 16 : 64), 1));
   const int64_t per = 64 / (2 * a.G);
   k = (k + per - 1) / per * per;
+  if (forced && k >= a.nseg) return 0;
   return std::min(k, a.nseg);
 }
 
