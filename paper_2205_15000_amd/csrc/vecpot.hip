@@ -567,20 +567,26 @@ static dim3 fft_cols_block(FftLen ly, int lc) {
   return dim3(static_cast<unsigned>(std::min(std::max(((ly.n() << lc) / 4 + 63) / 64 * 64, 64), 1024)));
 }
 static size_t fft_lds(int elems, int tw) { return sizeof(double2) * static_cast<size_t>(elems + tw); }
-// above 64 KB of LDS (lengths beyond 2048) a kernel has to ask for it
+// A kernel has to ask for more than 64 KB of LDS, dynamic and static together
+// (the rows forward hold their two means beside the rows): rows from length
+// 2048 on, columns beyond it.  The limit belongs to the function, not to the
+// grain, so every grain that needs one asks for the largest that any length
+// needs (4096: one sequence and its twiddles), and none lowers another's.
+constexpr size_t kFftLdsMax = sizeof(double2) * 2 * 4096;
 hipError_t vecpot_prepare(FftLen lx, FftLen ly) {
   const int px = lx.n(), py = ly.n();
   hipError_t e = hipSuccess;
-  auto ask = [&](const void* f, size_t b) {
-    if (e == hipSuccess && b > 65536)
-      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(b));
+  auto ask = [&](const void* f, size_t dynamic, size_t fixed) {
+    if (dynamic > kFftLdsMax) e = hipErrorInvalidValue;
+    if (e == hipSuccess && dynamic + fixed > 65536)
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kFftLdsMax));
   };
   const size_t rows = fft_lds(fft_rpb(lx) * px, px), cols = fft_lds(py << fft_lc(ly, lx), py);
-  ask(reinterpret_cast<const void*>(vecpot_rows_kernel), rows);
-  ask(reinterpret_cast<const void*>(vecpot_rows_back_kernel), rows);
-  ask(reinterpret_cast<const void*>(vecpot_kernel_rows_kernel), fft_lds(px, px));
-  ask(reinterpret_cast<const void*>(vecpot_cols_kernel<true>), cols);
-  ask(reinterpret_cast<const void*>(vecpot_cols_kernel<false>), cols);
+  ask(reinterpret_cast<const void*>(vecpot_rows_kernel), rows, 2 * sizeof(double));
+  ask(reinterpret_cast<const void*>(vecpot_rows_back_kernel), rows, 0);
+  ask(reinterpret_cast<const void*>(vecpot_kernel_rows_kernel), fft_lds(px, px), 0);
+  ask(reinterpret_cast<const void*>(vecpot_cols_kernel<true>), cols, 0);
+  ask(reinterpret_cast<const void*>(vecpot_cols_kernel<false>), cols, 0);
   return e;
 }
 
