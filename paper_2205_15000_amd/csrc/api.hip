@@ -2603,7 +2603,7 @@ struct qc_batch {
   std::vector<double*> delta, A;   // per-grain fields owned by the batch
   int epl = 0;  // energies per lane of every grain; 0: each grain's automatic choice
   int nblocks = 0;
-  qc::BatchGrainDev* d_args = nullptr;  // [n] for the current launch
+  qc::BatchGrainDev* d_args = nullptr;  // [n], of eager iterations
   int2* d_tiles = nullptr;
   // spill of the persistent sweep: wave_elems records per resident block
   // (a wave pair), sized for the largest tile of any grain
@@ -2620,8 +2620,12 @@ struct qc_batch {
   std::vector<char> paired;  // the grains' pairing that the tiles were built for
   int* d_counter = nullptr;  // one tile counter per group
   hipStream_t own = nullptr;
+  // a captured graph of two iterations, argument blocks of its own ([2][n],
+  // one for each store parity), and what it was captured with: bc_cur of every
+  // grain, the energies per lane
   hipGraphExec_t gexec = nullptr;
-  std::vector<int> graph_parity;   // bc_cur of every grain when the graph was captured
+  qc::BatchGrainDev* g_args = nullptr;
+  std::vector<int> graph_parity;
   int graph_epl = 0;
   int64_t steps_per_iter = 0;
   double last_ms = 0.0;
@@ -2743,7 +2747,7 @@ void build_tiles(qc_batch* b) {
 }
 
 // per-grain arguments of the next sweep (each grain's current store parity)
-void upload_args(qc_batch* b, hipStream_t st) {
+void upload_args(qc_batch* b, qc::BatchGrainDev* args, hipStream_t st) {
   std::vector<qc::BatchGrainDev>& v = b->host_args;
   v.resize(b->grains.size());
   for (size_t gi = 0; gi < b->grains.size(); ++gi) {
@@ -2767,31 +2771,30 @@ void upload_args(qc_batch* b, hipStream_t st) {
     v[gi].cells = g->ncomp == 1 ? g->cells : nullptr;
     v[gi].ra = back_args(g, b->delta[gi], b->delta[gi], g->jcur, nullptr);
   }
-  hcheck(hipMemcpyAsync(b->d_args, v.data(), sizeof(qc::BatchGrainDev) * v.size(), hipMemcpyHostToDevice, st),
-         "H2D");
+  hcheck(hipMemcpyAsync(args, v.data(), sizeof(qc::BatchGrainDev) * v.size(), hipMemcpyHostToDevice, st), "H2D");
   hcheck(hipStreamSynchronize(st), "sync");  // the host block is reused by the next upload
 }
 
 // one Picard iteration (alpha = 1) of every grain: interpolation, one
 // persistent sweep over all grains, rotate-back with the step of Delta, and
 // per grain with screening the A-solve and the step of A (without, A is zero
-// and stays zero).  Only kernel launches: it can be captured into a graph.
-void batch_iteration(qc_batch* b, hipStream_t st, bool upload) {
-  if (upload) upload_args(b, st);
+// and stays zero).  args: the uploaded arguments.  Only kernel launches: it
+// can be captured into a graph.
+void batch_iteration(qc_batch* b, const qc::BatchGrainDev* args, hipStream_t st) {
   const bool mixed = b->precision == QC_MIXED;
   const auto pass = [&](int k) { return b->d_tiles + b->pass_off[k]; };
   (mixed ? qc::launch_batch_interp<float> : qc::launch_batch_interp<double>)(
-      b->d_args, pass(0), b->pass_n[0], pass(1), b->pass_n[1], b->d_counter, st);
+      args, pass(0), b->pass_n[0], pass(1), b->pass_n[1], b->d_counter, st);
   for (size_t k = 0; k < b->grp_epl.size(); ++k) {
     if (mixed)
-      qc::launch_batch_sweep<float>(b->grp_epl[k], b->d_args, b->d_tiles + b->grp_off[k], b->grp_n[k],
+      qc::launch_batch_sweep<float>(b->grp_epl[k], args, b->d_tiles + b->grp_off[k], b->grp_n[k],
                                     b->d_counter + k, b->nblocks, b->spill, b->wave_elems, st);
     else
-      qc::launch_batch_sweep<double>(b->grp_epl[k], b->d_args, b->d_tiles + b->grp_off[k], b->grp_n[k],
+      qc::launch_batch_sweep<double>(b->grp_epl[k], args, b->d_tiles + b->grp_off[k], b->grp_n[k],
                                      b->d_counter + k, b->nblocks, b->spill, b->wave_elems, st);
   }
-  qc::launch_batch_back(false, b->d_args, pass(2), b->pass_n[2], st);
-  qc::launch_batch_back(true, b->d_args, pass(3), b->pass_n[3], st);
+  qc::launch_batch_back(false, args, pass(2), b->pass_n[2], st);
+  qc::launch_batch_back(true, args, pass(3), b->pass_n[3], st);
   for (size_t gi = 0; gi < b->grains.size(); ++gi) {
     qc_grain* g = b->grains[gi];
     if (g->kappa > 0.0) {
@@ -2808,6 +2811,8 @@ void batch_iteration(qc_batch* b, hipStream_t st, bool upload) {
 void drop_graph(qc_batch* b) {
   if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
   b->gexec = nullptr;
+  if (b->g_args) (void)hipFree(b->g_args);
+  b->g_args = nullptr;
   b->graph_parity.clear();
 }
 
@@ -2940,43 +2945,36 @@ qc_status qc_batch_iterate(qc_batch* b, int n_iter, int use_graph, void* stream)
     // the first sweep of a fresh grain starts from bulk roots: run it eagerly
     bool fresh = false;
     for (qc_grain* g : b->grains) fresh = fresh || !g->bc_valid;
-    if (fresh && left > 0) {
-      batch_iteration(b, st, true);
+    const auto eager = [&]() {
+      upload_args(b, b->d_args, st);
+      batch_iteration(b, b->d_args, st);
       --left;
-    }
+    };
+    if (fresh && left > 0) eager();
     if (use_graph && left >= 2) {
       std::vector<int> par;
       for (qc_grain* g : b->grains) par.push_back(g->bc_cur);
       if (!b->gexec || par != b->graph_parity || b->graph_epl != b->epl) {
+        hcheck(hipStreamSynchronize(st), "sync");
         drop_graph(b);
         // the graph holds two iterations (both store parities); the argument
         // blocks are baked per parity into two device copies
-        hcheck(hipStreamSynchronize(st), "sync");
-        qc::BatchGrainDev* saved = b->d_args;
-        qc::BatchGrainDev* args2 =
-            static_cast<qc::BatchGrainDev*>(dalloc(sizeof(qc::BatchGrainDev) * 2 * b->grains.size()));
-        b->d_args = args2;
-        upload_args(b, st);
-        for (qc_grain* g : b->grains) g->bc_cur = 1 - g->bc_cur;
-        b->d_args = args2 + b->grains.size();
-        upload_args(b, st);
-        for (qc_grain* g : b->grains) g->bc_cur = 1 - g->bc_cur;
-        hcheck(hipStreamSynchronize(st), "sync");
+        const size_t n = b->grains.size();
+        b->g_args = static_cast<qc::BatchGrainDev*>(dalloc(sizeof(qc::BatchGrainDev) * 2 * n));
+        for (int half = 0; half < 2; ++half) {
+          upload_args(b, b->g_args + half * n, st);
+          for (qc_grain* g : b->grains) g->bc_cur = 1 - g->bc_cur;
+        }
         hipStream_t cs;
         hcheck(hipStreamCreate(&cs), "stream");
         hipGraph_t graph;
         hcheck(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "capture");
-        b->d_args = args2;
-        batch_iteration(b, cs, false);
-        b->d_args = args2 + b->grains.size();
-        batch_iteration(b, cs, false);
+        // (two flips of the parities: back where they started)
+        for (int half = 0; half < 2; ++half) batch_iteration(b, b->g_args + half * n, cs);
         hcheck(hipStreamEndCapture(cs, &graph), "capture");
-        // the capture flipped the parities twice: back where it started
         hcheck(hipGraphInstantiate(&b->gexec, graph, nullptr, nullptr, 0), "instantiate");
         (void)hipGraphDestroy(graph);
         (void)hipStreamDestroy(cs);
-        if (saved) (void)hipFree(saved);
-        b->d_args = args2;  // kept alive for the graph (first half; second half follows)
         b->graph_parity = par;
         b->graph_epl = b->epl;
       }
@@ -2985,16 +2983,7 @@ qc_status qc_batch_iterate(qc_batch* b, int n_iter, int use_graph, void* stream)
         left -= 2;
       }
     }
-    while (left > 0) {
-      if (b->gexec) {
-        // eager iterations must not overwrite the graph's argument blocks
-        drop_graph(b);
-        (void)hipFree(b->d_args);
-        b->d_args = static_cast<qc::BatchGrainDev*>(dalloc(sizeof(qc::BatchGrainDev) * b->grains.size()));
-      }
-      batch_iteration(b, st, true);
-      --left;
-    }
+    while (left > 0) eager();
     hcheck(hipEventRecord(e1, st), "event");
     hcheck(hipEventSynchronize(e1), "event");
     float ms = 0.f;
