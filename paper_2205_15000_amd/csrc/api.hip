@@ -383,6 +383,7 @@ struct qc_grain {
   // eigenvectors [a_nmodes][nx], masked current and per-mode products
   double a_eps = 0.0;
   int a_nmodes = 0;
+  int64_t a_changes = 0;  // times the solver was set
   double* a_lam = nullptr;
   double* a_vk = nullptr;
   double* a_jp = nullptr;
@@ -1603,6 +1604,7 @@ qc_status qc_grain_set_A_solver(qc_grain* g, double eps) {
       }
     g->a_nmodes = 0;
     g->a_eps = eps;
+    ++g->a_changes;  // (captured graphs hold the old solver's buffers)
     if (eps == 0.0) return QC_OK;
     const int n = g->nx;
     std::vector<double> G(static_cast<size_t>(n) * n);
@@ -2621,11 +2623,12 @@ struct qc_batch {
   int* d_counter = nullptr;  // one tile counter per group
   hipStream_t own = nullptr;
   // a captured graph of two iterations, argument blocks of its own ([2][n],
-  // one for each store parity), and what it was captured with: bc_cur of every
-  // grain, the energies per lane
+  // one for each store parity), and what it was captured with: bc_cur and the
+  // A-solver of every grain, the energies per lane
   hipGraphExec_t gexec = nullptr;
   qc::BatchGrainDev* g_args = nullptr;
   std::vector<int> graph_parity;
+  std::vector<int64_t> graph_solver;
   int graph_epl = 0;
   int64_t steps_per_iter = 0;
   double last_ms = 0.0;
@@ -2953,8 +2956,12 @@ qc_status qc_batch_iterate(qc_batch* b, int n_iter, int use_graph, void* stream)
     if (fresh && left > 0) eager();
     if (use_graph && left >= 2) {
       std::vector<int> par;
-      for (qc_grain* g : b->grains) par.push_back(g->bc_cur);
-      if (!b->gexec || par != b->graph_parity || b->graph_epl != b->epl) {
+      std::vector<int64_t> solver;
+      for (qc_grain* g : b->grains) {
+        par.push_back(g->bc_cur);
+        solver.push_back(g->a_changes);
+      }
+      if (!b->gexec || par != b->graph_parity || solver != b->graph_solver || b->graph_epl != b->epl) {
         hcheck(hipStreamSynchronize(st), "sync");
         drop_graph(b);
         // the graph holds two iterations (both store parities); the argument
@@ -2976,6 +2983,7 @@ qc_status qc_batch_iterate(qc_batch* b, int n_iter, int use_graph, void* stream)
         (void)hipGraphDestroy(graph);
         (void)hipStreamDestroy(cs);
         b->graph_parity = par;
+        b->graph_solver = solver;
         b->graph_epl = b->epl;
       }
       while (left >= 2) {

@@ -73,3 +73,17 @@ def test_bulk_starts_between_replays():
         _check(ref, b)
     _close(ref, grains, b)
 
+
+def test_another_A_solver_between_replays():
+    import paper_2205_15000_amd as qs
+    ref, grains, b = _batch(qs)
+    for eps in (0.0, 1e-6, 1e-2, 0.0, 1e-6):
+        print("case eps %g" % eps, flush=True)
+        for g in (grains[0], ref[0].g):
+            g.set_A_solver(eps)
+        n = 5 if eps == 0.0 else 4
+        b.iterate(n, graph=True)
+        for r in ref:
+            r.iterate(n)
+        _check(ref, b)
+    _close(ref, grains, b)
