@@ -2620,6 +2620,7 @@ struct qc_batch {
   int pass_off[4] = {0, 0, 0, 0}, pass_n[4] = {0, 0, 0, 0};
   int shape = 0;             // energies per lane of the tiles (0: each grain's own)
   std::vector<char> paired;  // the grains' pairing that the tiles were built for
+  bool tiled = false;        // tiles and spill are whole (not after a failed build_tiles)
   int* d_counter = nullptr;  // one tile counter per group
   hipStream_t own = nullptr;
   // a captured graph of two iterations, argument blocks of its own ([2][n],
@@ -2679,6 +2680,7 @@ int auto_batch_epl(const qc_batch* b) {
 }
 
 void build_tiles(qc_batch* b) {
+  b->tiled = false;
   b->shape = b->epl != 0 ? b->epl : auto_batch_epl(b);
   struct T3 {
     int g, w0, cost;
@@ -2747,6 +2749,7 @@ void build_tiles(qc_batch* b) {
     b->spill = dalloc(need);
     b->spill_bytes = need;
   }
+  b->tiled = true;
 }
 
 // per-grain arguments of the next sweep (each grain's current store parity)
@@ -2938,13 +2941,15 @@ qc_status qc_batch_iterate(qc_batch* b, int n_iter, int use_graph, void* stream)
     hcheck(hipEventCreate(&e1), "event");
     hcheck(hipEventRecord(e0, st), "event");
     int left = n_iter;
-    // (a grain's pairing may have been switched since the tiles were built)
-    for (size_t gi = 0; gi < b->grains.size(); ++gi)
-      if (b->grains[gi]->pairing != static_cast<bool>(b->paired[gi])) {
-        drop_graph(b);
-        build_tiles(b);
-        break;
-      }
+    // (a grain's pairing may have been switched since the tiles were built, or
+    // building them again may have failed)
+    bool current = b->tiled;
+    for (size_t gi = 0; current && gi < b->grains.size(); ++gi)
+      current = b->grains[gi]->pairing == static_cast<bool>(b->paired[gi]);
+    if (!current) {
+      drop_graph(b);
+      build_tiles(b);
+    }
     // the first sweep of a fresh grain starts from bulk roots: run it eagerly
     bool fresh = false;
     for (qc_grain* g : b->grains) fresh = fresh || !g->bc_valid;
@@ -3014,8 +3019,9 @@ qc_status qc_batch_autotune(qc_batch* b, int iters_per_trial, int* best_epl, voi
   int maxp = 0;
   for (qc_grain* g : b->grains) maxp = std::max(maxp, g->n_poles);
   double best = INFINITY;
-  int arg = b->epl;
-  // 0: every grain its own automatic lane shape (one launch per shape)
+  const int before = b->epl;
+  int arg = before;
+  // 0: the library's choice for the batch
   const int cand[6] = {0, 1, 2, 3, 4, 8};
   for (int e : cand) {
     if (e > 0 && (maxp + e - 1) / e > 64) continue;
@@ -3025,9 +3031,12 @@ qc_status qc_batch_autotune(qc_batch* b, int iters_per_trial, int* best_epl, voi
       build_tiles(b);
       return QC_OK;
     });
-    if (st != QC_OK) return st;
-    st = qc_batch_iterate(b, iters_per_trial, 0, stream);
-    if (st != QC_OK) return st;
+    if (st == QC_OK) st = qc_batch_iterate(b, iters_per_trial, 0, stream);
+    if (st != QC_OK) {  // the shape of before; its tiles at the next iteration
+      b->epl = before;
+      b->tiled = false;
+      return st;
+    }
     if (b->last_ms < best) {
       best = b->last_ms;
       arg = e;

@@ -50,3 +50,34 @@ def test_grain_tables_take_the_place_of_idle_work_memory():
     # the first grain maps its work memory again
     assert torch.equal(g.ldos(d, a, en, 0.03, 1), out)
     g.close()
+
+
+def test_batch_after_an_autotune_that_ran_out_of_memory():
+    """Three energies per lane need 2.5 GB of spill, more than there is: the
+    autotuner fails, and the batch iterates as one that was never tuned."""
+    import paper_2205_15000_amd as qs
+    sp = wl.spec("d_disc_200")
+    d = torch.as_tensor(wl.initial_delta("d_disc_200", sp)).cuda()
+    a = torch.as_tensor(wl.initial_A("d_disc_200", sp)).cuda()
+    out = []
+    for tune in (False, True):
+        g = qs.Grain(sp, "fp64")
+        b = qs.Batch([g])
+        b.set_fields(0, d, a)
+        b.iterate(1, graph=False)
+        if tune:
+            full = _fill(300 * MIB)
+            try:
+                with pytest.raises(qs.QcError, match="memory"):
+                    b.autotune(1)
+            finally:
+                del full
+                torch.cuda.empty_cache()
+            assert b.info()["energies_per_lane"] == 0
+        b.set_fields(0, d, a)
+        g.reset_bc()
+        b.iterate(3, graph=True)
+        out.append(b.get_fields(0)[0])
+        b.close()
+        g.close()
+    assert torch.equal(out[0], out[1])
