@@ -2340,6 +2340,9 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     // threads of the reverse kernel: two waves per 64/G segments
     const int64_t nthr = 2 * (((pair ? g->nseg_pair : g->nseg) * G + 63) / 64 * 64);
     if (g->adj_ck == 0) {
+      // (gamma goes where the forward sweep spills, which a grain whose sweeps
+      // are batched or allocation-free does not have yet)
+      if (!g->gbuf) g->gbuf = dalloc(nb);
       if (!g->gtbuf) g->gtbuf = dalloc(nb);
     } else {
       const int ck = g->adj_ck;
