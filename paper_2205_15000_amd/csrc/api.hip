@@ -2204,11 +2204,20 @@ Csr to_csr(int64_t nrows, const std::vector<int64_t>& row, const std::vector<int
   return c;
 }
 
+// a table in place of an earlier one
+template <typename V>
+void upload_to(V*& p, const std::vector<V>& v) {
+  if (p) (void)hipFree(p);
+  p = nullptr;
+  p = static_cast<V*>(upload(v));
+}
+
 // The adjoint's transposed tables, built on the host from the device tables
 // the forward path uses: rotate-back entries by slot, interpolation entries
-// (the same stencil code as the device) by cell.
+// (the same stencil code as the device) by cell.  The last one uploaded says
+// that all are there (an upload may have failed in an earlier call).
 void ensure_adjoint_tables(qc_grain* g) {
-  if (g->bt_ptr) return;
+  if (g->it_aw) return;
   {
     const size_t n = static_cast<size_t>(g->n_theta) * 4 * g->ncg;
     const std::vector<int32_t> idx = download(g->rb_idx, n);
@@ -2223,9 +2232,9 @@ void ensure_adjoint_tables(qc_grain* g) {
       ww.push_back(w[o]);
     }
     const Csr c = to_csr(g->nslot, row, col, ww);
-    g->bt_ptr = static_cast<int64_t*>(upload(c.ptr));
-    g->bt_c = static_cast<int32_t*>(upload(c.col));
-    g->bt_w = static_cast<double*>(upload(c.w));
+    upload_to(g->bt_ptr, c.ptr);
+    upload_to(g->bt_c, c.col);
+    upload_to(g->bt_w, c.w);
   }
   const std::vector<double> px = download(g->slot_px, g->nslot), py = download(g->slot_py, g->nslot);
   const std::vector<int32_t> fb = download(g->slot_fb, g->nslot);
@@ -2257,12 +2266,12 @@ void ensure_adjoint_tables(qc_grain* g) {
   }
   const Csr d = to_csr(g->ncell, drow, dcol, dw);
   const Csr a = to_csr(g->ncell, arow, acol, aw);
-  g->it_dptr = static_cast<int64_t*>(upload(d.ptr));
-  g->it_ds = static_cast<int32_t*>(upload(d.col));
-  g->it_dw = static_cast<double*>(upload(d.w));
-  g->it_aptr = static_cast<int64_t*>(upload(a.ptr));
-  g->it_as = static_cast<int32_t*>(upload(a.col));
-  g->it_aw = static_cast<double*>(upload(a.w));
+  upload_to(g->it_dptr, d.ptr);
+  upload_to(g->it_ds, d.col);
+  upload_to(g->it_dw, d.w);
+  upload_to(g->it_aptr, a.ptr);
+  upload_to(g->it_as, a.col);
+  upload_to(g->it_aw, a.w);
 }
 
 // The transposed rotate-back for the paired reverse mode.  A corner of an
@@ -2272,7 +2281,7 @@ void ensure_adjoint_tables(qc_grain* g) {
 // sign), are those of a corner of angle k, so the entry moves onto the
 // mirror slot with its weight.
 void ensure_adjoint_pair_tables(qc_grain* g) {
-  if (g->btp_ptr || !g->pair_ok) return;
+  if (g->btp_w || !g->pair_ok) return;
   const int64_t nc = g->ncg;
   const int n2 = g->n_theta / 2;
   const size_t n = static_cast<size_t>(g->n_theta) * 4 * nc;
@@ -2314,9 +2323,9 @@ void ensure_adjoint_pair_tables(qc_grain* g) {
   };
   if (!g->itp_dend) g->itp_dend = lower_ends(g->it_dptr, g->it_ds);
   if (!g->itp_aend) g->itp_aend = lower_ends(g->it_aptr, g->it_as);
-  g->btp_ptr = static_cast<int64_t*>(upload(c.ptr));
-  g->btp_c = static_cast<int32_t*>(upload(c.col));
-  g->btp_w = static_cast<double*>(upload(c.w));
+  upload_to(g->btp_ptr, c.ptr);
+  upload_to(g->btp_c, c.col);
+  upload_to(g->btp_w, c.w);
 }
 
 }  // namespace
@@ -2351,9 +2360,12 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
         const std::vector<int32_t> n = download(g->seg_n, g->nseg);
         std::vector<int64_t> base(g->nseg + 1, 0);
         for (int64_t sg = 0; sg < g->nseg; ++sg) base[sg + 1] = base[sg] + (n[sg] + ck - 1) / ck;
-        for (void* p : {static_cast<void*>(g->ckbase), g->ckg, g->ckgt})
-          if (p) (void)hipFree(p);
-        g->ckbase = static_cast<int64_t*>(upload(base));
+        g->ck_built = 0;  // (until all three are there)
+        for (void** p : {&g->ckg, &g->ckgt}) {
+          if (*p) (void)hipFree(*p);
+          *p = nullptr;
+        }
+        upload_to(g->ckbase, base);
         const size_t cbytes = sizeof(double) * 2 * std::max<int64_t>(base[g->nseg], 1) * g->n_poles;
         g->ckg = dalloc(cbytes);
         g->ckgt = dalloc(cbytes);

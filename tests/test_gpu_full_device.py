@@ -81,3 +81,38 @@ def test_batch_after_an_autotune_that_ran_out_of_memory():
         b.close()
         g.close()
     assert torch.equal(out[0], out[1])
+
+
+def test_reverse_mode_after_calls_that_ran_out_of_memory():
+    """Its tables and buffers take about 1 GB. Calls that find less free, from
+    nearly nothing on, fail or not; the call with enough memory afterwards
+    gives what a grain that never failed gives (the same kernels: 1e-13)."""
+    import paper_2205_15000_amd as qs
+    sp = wl.spec("d_disc_200")
+    d = torch.as_tensor(wl.initial_delta("d_disc_200", sp)).cuda()
+    a = torch.as_tensor(wl.initial_A("d_disc_200", sp)).cuda()
+    gj = torch.randn(a.shape, dtype=a.dtype, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    ref, g = qs.Grain(sp, "fp64"), qs.Grain(sp, "fp64")
+    ref.sweep(d, a)
+    want = ref.sweep_adjoint(d, a, d, gj, 0.2)
+    ref.close()
+    g.sweep(d, a)
+    failed = 0
+    for mib, every in ((80, 32), (350, 32), (500, 32), (520, 7), (560, 32), (100, 7)):
+        full = _fill(mib * MIB)
+        g.set_adjoint_checkpoint(every)
+        try:
+            g.sweep_adjoint(d, a, d, gj, 0.2)
+        except qs.QcError as e:
+            assert "memory" in str(e)
+            failed += 1
+        finally:
+            torch.cuda.synchronize()
+            del full
+            torch.cuda.empty_cache()
+    assert failed >= 3, failed
+    g.set_adjoint_checkpoint(32)
+    got = g.sweep_adjoint(d, a, d, gj, 0.2)
+    for p, q in zip(got, want):
+        assert (p - q).abs().max() <= 1e-13 * q.abs().max()
+    g.close()
