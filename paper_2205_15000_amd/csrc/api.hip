@@ -2181,14 +2181,15 @@ std::vector<T> download(const T* d, size_t n) {
 }
 
 // Compressed rows from (row, column, weight) triples given row by row in
-// any order: counting sort by row, entries of a row in input order.
+// any order: counting sort by row, entries of a row in input order.  mid: the
+// end of each row's entries among the first `half` given.
 struct Csr {
-  std::vector<int64_t> ptr;
+  std::vector<int64_t> ptr, mid;
   std::vector<int32_t> col;
   std::vector<double> w;
 };
 Csr to_csr(int64_t nrows, const std::vector<int64_t>& row, const std::vector<int32_t>& col,
-           const std::vector<double>& w) {
+           const std::vector<double>& w, size_t half = 0) {
   Csr c;
   c.ptr.assign(nrows + 1, 0);
   for (int64_t r : row) ++c.ptr[r + 1];
@@ -2196,11 +2197,16 @@ Csr to_csr(int64_t nrows, const std::vector<int64_t>& row, const std::vector<int
   c.col.resize(row.size());
   c.w.resize(row.size());
   std::vector<int64_t> pos(c.ptr.begin(), c.ptr.end() - 1);
-  for (size_t e = 0; e < row.size(); ++e) {
-    const int64_t p = pos[row[e]]++;
-    c.col[p] = col[e];
-    c.w[p] = w[e];
-  }
+  const auto place = [&](size_t e0, size_t e1) {
+    for (size_t e = e0; e < e1; ++e) {
+      const int64_t p = pos[row[e]]++;
+      c.col[p] = col[e];
+      c.w[p] = w[e];
+    }
+  };
+  place(0, half);
+  if (half > 0) c.mid = pos;
+  place(half, row.size());
   return c;
 }
 
@@ -2246,7 +2252,13 @@ void ensure_adjoint_tables(qc_grain* g) {
   std::vector<double> dw, aw;
   drow.reserve(4 * g->nslot);
   arow.reserve(4 * g->nslot);
+  // the paired reverse mode stops at the upper angles' slots, which come last
+  size_t dlow = 0, alow = 0;
   for (int64_t s = 0; s < g->nslot; ++s) {
+    if (g->pair_ok && s == g->nslot_pair) {
+      dlow = drow.size();
+      alow = arow.size();
+    }
     int di[4], ai[4];
     double dwt[4], awt[4];
     qc::delta_stencil(gg, px[s], py[s], fb[s], di, dwt);
@@ -2264,8 +2276,10 @@ void ensure_adjoint_tables(qc_grain* g) {
       }
     }
   }
-  const Csr d = to_csr(g->ncell, drow, dcol, dw);
-  const Csr a = to_csr(g->ncell, arow, acol, aw);
+  const Csr d = to_csr(g->ncell, drow, dcol, dw, dlow);
+  const Csr a = to_csr(g->ncell, arow, acol, aw, alow);
+  upload_to(g->itp_dend, d.mid);
+  upload_to(g->itp_aend, a.mid);
   upload_to(g->it_dptr, d.ptr);
   upload_to(g->it_ds, d.col);
   upload_to(g->it_dw, d.w);
@@ -2312,17 +2326,6 @@ void ensure_adjoint_pair_tables(qc_grain* g) {
     ww.push_back(w[o]);
   }
   const Csr c = to_csr(g->nslot, row, col, ww);
-  // first entry of a cell that belongs to an upper angle's slot
-  auto lower_ends = [&](const int64_t* dptr, const int32_t* dcol) {
-    const std::vector<int64_t> ptr = download(dptr, g->ncell + 1);
-    const std::vector<int32_t> col = download(dcol, static_cast<size_t>(ptr[g->ncell]));
-    std::vector<int64_t> end(static_cast<size_t>(g->ncell));
-    for (int64_t i = 0; i < g->ncell; ++i)
-      end[i] = std::lower_bound(col.begin() + ptr[i], col.begin() + ptr[i + 1], g->nslot_pair) - col.begin();
-    return static_cast<int64_t*>(upload(end));
-  };
-  if (!g->itp_dend) g->itp_dend = lower_ends(g->it_dptr, g->it_ds);
-  if (!g->itp_aend) g->itp_aend = lower_ends(g->it_aptr, g->it_as);
   upload_to(g->btp_ptr, c.ptr);
   upload_to(g->btp_c, c.col);
   upload_to(g->btp_w, c.w);
