@@ -411,7 +411,8 @@ qc_status qc_grain_get_accel_stats(const qc_grain* grain, int64_t* bisected, int
  * of all energies, marches and densities of a block of them) stays with the
  * grain after the call, up to a sixteenth of the device's memory over all
  * grains; it is given back when the grain is destroyed or when another
- * allocation of the library on the device fails without it.
+ * allocation of the library on the device fails without it.  (Allocations
+ * of others on the device, such as PyTorch's, do not bring it back.)
  *   energies host double [n_e]
  *   ldos_out device double [n_e][ny][nx] (0 off-grain) */
 qc_status qc_ldos(qc_grain* grain, const double* delta, const double* A_ind,

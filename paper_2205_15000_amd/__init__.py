@@ -578,7 +578,7 @@ class Grain:
 
     def set_adjoint_checkpoint(self, every):
         """Reverse mode with checkpoints every `every` slots (default 32;
-        0 stores gamma~ and its adjoint terms at every node)."""
+        0 keeps gamma and gamma~ at every node)."""
         _check(lib.qc_grain_set_adjoint_checkpoint(self._g, int(every)))
 
     def set_lanes(self, energies_per_lane):

@@ -292,6 +292,8 @@ struct qc_grain {
   int32_t* tap_e_seg = nullptr;
   double* tap_e_w = nullptr;
   int32_t* grain_cells = nullptr;
+  // rotate-back stencils with their weights, from which the reverse mode's
+  // tables are made (no kernel reads them: the gathers take rb4)
   int32_t* rb_idx = nullptr;
   double* rb_w = nullptr;
   int4* rb4 = nullptr;
@@ -795,8 +797,8 @@ void output_shape(const qc_grain* g, qc::SweepArgs& a) {
 // less than six times takes it for the segments longer than split_frac x the
 // longest, which otherwise finish last, rounded up to whole waves; beyond
 // that the last round weighs too little.  At most a 16th of the segments at
-// four per lane and more (400 x 400 square, mixed: 978 us without, 963 with a
-// 16th, 1018 with a sixth of them wide), a 64th at two per lane, since one
+// four per lane and more (400 x 400 square, mixed, sweeps alone: 978 us without,
+// 963 with a 16th, 1018 with a sixth of them wide), a 64th at two per lane, since one
 // per lane costs more per energy (FP64: 2022 us without, 2026 with a 64th,
 // 2068 with an eighth).  A shape that the caller forced runs as it is for all
 // but these longest ones, also where slots stay empty.
@@ -2039,7 +2041,7 @@ qc_status qc_ldos_converge(qc_grain* g, const double* delta, const double* A_ind
         b.gbuf = lg;
         b.ebuf = le;
         output_shape(g, a);
-      launch_sweep_timed(g, 1, a, b, st);
+        launch_sweep_timed(g, 1, a, b, st);
         cur = 1 - cur;
         if (it > 0)
           hcheck(hipMemcpyAsync(prev, out, sizeof(double) * ne * g->ncell, hipMemcpyDeviceToDevice, st), "copy");
@@ -2398,8 +2400,6 @@ qc_status qc_sweep_adjoint(qc_grain* g, const double* delta, const double* A_ind
     ba.ncomp = g->ncomp;
     ba.n_theta = g->n_theta;
     ba.grain_cells = g->grain_cells;
-    ba.rb_idx = g->rb_idx;
-    ba.rb_w = g->rb_w;
     ba.wk = g->wk;
     ba.cosk = g->cosk;
     ba.sink = g->sink;

@@ -234,9 +234,10 @@ __global__ void __launch_bounds__(256) interp1_kernel(InterpArgs a, const cell4<
 // the serial chain (n + 1 steps instead of 2 n + 2); every second node halves
 // the traffic for half a march more arithmetic (26 of about 90 VALU
 // instructions per node and pole), and the sweep is bound by VALU issue.
-// Measured there: 1.41 -> 0.98 ms mixed, 2.84 -> 2.04 ms FP64; on smaller
+// Measured there: 1.41 -> 0.98 ms mixed, 2.84 -> 2.04 ms FP64 (sweeps alone;
+// 1.05 to 1.09 and 2.10 ms inside iterations, at a lower clock); on smaller
 // grains, which the chain's latency bounds, 565 -> 330 us (200 x 200 disc, 48
-// poles, FP64) and 37 -> 17 us (32 x 32 disc).
+// poles, FP64) and 29 -> 17 us (32 x 32 disc).
 //
 // Per node and pole (Sec. II.A): X = gamma gamma~, g = -i pi (1-X)/(1+X),
 // f = -2 i pi gamma/(1+X), f~ = 2 i pi gamma~/(1+X); the pole sums are
@@ -1107,7 +1108,7 @@ __global__ void __launch_bounds__(256) block_sum_kernel(BlockSumRow r0, BlockSum
 
 // Block partials to pinned host memory, visible there when the stream has been
 // waited for.  A launch: as a copy call these few KB took some 8 us more (sweep of
-// the 32 x 32 disc 59 -> 51 us, ten iterations on 40 x 40 983 -> 819 us).
+// the 32 x 32 disc 59 -> 50 us, ten iterations on 40 x 40 983 -> 850 us).
 __global__ void __launch_bounds__(256) parts_to_host_kernel(const double* __restrict__ part, int n,
                                                             double* __restrict__ host) {
   const int i = blockIdx.x * 256 + threadIdx.x;

@@ -200,8 +200,6 @@ struct BackAdjArgs {
   int64_t ncg, ncell;
   int ncomp, n_theta;
   const int32_t* grain_cells;
-  const int32_t* rb_idx;
-  const double* rb_w;
   const double* wk;
   const double* cosk;
   const double* sink;
@@ -282,9 +280,6 @@ void launch_batch_interp(const BatchGrainDev* grains, const int2* pack, int npac
 void launch_batch_back(bool several, const BatchGrainDev* grains, const int2* tiles, int n, hipStream_t st);
 void launch_batch_set(const double* delta, const double* A, const uint8_t* mask, int64_t ncell, int ncomp,
                       double* delta_out, double* A_out, hipStream_t st);
-// End values of the upper angle of each pair from its mirror segment:
-// gamma_end(s') = conj(gamma~_end(s)), gamma~_end(s') = conj(gamma_end(s))
-// for each (s', s) in pairs, n_e energies per segment (T = float or double)
 // blocks of 256 lanes, each lane writes out[lane]: out holds nblocks * 256 floats
 void launch_valu_rate(int op, float* out, int nblocks, int iters, hipStream_t st);
 template <typename T>
@@ -298,15 +293,15 @@ template <typename T>
 void launch_green_back(const LdosBackArgs& a, const void* ebuf, hipStream_t st);
 void launch_fill(double* p, int64_t n, double v, hipStream_t st);
 void launch_curl(const double* A, double* B, int nx, int ny, double h, hipStream_t st);
-// one block-partial sum: nparts partials of x[i] (mode 0) or x[i]^2 (mode 1)
-// over i < n, gathered through idx when given
+// one block-partial sum: nparts partials over i < n of x[i] (mode 0, gathered
+// through idx when given) or of the square of curl x at cell i (mode 1)
 struct BlockSumRow {
   const double* x;
   const int32_t* idx;
   int64_t n;
   double* part;
-  int mode;       // 0: sum of x, 1: sum of (curl x)^2 over an nx x ny grid
-  int nx, ny;
+  int mode;
+  int nx, ny;     // mode 1: the grid
   double h;
 };
 void launch_parts_to_host(const double* part, int n, double* host, hipStream_t st);
