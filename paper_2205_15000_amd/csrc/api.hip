@@ -2521,9 +2521,8 @@ qc_status qc_grain_get_pairing(const qc_grain* g, int* available, int* enabled, 
     if (!g->pairing) {
       *swept_steps_per_sweep = g->info.steps_per_sweep;
     } else {
-      const std::vector<int32_t> n = download(g->seg_n, g->nseg_pair);
       int64_t s = 0;
-      for (int32_t v : n) s += v + 1;
+      for (int32_t v : g->len_order_pair) s += v + 1;
       *swept_steps_per_sweep = 2 * static_cast<int64_t>(g->n_poles) * s;
     }
   }
